@@ -49,8 +49,8 @@
  *   without a pass over the lattice, so it is reported in the stats output (flag = 1) and the
  *   field is then all zeros.
  * Determinism: fields, sign maps, counts, the statistics (mean and variance come from a
- *   fixed-order reduction) and the binned spectra (tile partials combined in integer
- *   arithmetic, then summed in a fixed order) are bit-reproducible for a given plan (see
+ *   fixed-order reduction) and the binned spectra (tile partials, then their sums, in a fixed
+ *   order) are bit-reproducible for a given plan (see
  *   hu_autotune), also across batch layouts and, under the default plans, across batch sizes.
  */
 #ifndef HUFIELD_H
@@ -184,9 +184,7 @@ int hu_pipeline(hu_dims dims, int32_t batch, const hu_filter* filt, const uint64
  *   earlier in the process; otherwise HU_ERR_TABLES is returned and nothing is enqueued.
  *   Every call on one GPU shares that GPU's array: calls that overlap in time on one GPU (two
  *   streams, two host threads) race on it and corrupt each other's results; order them on one
- *   stream.  The only words that must start at zero (the work counter of the persistent
- *   binning pass) are cleared by the first kernel of every call; everything else a pass reads was
- *   written by an earlier pass of the same call.
+ *   stream.  Everything a pass reads was written by an earlier pass of the same call.
  *   Arguments, outputs and errors otherwise as hu_pipeline. */
 #define HU_NOALLOC_WORK_BYTES ((size_t)128 << 20)
 int hu_pipeline_noalloc(hu_dims dims, int32_t batch, const hu_filter* filt, const uint64_t* seeds, hu_bins bins,
@@ -319,10 +317,8 @@ int hu_pipeline_batch(const hu_job* jobs, int32_t njobs, float near_tol, int32_t
                       size_t work_bytes, void* stream);
 
 /* Plan autotuner.  A plan has 13 entries, each 0 or 1: the tile width of the kernel families
- * rows_r2c, cols_y, cols_filter, rows_c2r, cols_bin (0 the default, 1 half of it), then three
- * schedules (0 the default, 1 the other one): bin_schedule (the +-1 binning pass one tile of one
- * field per workgroup, or persistent with a work counter and the next tile's loads overlapping the
- * binning; default one-per-workgroup in 2D, persistent in 3D), field_placement (the fields of an
+ * rows_r2c, cols_y, cols_filter, rows_c2r, cols_bin (0 the default, 1 half of it), then
+ * bin_schedule (reserved: accepted, without effect), two schedules (0 the default, 1 the other one): field_placement (the fields of an
  * axis-0 tile on consecutive workgroup ids of one XCD, sharing the tile's bin-table slice in its
  * L2, or field-major; default the former in 2D, the latter in 3D) and y_group (the 3D y passes give
  * groups of 16 or of 4 neighbouring tiles to one XCD); last `radix`, the radix lists of the
@@ -332,8 +328,7 @@ int hu_pipeline_batch(const hu_job* jobs, int32_t njobs, float near_tol, int32_t
  * and filter_exchange, the exchange of the axis-0 binning and filter passes: complex values
  * through LDS, or split (real and imaginary parts in two rounds through half the LDS, so more
  * workgroups are resident, at two more barriers per exchange; axis-0 lengths of 192 and more);
- * default the binning pass split in 2D and complex in 3D, the filter pass complex, 1 the other
- * one; last whole_field (2D grids with n_x / 2 in 8 .. 64 and n0 in 16 .. 128, powers of two, whose
+ * default the binning pass split, the filter pass complex, 1 the other one; last whole_field (2D grids with n_x / 2 in 8 .. 64 and n0 in 16 .. 128, powers of two, whose
  * half spectrum and bins fit in one workgroup's LDS): 1 runs the whole path as one kernel, one
  * workgroup per field, the spectrum never leaving LDS (HBM traffic: the outputs only); and plane
  * (3D grids with n_x / 2 in {16, 24, 32, 48, 64} and n_y in {32, 48, 64, 96, 128}): 1 runs the x
@@ -383,7 +378,7 @@ int hu_debug_philox(uint64_t seed, uint64_t first, uint64_t count, uint32_t* wor
  *   toff  [ntiles + 1]: the partials of tile t are toff[t] .. toff[t+1]-1, one per distinct bin
  *   coff  [R A + 2], cpos [M]: the partials of bin k are cpos[coff[k] .. coff[k+1]-1], tile order
  * Each array may be NULL (host arrays).  A tile's partial is the sum over its modes in that bin,
- * combined in integer arithmetic; a spectrum bin is a fixed-order sum of its partials, so the
+ * summed in a fixed order; a spectrum bin is a fixed-order sum of its partials, so the
  * spectra are the same bits on every run. */
 int hu_debug_bin_tables(hu_dims dims, hu_bins bins, int32_t variant, int32_t* sizes, uint16_t* table,
                         uint16_t* ltab, uint32_t* toff, uint32_t* coff, uint32_t* cpos);

@@ -217,7 +217,6 @@ int hu_power_spectrum(hu_dims dims, int32_t batch, const void* x, int32_t dtype,
   if (tb.M > lay.Mp) return HU_ERR_WORKSPACE;
   float2* spec = reinterpret_cast<float2*>(reinterpret_cast<char*>(work) + lay.spec);
   double* parts = reinterpret_cast<double*>(reinterpret_cast<char*>(work) + lay.parts_p);
-  unsigned* queue = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(work) + lay.queue);
   const size_t esz = dtype == HU_F32 ? 4 : 1;
   for (int f0 = 0; f0 < batch; f0 += MAX_CHUNK) {
     const int B = batch - f0 < MAX_CHUNK ? batch - f0 : MAX_CHUNK;
@@ -230,8 +229,6 @@ int hu_power_spectrum(hu_dims dims, int32_t batch, const void* x, int32_t dtype,
     ra.src = reinterpret_cast<const char*>(x) + (size_t)f0 * g.N * esz;
     ra.tw = tw_row;
     ra.tw2 = tw2_row;
-    ra.zero = queue;
-    ra.nzero = NQUEUE;
     uint64_t* c = cnt ? cnt + (long long)f0 * nb : nullptr;
     int fs = 0;
     if (c) ra.fill[fs++] = FillSpan{reinterpret_cast<uint32_t*>(c), reinterpret_cast<const uint32_t*>(geo.counts), 2 * nb};
@@ -249,10 +246,6 @@ int hu_power_spectrum(hu_dims dims, int32_t batch, const void* x, int32_t dtype,
       HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, 0, cy, st); }));
     }
     BinArgs ba{};
-    ba.ntiles = col_tiles(g.n[0], 0, g.Nh / g.n[0]);
-    ba.batch = B;
-    ba.persistent = g.nd == 3 ? 1 : 0;
-    ba.q = ItemQueue{queue + Q_BIN, ba.ntiles * B, 8};
     ba.sc = g.nd == 2 ? col_sched_fields(g.n[0], 0, g.Nh / g.n[0], B) : col_sched(g.n[0], 0, g.Nh / g.n[0], B);
     ba.spec = spec;
     ba.Nh = g.Nhp;

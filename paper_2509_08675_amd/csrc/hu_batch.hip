@@ -391,6 +391,7 @@ int hu_autotune(hu_dims dims, int32_t batch, const hu_bins* bins, const char* ca
     for (int k = 0; k < NPASS && rc == HU_OK; ++k) {
       if (g.nd == 2 && (k == P_COLY || k == P_YGROUP)) continue;
       if (k == P_RADIX && !plan_has_alt(g.n[0]) && !(g.nd == 3 && plan_has_alt(g.n[1]))) continue;
+      if (k == P_BINSCHED) continue;                        // reserved
       if ((k == P_BSPLIT || k == P_FSPLIT) && !split_length(g.n[0])) continue;
       if (k == P_WHOLE && !whole_field_ok(g, nb)) continue;
       if (k == P_PLANE && !plane_ok(g)) continue;

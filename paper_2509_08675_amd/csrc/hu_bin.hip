@@ -9,125 +9,60 @@
 
 namespace hu {
 
-// Persistent (the default in 3D) over the items (tile, field), tile-major, taken from the work counter in chunks: the
-// forward transform of a tile's columns, the per-mode values w |X|^2 into LDS, then (while the next
-// item's columns are already being loaded into the transform's registers) the tile's deterministic
-// bin partials.
+// The forward transform of a tile's columns, the per-mode values w |X|^2 into LDS, and the tile's
+// deterministic bin partials; one tile of one field per workgroup.  A read-only streaming pass, bound
+// by the latency of its phases (three to seven workgroups per CU overlap them).  One workgroup per
+// tile in 3D too: a persistent form over a work counter, which loaded the next tile's columns during
+// the binning, needs 95 and more registers and took 43 us for 24 x 64^3 and 64 us for 16 x 128^3,
+// against 12 and 30 us here.
 template <int L, int V, int RV, bool SPLIT>
 __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_bin(BinArgs a) {
   constexpr int P = Plan<L>::P, E = Plan<L>::E, C = ColTile<L, V>::C, T = ColTile<L, V>::T;
   constexpr int LP = ColTile<L, V>::LP;
   using Rad = typename Plan<L, RV>::fwd;
   constexpr int R1 = RadInfo<Rad>::first, RL = RadInfo<Rad>::last;
-  extern __shared__ float2 lds[];
-  __shared__ int grab[2];
-  float* pw = reinterpret_cast<float*>(lds);
-  int* hx = reinterpret_cast<int*>(reinterpret_cast<char*>(lds) + a.hx_off);
-  unsigned long long* hq = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(lds) + a.hq_off);
-  const int tid = threadIdx.x;
-  const int c = tid % C, p = tid / C;
-  for (int j = tid; j < a.tb.nloc_max; j += T) {
-    hx[j] = HX_EMPTY;
-    hq[j] = 0ull;
-  }
-  int last = 0;
-  float2 v[E];
-  for (;;) {
-    if (tid == 0) {
-      int ch = (a.q.nitems - last) / (2 * (int)gridDim.x);
-      ch = ch < 1 ? 1 : (ch > a.q.chunk_max ? a.q.chunk_max : ch);
-      const int s0 = (int)atomicAdd(a.q.counter, (unsigned)ch);
-      grab[0] = s0;
-      grab[1] = s0 + ch < a.q.nitems ? s0 + ch : a.q.nitems;
-    }
-    __syncthreads();
-    const int i0 = grab[0], i1 = grab[1];
-    if (i0 >= a.q.nitems) break;
-    last = i0;
-    {
-      const int tile = i0 / a.batch, b = i0 - tile * a.batch;
-      col_load<L, R1, P, E>(v, col_io<L>(a.spec + (long long)b * a.Nh, a.Nh, a.gm.inner0, tile * C + c, p));
-    }
-    for (int it = i0; it < i1; ++it) {
-      const int tile = it / a.batch, b = it - tile * a.batch;
-      const int g = tile * C + c;
-      const bool valid = g < a.gm.ncol;
-      fft_run<L, P, E, false, false, RV>(Rad{}, v, col_region<L, V, SPLIT>(lds, c), p, a.tw);
-      const float wm = (valid && col_coord(a.gm, g).wm > 1.5f) ? 2.0f : 1.0f;
-      __syncthreads();                              // the exchange buffer is free from here
-#pragma unroll
-      for (int s = 0; s < E; ++s)
-        pw[c * LP + pw_index(slot_index<L, RL, P>(s, p))] = valid ? wm * (v[s].x * v[s].x + v[s].y * v[s].y) : 0.0f;
-      if (it + 1 < i1) {                            // the next item's columns, in flight during the binning
-        const int tn = (it + 1) / a.batch, bn = it + 1 - tn * a.batch;
-        col_load<L, R1, P, E>(v, col_io<L>(a.spec + (long long)bn * a.Nh, a.Nh, a.gm.inner0, tn * C + c, p));
-      }
-      __syncthreads();
-      tile_bins<L, E, C, LP, T>(pw, hx, hq, a.tb, tile, a.gm.ncol, a.parts + (long long)b * a.tb.M, tid);
-    }
-  }
-}
-
-// One item per workgroup (the default in 2D, where the schedule's XCD mapping puts the fields of a
-// tile on one XCD, which then reads the tile's slice of the bin table once).
-template <int L, int V, int RV, bool SPLIT>
-__global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_bin_tile(BinArgs a) {
-  constexpr int P = Plan<L>::P, E = Plan<L>::E, C = ColTile<L, V>::C, T = ColTile<L, V>::T;
-  constexpr int LP = ColTile<L, V>::LP;
-  using Rad = typename Plan<L, RV>::fwd;
-  constexpr int R1 = RadInfo<Rad>::first, RL = RadInfo<Rad>::last;
-  extern __shared__ float2 lds[];
+  extern __shared__ __align__(16) float2 lds[];
   int b;
   long long tile;
   if (!map_tile(a.sc, b, tile)) return;
   float* pw = reinterpret_cast<float*>(lds);
-  int* hx = reinterpret_cast<int*>(reinterpret_cast<char*>(lds) + a.hx_off);
-  unsigned long long* hq = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(lds) + a.hq_off);
   const int tid = threadIdx.x;
   const int c = tid % C, p = tid / C;
   const int g = (int)tile * C + c;
   const bool valid = g < a.gm.ncol;
   float2 v[E];
   col_load<L, R1, P, E>(v, col_io<L>(a.spec + (long long)b * a.Nh, a.Nh, a.gm.inner0, g, p));
+  const TileBinPre pre = tile_bins_pre<T>(a.tb, (int)tile, tid);
   fft_run<L, P, E, false, false, RV>(Rad{}, v, col_region<L, V, SPLIT>(lds, c), p, a.tw);
   const float wm = (valid && col_coord(a.gm, g).wm > 1.5f) ? 2.0f : 1.0f;
-  for (int j = tid; j < a.tb.nloc_max; j += T) {
-    hx[j] = HX_EMPTY;
-    hq[j] = 0ull;
-  }
   __syncthreads();                                  // the exchange buffer is free from here
 #pragma unroll
   for (int s = 0; s < E; ++s)
     pw[c * LP + pw_index(slot_index<L, RL, P>(s, p))] = valid ? wm * (v[s].x * v[s].x + v[s].y * v[s].y) : 0.0f;
   __syncthreads();
-  tile_bins<L, E, C, LP, T>(pw, hx, hq, a.tb, (int)tile, a.gm.ncol, a.parts + (long long)b * a.tb.M, tid);
+  tile_bins<L, E, C, LP, T, ColTile<L, V>::PWV>(lds, a.tb, pre, (int)tile, a.gm.ncol, a.parts + (long long)b * a.tb.M, tid);
 }
 
 template <int L, int V, int RV, bool SPLIT>
-static hipError_t launch_cols_bin_L(BinArgs a, hipStream_t st) {
+static hipError_t launch_cols_bin_L(const BinArgs& a, hipStream_t st) {
   constexpr int T = ColTile<L, V>::T;
-  if (a.q.nitems <= 0) return hipSuccess;
-  a.hx_off = (int)col_bin_base<L, V, SPLIT>();
-  a.hq_off = a.hx_off + (a.tb.nloc_max * 4 + 15) / 16 * 16;
-  const size_t lds = (size_t)a.hq_off + (size_t)a.tb.nloc_max * 8;
-  if (!a.persistent) {
-    hipLaunchKernelGGL((k_cols_bin_tile<L, V, RV, SPLIT>), dim3(sched_blocks(a.sc)), dim3(T), lds, st, a);
-    return hipGetLastError();
-  }
-  int slots = 0;
-  const hipError_t e = resident_blocks(reinterpret_cast<const void*>(&k_cols_bin<L, V, RV, SPLIT>), T, lds, &slots);
-  if (e != hipSuccess) return e;
-  const unsigned grid = (unsigned)(slots < a.q.nitems ? slots : a.q.nitems);
-  hipLaunchKernelGGL((k_cols_bin<L, V, RV, SPLIT>), dim3(grid), dim3(T), lds, st, a);
+  const size_t lds = col_bin_bytes<L, V, SPLIT>(a.tb);
+  hipLaunchKernelGGL((k_cols_bin<L, V, RV, SPLIT>), dim3(sched_blocks(a.sc)), dim3(T), lds, st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_cols_bin(int L, int variant, const BinArgs& a, hipStream_t st, int radix, int split) {
+// The exchange: split from 64 on, half the LDS, so a third (fourth) workgroup is resident (against the
+// complex exchange 16 x 2048^2 101 -> 88 us, 4 x 256^3 72 -> 65 us, 16 x 128^3 33 -> 30 us, 24 x 64^3
+// the same); `complex_x` takes the complex one where split_length(L)
+hipError_t launch_cols_bin(int L, int variant, const BinArgs& a, hipStream_t st, int radix, int complex_x) {
   switch (L) {
-#define X(LL)                                                                                             \
-  case LL:                                                                                                \
-    return with_choices3<LL>(variant, radix, split, [&](auto v, auto r, auto s) {                         \
-      return launch_cols_bin_L<LL, decltype(v)::value, decltype(r)::value, decltype(s)::value>(a, st);    \
+#define X(LL)                                                                                               \
+  case LL:                                                                                                  \
+    return with_choices<LL>(variant, radix, [&](auto v, auto r) {                                           \
+      constexpr int V = decltype(v)::value, RV = decltype(r)::value;                                        \
+      if constexpr (split_length(LL))                                                                       \
+        if (complex_x) return launch_cols_bin_L<LL, V, RV, false>(a, st);                                   \
+      return launch_cols_bin_L<LL, V, RV, (LL >= 64)>(a, st);                                               \
     });
     HU_COL_LENGTHS(X)
 #undef X

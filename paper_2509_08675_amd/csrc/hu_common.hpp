@@ -64,9 +64,14 @@ struct ColTile {
   // stride.  Narrow tiles (a 16-lane phase spans 4 columns x 4 threads): L + L/16 + 4 complex,
   // i.e. 8 mod 32 words, so the four columns of a phase use disjoint banks.
   static constexpr int RS = C >= 16 ? RegionWide<L>::value : L + (L >> 4) + 4;
-  // padded power-value layout for run-length binning: 4 floats after every 16, and an odd
-  // number of words per column
-  static constexpr int LP = (L + (L / 16) * 4 + 31) / 32 * 32 + 1;
+  // padded power-value layout for run-length binning: 4 floats after every 16; words per column:
+  // wide tiles (a wave writes 32 columns at one e): odd, so that the 32 columns hit distinct banks;
+  // narrow tiles: 4 or 8 mod 32, so that a column starts on 16 bytes (a binning thread then reads its
+  // 16 values as four 16-byte vectors, whose 80-byte stride over the lanes is free of conflicts)
+  // and the lanes of a write (C columns x 32 / C modes) still hit distinct banks
+  static constexpr int LP0 = (L + (L / 16) * 4 + 31) / 32 * 32;
+  static constexpr bool PWV = C <= 16 && Plan<L>::E == 16;      // the four-vector reads
+  static constexpr int LP = PWV ? LP0 + (C <= 4 ? 8 : 4) : LP0 + 1;
   // split exchange (real and imaginary parts in two rounds): floats per column region
   static constexpr int RSH = L + (L >> 4) + split_extra(L, C);
 };
@@ -329,18 +334,11 @@ __device__ __forceinline__ float amp_sym(const FiltDev& f, const Axis0Geom& gm, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Deterministic binning of one tile.  The per-mode power values w |X|^2 of the tile's C columns sit
-// in LDS (padded layout pw_index).  Thread (column cb, segment pb) takes the E consecutive modes
-// e = pb E .. pb E + E - 1 of its column, reads their tile-local bins j (the position of the mode's
-// bin in the tile's ascending list of distinct bins, from the per-geometry table ltab) and sums
-// each run of equal j in FP64 in mode order.  The runs of one bin are combined in integer
-// arithmetic, which does not depend on the order in which the atomics land:
+// Order-independent integer combination of runs of one bin (whole-field kernel, expected spectrum):
 //   pass 1: hx[j] = the largest binary exponent of the bin's runs (integer maximum);
 //   pass 2: hq[j] += each run rounded to a multiple of 2^(hx[j] - 48), as an unsigned integer.
-// A run is below 2^hx[j], so it contributes less than 2^48 units, and a bin of one tile gathers
-// at most T E <= 2^15 runs: the sum stays below 2^63.  The tile's partial of bin j is then
-// hq[j] 2^(hx[j] - 48), the same bits for every schedule of the workgroup; its error is at most
-// 2^-48 of the bin's largest run per run.
+// A run is below 2^hx[j], so it contributes less than 2^48 units, and at most 2^15 of them fit: the
+// sum stays below 2^63.  The bin is then hq[j] 2^(hx[j] - 48), the same bits in any order.
 // ---------------------------------------------------------------------------------------------
 constexpr int HX_EMPTY = -100000;
 constexpr int HQ_SHIFT = 48;
@@ -358,129 +356,132 @@ __device__ __forceinline__ void run_commit(int j, double s, int* hx, unsigned lo
   else atomicAdd(hq + j, run_to_fixed(s, hx[j]));
 }
 
-template <int E, bool PASS2>
-__device__ __forceinline__ void runs_commit(const int (&loc)[E], const float (&v)[E], int* hx,
-                                            unsigned long long* hq) {
-  int cur = loc[0];
+// ---------------------------------------------------------------------------------------------
+// Deterministic binning of one tile.  The per-mode power values w |X|^2 of the tile's C columns sit
+// in LDS (padded layout pw_index).  Thread (column cb, segment pb) takes the E consecutive modes
+// e = pb E .. pb E + E - 1 of its column into registers and, once every thread has, sums each run of
+// equal bin in FP64 in mode order and leaves it in LDS at the next place of its own (the run
+// boundaries are a bit mask per thread, the runs numbered thread by thread: no bin numbers, no
+// atomics).  Then a lane -- for bins of many runs a group of lanes -- adds a bin's runs in the order
+// of the tile's list and stores the partial.  The order is fixed by the tables, so the partials are
+// the same bits for every schedule.  The runs reuse the storage of the power values.  (An integer
+// combination of the runs by LDS atomics, two passes over them, took the binning pass 91 us at
+// 4 x 256^3 and 88 us at 16 x 2048^2; this form 78 and 85-88 us.)
+// ---------------------------------------------------------------------------------------------
+constexpr int LIST_AHEAD = 8;             // list entries of a lane loaded before the runs are complete
+
+template <int N, class V>
+__device__ __forceinline__ void runs_store(const V (&v)[N], uint2 sg, double* runs) {
+  double* r = runs + sg.y;
   double acc = (double)v[0];
 #pragma unroll
-  for (int i = 1; i < E; ++i) {
-    if (loc[i] != cur) {
-      run_commit<PASS2>(cur, acc, hx, hq);
-      cur = loc[i];
+  for (int i = 1; i < N; ++i) {
+    if ((sg.x >> i) & 1u) {
+      *r++ = acc;
       acc = 0.0;
     }
     acc += (double)v[i];
   }
-  run_commit<PASS2>(cur, acc, hx, hq);
+  *r = acc;
 }
 
-// the E tile-local bins and power values of binning thread (cb, pb), all loads issued first
-template <int L, int E>
-__device__ __forceinline__ void seg_read(const float* pwc, const uint16_t* __restrict__ ltab, int g, int pb,
-                                         int (&loc)[E], float (&v)[E]) {
-  const int e0 = pb * E;
-  const uint16_t* t = ltab + (unsigned)(g * L + e0);
-  if constexpr ((L % 8) == 0 && (E % 8) == 0) {
-    uint4 w[E / 8];
-#pragma unroll
-    for (int q = 0; q < E / 8; ++q) w[q] = *reinterpret_cast<const uint4*>(t + 8 * q);
-#pragma unroll
-    for (int q = 0; q < E / 8; ++q) {
-      const uint32_t ws[4] = {w[q].x, w[q].y, w[q].z, w[q].w};
-#pragma unroll
-      for (int h = 0; h < 8; ++h) loc[8 * q + h] = (int)((ws[h >> 1] >> (16 * (h & 1))) & 0xFFFFu);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < E; ++i) loc[i] = (int)t[i];
-  }
-#pragma unroll
-  for (int i = 0; i < E; ++i) v[i] = pwc[pw_index(e0 + i)];
+// The thread's entries of the tile tables, loaded at the start of the kernel: their latency (the slot's
+// place is itself a load) passes behind the transform.
+struct TileBinPre {
+  unsigned list, slot, nslots;
+  uint2 sg, sl;
+};
+
+template <int T>
+__device__ __forceinline__ TileBinPre tile_bins_pre(const TileBinDev& tb, int tile, int tid) {
+  const uint4 info = tb.info[tile];
+  TileBinPre pre;
+  pre.list = info.x;
+  pre.slot = info.y;
+  pre.nslots = info.z;
+  pre.sg = tb.seg[tile * T + tid];
+  pre.sl = (unsigned)tid < pre.nslots ? tb.slot[pre.slot + tid] : make_uint2(0u, ~0u);
+  return pre;
 }
 
-// Radial bins only (sym): the bin of a mode depends on the axis-0 index e only through its square,
-// so e and n0 - e share it.  Thread (cb, pb) then takes the pairs q = pb E/2 .. pb E/2 + E/2 - 1 of
-// its column with the value pw[q] + pw[n0 - q] (pw[q] alone for q = 0), the last thread also
-// q = n0 / 2 (its own partner): half the runs.  Other threads carry an empty last entry.
-template <int L, int E, int P>
-__device__ __forceinline__ void seg_read_sym(const float* pwc, const uint16_t* __restrict__ ltab, int g, int pb,
-                                             int (&loc)[E / 2 + 1], double (&v)[E / 2 + 1]) {
-  constexpr int H = E / 2;
-  const int q0 = pb * H;
-  const uint16_t* t = ltab + (unsigned)(g * L);
-#pragma unroll
-  for (int i = 0; i < H; ++i) loc[i] = (int)t[q0 + i];
-#pragma unroll
-  for (int i = 0; i < H; ++i) {
-    const int q = q0 + i;
-    v[i] = q == 0 ? (double)pwc[pw_index(0)] : (double)pwc[pw_index(q)] + (double)pwc[pw_index(L - q)];
-  }
-  const bool nyq = pb == P - 1;
-  loc[H] = nyq ? (int)t[L / 2] : loc[H - 1];
-  v[H] = nyq ? (double)pwc[pw_index(L / 2)] : 0.0;
-}
-
-template <int N, bool PASS2>
-__device__ __forceinline__ void runs_commit_d(const int (&loc)[N], const double (&v)[N], int* hx,
-                                              unsigned long long* hq) {
-  int cur = loc[0];
-  double acc = v[0];
-#pragma unroll
-  for (int i = 1; i < N; ++i) {
-    if (loc[i] != cur) {
-      run_commit<PASS2>(cur, acc, hx, hq);
-      cur = loc[i];
-      acc = 0.0;
-    }
-    acc += v[i];
-  }
-  run_commit<PASS2>(cur, acc, hx, hq);
-}
-
-// The whole tile: both passes and the stores of the partials (thread j < nloc stores the partial of
-// local bin j at its position wpos[toff[tile] + j] and clears its slots for the next tile).  Called
-// by every thread of the workgroup after the power values are in LDS and a barrier; ends with the
-// LDS histogram cleared, without a final barrier.
-template <int L, int E, int C, int LP, int T>
-__device__ __forceinline__ void tile_bins(const float* pw, int* hx, unsigned long long* hq, const TileBinDev& tb,
-                                          int tile, int ncol, double* __restrict__ out, int tid) {
-  constexpr int P = Plan<L>::P;
+// Called by every thread of the workgroup after the power values are in LDS and a barrier; ends
+// without a barrier (the region is still being read).  Radial bins only (sym): the bin of a mode
+// depends on the axis-0 index e only through its square, so e and n0 - e share it, and thread
+// (cb, pb) takes the pairs q = pb E/2 .. pb E/2 + E/2 - 1 of its column with the value pw[q] + pw[n0 - q]
+// (pw[q] alone for q = 0), the last thread also q = n0 / 2 (its own partner): half the runs.
+template <int L, int E, int C, int LP, int T, bool PWV>
+__device__ __forceinline__ void tile_bins(float2* lds, const TileBinDev& tb, const TileBinPre& pre, int tile, int ncol,
+                                          double* __restrict__ out, int tid) {
+  constexpr int P = Plan<L>::P, H = E / 2;
+  static_assert(E % 2 == 0, "pairs of modes split a thread's E modes in halves");
   const int cb = tid / P, pb = tid - cb * P;
-  const int g = tile * C + cb;
-  const bool act = cb < C && g < ncol;
-  // the tile's partial range and store positions first: their loads overlap the two passes
-  const unsigned j0 = tb.toff[tile];
-  const int nloc = (int)(tb.toff[tile + 1] - j0);
-  const unsigned wp0 = tid < nloc ? tb.wpos[j0 + tid] : 0u;
+  const bool act = cb < C && tile * C + cb < ncol;
+  const float* pwc = reinterpret_cast<const float*>(lds) + cb * LP;
+  double* runs = reinterpret_cast<double*>(lds);
+  const int nslots = (int)pre.nslots;
+  const uint2 sg = pre.sg;
+  uint2 sl = pre.sl;
+  const uint16_t* list = tb.list + pre.list;
+  unsigned idx[LIST_AHEAD];
+  // the first list entries of the lane's slot, on their way while the runs are formed
+  auto ahead = [&]() {
+#pragma unroll
+    for (int q = 0; q < LIST_AHEAD; ++q)
+      idx[q] = (unsigned)q < (sl.x >> 16 & 0x1FFFu) ? (unsigned)list[(sl.x & 0xFFFFu) + ((unsigned)q << (sl.x >> 29))] : 0u;
+  };
+  ahead();
   if (tb.sym) {                                      // uniform over the launch
-    static_assert(E % 2 == 0, "pairs of modes split a thread's E modes in halves");
-    int loc[E / 2 + 1];
-    double v[E / 2 + 1];
+    double v[H + 1];
     if (act) {
-      seg_read_sym<L, E, P>(pw + cb * LP, tb.ltab, g, pb, loc, v);
-      runs_commit_d<E / 2 + 1, false>(loc, v, hx, hq);
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        const int q = pb * H + i;
+        v[i] = q == 0 ? (double)pwc[pw_index(0)] : (double)pwc[pw_index(q)] + (double)pwc[pw_index(L - q)];
+      }
+      v[H] = pb == P - 1 ? (double)pwc[pw_index(L / 2)] : 0.0;
     }
     __syncthreads();
-    if (act) runs_commit_d<E / 2 + 1, true>(loc, v, hx, hq);
-    __syncthreads();
+    if (act) runs_store<H + 1>(v, sg, runs);
   } else {
-    int loc[E];
     float v[E];
     if (act) {
-      seg_read<L, E>(pw + cb * LP, tb.ltab, g, pb, loc, v);
-      runs_commit<E, false>(loc, v, hx, hq);
+      if constexpr (PWV) {
+        const float4* p4 = reinterpret_cast<const float4*>(pwc + pw_index(pb * E));
+#pragma unroll
+        for (int i = 0; i < E / 4; ++i) {
+          const float4 x = p4[i];
+          v[4 * i] = x.x;
+          v[4 * i + 1] = x.y;
+          v[4 * i + 2] = x.z;
+          v[4 * i + 3] = x.w;
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < E; ++i) v[i] = pwc[pw_index(pb * E + i)];
+      }
     }
     __syncthreads();
-    if (act) runs_commit<E, true>(loc, v, hx, hq);
-    __syncthreads();
+    if (act) runs_store<E>(v, sg, runs);
   }
-  for (int j = tid; j < nloc; j += T) {
-    const int e = hx[j];
-    const unsigned long long q = hq[j];
-    out[j == tid ? wp0 : tb.wpos[j0 + j]] = e == HX_EMPTY ? 0.0 : ldexp((double)q, e - HQ_SHIFT);
-    hx[j] = HX_EMPTY;
-    hq[j] = 0ull;
+  __syncthreads();                                   // the runs are complete
+  for (int i = tid; i < nslots;) {                   // uniform over a wave: nslots and T are multiples of 64
+    const unsigned first = sl.x & 0xFFFFu, n = (sl.x >> 16) & 0x1FFFu, lg = sl.x >> 29;
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < LIST_AHEAD; ++q) s += (unsigned)q < n ? runs[idx[q]] : 0.0;
+    for (unsigned q = LIST_AHEAD; q < n; ++q) s += runs[list[first + (q << lg)]];
+    // the slots are sorted by lanes per bin, most first, so the wave's first lane has the largest
+    const int lgw = __builtin_amdgcn_readfirstlane((int)lg);
+    for (int o = 1 << lgw >> 1; o > 0; o >>= 1) {
+      const double t = __shfl_xor(s, o, 64);
+      if (o < (1 << lg)) s += t;
+    }
+    if (sl.y != ~0u) out[sl.y] = s;
+    i += T;
+    if (i < nslots) {
+      sl = tb.slot[pre.slot + i];
+      ahead();
+    }
   }
 }
 
@@ -489,13 +490,14 @@ __host__ __device__ constexpr size_t col_xchg_bytes() {
   return SPLIT ? (size_t)ColTile<L, V>::C * ColTile<L, V>::RSH * 4 : (size_t)ColTile<L, V>::C * ColTile<L, V>::RS * 8;
 }
 
-// LDS of an axis-0 pass that bins: the exchange buffer (the power values reuse it), then the tile
-// histogram (nloc_max exponents and fixed-point sums)
+// LDS of an axis-0 pass that bins: the exchange buffer, which the power values and then the runs
+// reuse
 template <int L, int V, bool SPLIT = false>
-__host__ __device__ constexpr size_t col_bin_base() {
-  return ((col_xchg_bytes<L, V, SPLIT>() > (size_t)ColTile<L, V>::C * ColTile<L, V>::LP * 4
-               ? col_xchg_bytes<L, V, SPLIT>()
-               : (size_t)ColTile<L, V>::C * ColTile<L, V>::LP * 4) + 15) / 16 * 16;
+inline size_t col_bin_bytes(const TileBinDev& tb) {
+  size_t n = col_xchg_bytes<L, V, SPLIT>();
+  const size_t pw = (size_t)ColTile<L, V>::C * ColTile<L, V>::LP * 4, runs = (size_t)tb.runs_max * 8;
+  n = n > pw ? n : pw;
+  return n > runs ? n : runs;
 }
 
 // the exchange region of column c of a tile: complex, or floats for the split exchange

@@ -16,7 +16,7 @@ __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a
   using Rad = typename Plan<L, RV>::fwd;
   using RadI = Reverse<Rad>;
   constexpr int R1 = RadInfo<Rad>::first, RL = RadInfo<Rad>::last;
-  extern __shared__ float2 lds[];
+  extern __shared__ __align__(16) float2 lds[];
   __shared__ double red_d[T / 64], red_d0[T / 64];
   __shared__ float red_f[T / 64];
   int b;
@@ -29,10 +29,11 @@ __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a
   const ColIO io = col_io<L>(a.spec + (long long)b * a.Nh, a.Nh, a.gm.inner0, g, p);
   float2 v[E];
   col_load<L, R1, P, E>(v, io);
+  const bool do_bins = a.parts != nullptr;
+  const TileBinPre pre = do_bins ? tile_bins_pre<T>(a.tb, (int)tile, tid) : TileBinPre{};
   fft_run<L, P, E, false, false, RV>(Rad{}, v, col_region<L, V, SPLIT>(lds, c), p, a.tw);
 
   // ---- filter and per-thread statistics
-  const bool do_bins = a.parts != nullptr;
   const FiltDev filt = a.io ? a.io[b].filt : a.filt;
   const ColCoord cc = col_coord(a.gm, valid ? g : 0);
   Col3 c3a{}, c3b{};
@@ -46,15 +47,7 @@ __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a
   // the exchange buffer is free once every thread has its transform in registers: the power
   // values of the continuous spectrum go to LDS as they are computed
   float* pw = reinterpret_cast<float*>(lds);
-  int* hx = reinterpret_cast<int*>(reinterpret_cast<char*>(lds) + a.hx_off);
-  unsigned long long* hq = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(lds) + a.hq_off);
-  if (do_bins) {
-    for (int j = tid; j < a.tb.nloc_max; j += T) {
-      hx[j] = HX_EMPTY;
-      hq[j] = 0ull;
-    }
-    __syncthreads();
-  }
+  if (do_bins) __syncthreads();
 #pragma unroll
   for (int s = 0; s < E; ++s) {
     const int e = slot_index<L, RL, P>(s, p);
@@ -86,9 +79,9 @@ __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a
     part[2] = (double)lm;
     part[3] = 0.0;
   }
-  // ---- continuous-spectrum bins of the tile -> parts[b][toff[tile] ..] (deterministic)
+  // ---- continuous-spectrum bins of the tile -> its partials in parts[b] (deterministic)
   if (do_bins) {
-    tile_bins<L, E, C, LP, T>(pw, hx, hq, a.tb, (int)tile, a.gm.ncol, a.parts + (long long)b * a.tb.M, tid);
+    tile_bins<L, E, C, LP, T, ColTile<L, V>::PWV>(lds, a.tb, pre, (int)tile, a.gm.ncol, a.parts + (long long)b * a.tb.M, tid);
   }
 
   // ---- inverse transform along axis 0 (first radix = last forward radix: no exchange needed)
@@ -162,11 +155,7 @@ template <int L, int V, int RV, bool SPLIT>
 static hipError_t launch_cols_filter_L(FilterArgs a, hipStream_t st) {
   constexpr int T = ColTile<L, V>::T;
   size_t lds = col_xchg_bytes<L, V, SPLIT>();
-  if (a.parts) {
-    a.hx_off = (int)col_bin_base<L, V, SPLIT>();
-    a.hq_off = a.hx_off + (a.tb.nloc_max * 4 + 15) / 16 * 16;
-    lds = (size_t)a.hq_off + (size_t)a.tb.nloc_max * 8;
-  }
+  if (a.parts) lds = col_bin_bytes<L, V, SPLIT>(a.tb);
   // the tabulated-form and FP64 branches only in the instantiation launched when a field may use one
   const dim3 grid(sched_blocks(a.sc));
   if (a.gm.ndim == 2) {
@@ -182,6 +171,15 @@ static hipError_t launch_cols_filter_L(FilterArgs a, hipStream_t st) {
 int col_width(int L, int variant) {
   switch (L) {
 #define X(LL) case LL: return variant ? ColTile<LL, 1>::C : ColTile<LL, 0>::C;
+    HU_COL_LENGTHS(X)
+#undef X
+    default: return 0;
+  }
+}
+
+int col_elems(int L) {
+  switch (L) {
+#define X(LL) case LL: return Plan<LL>::E;
     HU_COL_LENGTHS(X)
 #undef X
     default: return 0;

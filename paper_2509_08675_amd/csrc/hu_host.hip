@@ -31,6 +31,11 @@ struct TileHost {
   std::vector<uint16_t> ltab;                  // [ncol][n0]: position in the tile's list of distinct bins
   std::vector<uint32_t> toff, coff, cpos, wpos;   // wpos: the inverse of cpos
   int nloc_max = 0;
+  // the device tables of TileBinDev
+  std::vector<uint2> seg, slot;
+  std::vector<uint4> info;
+  std::vector<uint16_t> list;
+  int runs_max = 0;
 };
 std::map<std::vector<long long>, std::shared_ptr<BinHost>> g_binhost;    // {nd, n0, n1, n2, nr, na}
 std::map<std::vector<long long>, std::shared_ptr<TileHost>> g_tilehost;  // ... + C
@@ -417,8 +422,6 @@ int layout(const Geom& g, int batch, bool need_stats, const TunePlan& plan, cons
     L.parts_p = off;
     off += up256((size_t)batch * M * sizeof(double));
   }
-  L.queue = off;
-  off += up256(NQUEUE * sizeof(unsigned));
   L.total = off;
   *out = L;
   return HU_OK;
@@ -614,6 +617,65 @@ std::shared_ptr<BinHost> bin_host(const Geom& g, const hu_bins& bins) {
   return g_binhost.emplace(key, h).first->second;
 }
 
+// The runs of the binning threads, the lists of each bin's runs and the summing lanes of every tile
+// (TileBinDev).  A bin of n runs gets the smallest power of two of lanes, at most a wave, that leaves
+// a lane no more than LANE_RUNS of them.
+void tile_runs(const Axis0Geom& a, int C, bool sym, TileHost* th) {
+  constexpr int LANE_RUNS = 8;
+  const int E = col_elems(a.n0), P = a.n0 / E, T = C * P, H = E / 2;
+  const int ntiles = (int)th->toff.size() - 1;
+  th->seg.assign((size_t)ntiles * T, make_uint2(0u, 0u));
+  th->info.resize(ntiles);
+  std::vector<int> rbin, cnt, off;
+  for (int t = 0; t < ntiles; ++t) {
+    const int nloc = (int)(th->toff[t + 1] - th->toff[t]);
+    rbin.clear();
+    for (int cb = 0; cb < C && t * C + cb < a.ncol; ++cb) {
+      const uint16_t* col = th->ltab.data() + (size_t)(t * C + cb) * a.n0;
+      for (int pb = 0; pb < P; ++pb) {
+        const uint16_t* e = col + pb * (sym ? H : E);
+        const int n = sym ? H : E;
+        uint2& sg = th->seg[(size_t)t * T + cb * P + pb];
+        sg.y = (uint32_t)rbin.size();
+        rbin.push_back(e[0]);
+        for (int i = 1; i < n; ++i)
+          if (e[i] != e[i - 1]) {
+            sg.x |= 1u << i;
+            rbin.push_back(e[i]);
+          }
+        if (sym && pb == P - 1 && col[a.n0 / 2] != e[n - 1]) {
+          sg.x |= 1u << n;
+          rbin.push_back(col[a.n0 / 2]);
+        }
+      }
+    }
+    const int nr = (int)rbin.size();
+    th->runs_max = std::max(th->runs_max, nr);
+    cnt.assign(nloc, 0);
+    off.assign(nloc + 1, 0);
+    for (int r = 0; r < nr; ++r) cnt[rbin[r]]++;
+    for (int j = 0; j < nloc; ++j) off[j + 1] = off[j] + cnt[j];
+    const size_t l0 = th->list.size(), s0 = th->slot.size();
+    th->list.resize(l0 + nr);
+    std::vector<int> cur(off.begin(), off.end() - 1);
+    for (int r = 0; r < nr; ++r) th->list[l0 + cur[rbin[r]]++] = (uint16_t)r;
+    for (int lg = 6; lg >= 0; --lg)
+      for (int j = 0; j < nloc; ++j) {
+        int need = 0;
+        while (need < 6 && cnt[j] > (LANE_RUNS << need)) ++need;
+        if (need != lg) continue;
+        const int G = 1 << lg;
+        for (int u = 0; u < G; ++u) {
+          const int n = cnt[j] > u ? (cnt[j] - u + G - 1) / G : 0;
+          th->slot.push_back(make_uint2((uint32_t)(off[j] + u) | (uint32_t)n << 16 | (uint32_t)lg << 29,
+                                        u == 0 ? th->wpos[th->toff[t] + j] : ~0u));
+        }
+      }
+    while ((th->slot.size() - s0) % 64) th->slot.push_back(make_uint2(0u, ~0u));
+    th->info[t] = make_uint4((uint32_t)l0, (uint32_t)s0, (uint32_t)(th->slot.size() - s0), 0u);
+  }
+}
+
 // Tile tables for tiles of C columns: for tile t, its distinct bins in ascending order (their
 // partials occupy [toff[t], toff[t + 1])), each mode's position in that list, and per bin the
 // partial positions in tile order (CSR).
@@ -660,6 +722,7 @@ std::shared_ptr<TileHost> tile_host(const Geom& g, const hu_bins& bins, int C) {
   for (size_t i = 0; i < pbin.size(); ++i) th->cpos[cur[pbin[i]]++] = (uint32_t)i;
   th->wpos.resize(pbin.size());
   for (size_t k = 0; k < pbin.size(); ++k) th->wpos[th->cpos[k]] = (uint32_t)k;
+  tile_runs(a, C, bins.n_angular == 1, th.get());
   std::lock_guard<std::mutex> lk(g_mu);
   return g_tilehost.emplace(key, th).first->second;
 }
@@ -722,20 +785,21 @@ int get_tilebins(const Geom& g, const hu_bins& bins, int C, TileBinDev* out) {
   }
   if (C < 1) return HU_ERR_SIZE;
   const std::shared_ptr<TileHost> th = tile_host(g, bins, C);
-  uint16_t* ltab = nullptr;
-  uint32_t *toff = nullptr, *coff = nullptr, *wpos = nullptr;
-  HU_TRY(upload(th->ltab, &ltab));
-  HU_TRY(upload(th->toff, &toff));
-  HU_TRY(upload(th->wpos, &wpos));
+  uint2 *seg = nullptr, *slot = nullptr;
+  uint4* info = nullptr;
+  uint16_t* list = nullptr;
+  uint32_t* coff = nullptr;
+  HU_TRY(upload(th->seg, &seg));
+  HU_TRY(upload(th->slot, &slot));
+  HU_TRY(upload(th->info, &info));
+  HU_TRY(upload(th->list, &list));
   HU_TRY(upload(th->coff, &coff));
-  TileBinDev d{ltab, toff, wpos, coff, th->nloc_max, (int)th->toff.back(), bins.n_angular == 1 ? 1 : 0};
+  TileBinDev d{seg, info, slot, list, coff, th->runs_max, (int)th->toff.back(), bins.n_angular == 1 ? 1 : 0};
   std::lock_guard<std::mutex> lk(g_mu);
   auto it = g_tiledev.find(key);
   if (it != g_tiledev.end()) {
-    (void)hipFree(ltab);
-    (void)hipFree(toff);
-    (void)hipFree(coff);
-    (void)hipFree(wpos);
+    void* own[] = {seg, slot, info, list, coff};
+    for (void* p : own) (void)hipFree(p);
     *out = it->second;
     return HU_OK;
   }
@@ -901,11 +965,9 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   double* fstats = reinterpret_cast<double*>(r.work + r.lay.fstats);
   double* parts_c = reinterpret_cast<double*>(r.work + r.lay.parts_c);
   double* parts_p = reinterpret_cast<double*>(r.work + r.lay.parts_p);
-  unsigned* queue = reinterpret_cast<unsigned*>(r.work + r.lay.queue);
   const uint32_t* cnt_src = reinterpret_cast<const uint32_t*>(geo.counts);
 
-  // pass A: noise -> R2C rows; block 0 of each field sets up that field's bin counts, block (0, 0)
-  // clears the work counters of the persistent passes
+  // pass A: noise -> R2C rows; block 0 of each field sets up that field's bin counts
   RowsArgs ra{};
   ra.spec = spec;
   ra.Nh = g.Nhp;
@@ -917,8 +979,6 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   ra.io = r.io;
   ra.nb = nb;
   ra.cnt_src = cnt_src;
-  ra.zero = queue;
-  ra.nzero = NQUEUE;
   if (!batch_mode) {
     for (int i = 0; i < B; ++i) ra.seeds[i] = r.seeds[i];
     int fs = 0;
@@ -1010,10 +1070,6 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
     if (g.nd == 3 && !planes)
       HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, r.plan.v[P_COLY], cy, st, rad); }));
     BinArgs ba{};
-    ba.ntiles = col_tiles(g.n[0], r.plan.v[P_BIN], g.Nh / g.n[0]);
-    ba.batch = B;
-    ba.persistent = (g.nd == 3) != (r.plan.v[P_BINSCHED] != 0);
-    ba.q = ItemQueue{queue + Q_BIN, ba.ntiles * B, 8};
     ba.sc = fields_xcd ? col_sched_fields(g.n[0], r.plan.v[P_BIN], g.Nh / g.n[0], B)
                        : col_sched(g.n[0], r.plan.v[P_BIN], g.Nh / g.n[0], B);
     ba.spec = spec;
@@ -1022,7 +1078,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
     ba.tb = tb_p;
     ba.parts = parts_p;
     ba.tw = tw_0;
-    HU_HIP(timed("cols_bin", st, [&] { return launch_cols_bin(g.n[0], r.plan.v[P_BIN], ba, st, rad, (g.nd == 2) != (r.plan.v[P_BSPLIT] != 0)); }));
+    HU_HIP(timed("cols_bin", st, [&] { return launch_cols_bin(g.n[0], r.plan.v[P_BIN], ba, st, rad, r.plan.v[P_BSPLIT]); }));
   }
   if (want_cont || want_pm1 || want_counts) {
     SpecFinalArgs sf{};

@@ -33,16 +33,15 @@ struct Geom {
 };
 
 // Tunable choices of the pass sequence.  Entries 0-4: the tile width of each kernel family (0 the
-// default, 1 half of it).  Entries 5-7: schedules (0 the default): P_BINSCHED the binning pass's
-// (default one item per workgroup in 2D, persistent with a work counter in 3D; 1 the other one),
-// P_FIELDS the axis-0 passes' placement of a tile's fields (default consecutive on one XCD in 2D,
+// default, 1 half of it).  Entry 5, P_BINSCHED, is reserved (accepted, without effect).  Entries 6-7:
+// schedules (0 the default): P_FIELDS the axis-0 passes' placement of a tile's fields (default consecutive on one XCD in 2D,
 // field-major in 3D; 1 the other one), P_YGROUP the 3D y passes' tiles per XCD group (16, or 4).
 // Entry 8, P_RADIX: the radix lists of the column passes (y, filter, binning): 0 the default plan
 // of each length, 1 its alternative order where the length has one (Plan<L, 1>).  Entries 9 and
 // 10, P_BSPLIT and P_FSPLIT: the exchange of the binning and of the filter pass along axis 0,
 // complex or split (real and imaginary parts in two rounds: half the LDS, more resident
 // workgroups, two more barriers per exchange; axis-0 lengths >= 192).  Default: the binning pass
-// split in 2D and complex in 3D, the filter pass complex; 1 the other one.  Entry 11, P_WHOLE:
+// split, the filter pass complex; 1 the other one.  Entry 11, P_WHOLE:
 // for 2D grids whose half spectrum fits in one workgroup's LDS (n_x and n0 up to 128), 1 runs the
 // whole path as one kernel with one workgroup per field (whole_field_ok), 0 the pass sequence.
 enum { P_R2C = 0, P_COLY = 1, P_FILTER = 2, P_C2R = 3, P_BIN = 4, P_BINSCHED = 5, P_FIELDS = 6, P_YGROUP = 7,
@@ -56,14 +55,13 @@ struct TunePlan {
 };
 
 // Workspace of one class: half spectra, the filter pass's per-tile statistics, per-field stats,
-// the last row pass's per-tile sign counts, the tile partials of the continuous (parts_c) and the
-// +-1 (parts_p) spectra, and the work counter of the persistent binning pass.
+// the last row pass's per-tile sign counts, and the tile partials of the continuous (parts_c) and the
+// +-1 (parts_p) spectra.
 struct Layout {
-  size_t spec, partials, fstats, cpart, parts_c, parts_p, queue, total;
+  size_t spec, partials, fstats, cpart, parts_c, parts_p, total;
   int tiles;
   int Mc, Mp;                    // tile partials per field of each spectrum (0: none)
 };
-enum { Q_BIN = 0, NQUEUE = 1 };
 
 struct BinGeo {
   uint16_t* table;               // [ncol][n0] bin of each mode

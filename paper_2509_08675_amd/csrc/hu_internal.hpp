@@ -9,7 +9,7 @@
 
 namespace hu {
 
-// lengths whose axis-0 filter and binning passes are compiled with the split exchange too
+// lengths whose axis-0 filter and binning passes are compiled with either exchange
 // (shorter columns have small exchange buffers)
 constexpr bool split_length(int L) { return L >= 192; }
 
@@ -68,8 +68,6 @@ struct RowsArgs {
   const float2* tw2;       // exp(-2 pi i k / 2L), k < L
   FillSpan fill[6];
   int fill_spans;
-  unsigned* zero;          // words cleared by block (0, 0) before the later passes read them
-  int nzero;               // (the work counter of the persistent binning pass)
   const float2* tw_y;      // plane kernels (3D): stage table of n_y
 };
 
@@ -122,26 +120,22 @@ struct SmallArgs {
 
 
 // Tile-local bin tables of the axis-0 passes for one tile width.  The modes of a tile touch few of
-// the bins; each tile has one partial sum per distinct bin (in ascending bin order), stored grouped
-// by bin so that a bin's partials are contiguous, and the partials of a bin are combined in a
-// fixed order: the binned spectra are the same bits on every run.
+// the bins; each tile has one partial sum per distinct bin, stored grouped by bin so that a bin's
+// partials are contiguous, and the partials of a bin are combined in a fixed order: the binned
+// spectra are the same bits on every run.  Inside a tile every binning thread sums the runs of equal
+// bin among its consecutive modes; the runs of the tile are numbered thread by thread, and a list
+// names each bin's runs.
 struct TileBinDev {
-  const uint16_t* ltab;    // [ncol][n0]: position of the mode's bin in its tile's list of distinct bins
-  const uint32_t* toff;    // [ntiles + 1]: partials i = toff[t] .. toff[t+1]-1 belong to tile t
-  const uint32_t* wpos;    // [M]: where partial i is stored: grouped by bin, tile order inside a bin
+  const uint2* seg;        // [ntiles][threads]: x: bit i set where entry i of the thread starts a new run, y: its first run
+  const uint4* info;       // [ntiles]: x: the tile's first list entry, y: its first slot, z: its slots (a multiple of 64)
+  const uint2* slot;       // one per summing lane: x: first entry (relative to the tile) | entries << 16 | log2 lanes << 29,
+                           // y: where the partial is stored (the bin's first lane), or ~0; a bin's lanes are adjacent and
+                           // aligned, take every (lanes)-th entry and add up by a fixed butterfly
+  const uint16_t* list;    // runs of each bin of the tile, bin after bin
   const uint32_t* coff;    // [nb + 1]: the stored partials of bin k are coff[k] .. coff[k+1]-1
-  int nloc_max;            // most distinct bins in one tile
+  int runs_max;            // most runs in one tile
   int M;                   // partials per field
   int sym;                 // radial bins only: modes e and n0 - e of a column share their bin
-};
-
-// Dynamic schedule of the persistent binning pass: the items (tile, field), tile-major, are
-// taken in chunks (shrinking towards the end) from a counter that the first pass of the same
-// launch sequence cleared.
-struct ItemQueue {
-  unsigned* counter;
-  int nitems;              // ntiles * batch
-  int chunk_max;
 };
 
 struct FilterArgs {
@@ -155,7 +149,6 @@ struct FilterArgs {
   double* parts;           // [B][M] tile partials of the continuous-spectrum bins, or null (no bins)
   const float2* tw;        // stage twiddle table of the axis length (StageTab layout)
   double* partials;        // [B][tiles][4]: sum w |F|^2, Re F(0), max ln chi
-  int hx_off, hq_off;      // LDS byte offsets of the tile histogram (set by the launcher)
   int any_gen;             // some field uses a tabulated radial form or the FP64 filter evaluation
 };
 
@@ -170,9 +163,6 @@ struct FinalizeArgs {
 };
 
 struct BinArgs {
-  int ntiles, batch;
-  int persistent;          // 1: persistent over the items of q; 0: one item per workgroup (sc)
-  ItemQueue q;
   ColSched sc;
   const float2* spec;
   long long Nh;
@@ -180,7 +170,6 @@ struct BinArgs {
   TileBinDev tb;
   double* parts;           // [B][M] tile partials of the bins of sum w |X|^2
   const float2* tw;        // stage twiddle table of the axis length (StageTab layout)
-  int hx_off, hq_off;      // LDS byte offsets of the tile histogram (set by the launcher)
 };
 
 // Per-field spectra from the tile partials (each bin summed over its tiles in tile order) and the
@@ -335,10 +324,11 @@ hipError_t launch_rows_r2c(int L, int src, int variant, const RowsArgs& a, int b
 hipError_t launch_cols(int L, bool inv, int variant, const ColsArgs& a, hipStream_t st, int radix = 0);
 // split: the split exchange (real and imaginary parts in two rounds, half the LDS), lengths >= 192
 hipError_t launch_cols_filter(int L, int variant, const FilterArgs& a, hipStream_t st, int radix = 0, int split = 0);
-// columns per tile of the axis-0 passes with tile variant `variant`
+// columns per tile of the axis-0 passes with tile variant `variant`, and their elements per thread
 int col_width(int L, int variant);
+int col_elems(int L);
 hipError_t launch_finalize(const FinalizeArgs& a, int batch, hipStream_t st);
-hipError_t launch_cols_bin(int L, int variant, const BinArgs& a, hipStream_t st, int radix = 0, int split = 0);
+hipError_t launch_cols_bin(int L, int variant, const BinArgs& a, hipStream_t st, int radix = 0, int complex_x = 0);
 hipError_t launch_rows_c2r(int L, bool thresh, int variant, const RowsZArgs& a, int batch, hipStream_t st);
 int row_tiles(int L, int variant, long long nrows);
 hipError_t launch_spec_final(const SpecFinalArgs& a, int batch, hipStream_t st);

@@ -150,8 +150,6 @@ __global__ void __launch_bounds__((PlaneShape<LR, NY>::T)) k_plane_fwd(RowsArgs 
   float2* plane = lds;
   const int tid = threadIdx.x, z = blockIdx.x, b = blockIdx.y;
   if (z == 0) {                                  // the first row pass's set-up duties for this field
-    if (b == 0)
-      for (int i = tid; i < a.nzero; i += T) a.zero[i] = 0u;
     if (a.io) {
       const FieldIO& io = a.io[b];
       uint32_t* dst[2] = {reinterpret_cast<uint32_t*>(io.cont_cnt), reinterpret_cast<uint32_t*>(io.pm1_cnt)};

@@ -278,8 +278,6 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_r2c(RowsArgs a) {
   const long long nx = 2 * L;
 
   if (blockIdx.x == 0) {                        // set up this field's outputs and counters for later passes
-    if (b == 0)
-      for (int i = tid; i < a.nzero; i += T) a.zero[i] = 0u;
     if (a.io) {
       const FieldIO& io = a.io[b];
       uint32_t* dst[2] = {reinterpret_cast<uint32_t*>(io.cont_cnt), reinterpret_cast<uint32_t*>(io.pm1_cnt)};
