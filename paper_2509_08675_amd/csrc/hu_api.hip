@@ -243,6 +243,7 @@ int hu_power_spectrum(hu_dims dims, int32_t batch, const void* x, int32_t dtype,
       cy.inner = g.nxh;
       cy.tw = tw_1;
       cy.sc = col_sched(g.n[1], 0, cy.ncol, B, Y_PASS_GROUP);
+      cy.sc.rev = 1;                     // against the row pass, as in the generator
       HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, 0, cy, st); }));
     }
     BinArgs ba{};
@@ -371,6 +372,7 @@ int hu_spectrum_grad(hu_dims dims, const hu_filter* filt, uint64_t seed, hu_bins
     cy.inner = g.nxh;
     cy.tw = tw_1;
     cy.sc = col_sched(g.n[1], 0, cy.ncol, 1, Y_PASS_GROUP);
+    cy.sc.rev = 1;
     HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, 0, cy, st); }));
   }
   GradCoefArgs ga{};
@@ -450,6 +452,7 @@ int hu_window_variance(hu_dims dims, int32_t batch, const void* x, int32_t dtype
       cy.inner = g.nxh;
       cy.tw = tw_1;
       cy.sc = col_sched(g.n[1], 0, cy.ncol, B, Y_PASS_GROUP);
+      cy.sc.rev = 1;                     // against the row pass, as in the generator
       HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, 0, cy, st); }));
     }
     WvarArgs wa{};
@@ -556,6 +559,7 @@ int hu_two_point(hu_dims dims, int32_t batch, const int8_t* pm1, float* s2, void
       cy.inner = g.nxh;
       cy.tw = tw_1;
       cy.sc = col_sched(g.n[1], 0, cy.ncol, B, Y_PASS_GROUP);
+      cy.sc.rev = 1;                     // against the row pass, as in the generator
       HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, 0, cy, st); }));
     }
     SquareArgs sa{};

@@ -36,6 +36,7 @@ static ColSched col_sched_L(long long ncol, int batch, int group) {
   s.ntiles_pad = (s.ntiles + s.G - 1) / s.G * s.G;
   s.batch = batch;
   s.finner = 0;
+  s.rev = 0;
   return s;
 }
 
@@ -45,7 +46,7 @@ ColSched col_sched(int L, int variant, long long ncol, int batch, int group) {
   case LL: return variant ? col_sched_L<LL, 1>(ncol, batch, group) : col_sched_L<LL, 0>(ncol, batch, group);
     HU_COL_LENGTHS(X)
 #undef X
-    default: return ColSched{0, 0, 1, 0, 0};
+    default: return ColSched{0, 0, 1, 0, 0, 0};
   }
 }
 

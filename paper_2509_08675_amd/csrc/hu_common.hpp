@@ -152,7 +152,7 @@ __device__ __forceinline__ void r2c_twist_store(const float2* lz, const float2* 
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ bool map_tile(const ColSched& s, int& b, long long& tile) {
   const unsigned id = blockIdx.x;
-  const unsigned xcd = id & 7u, round = id >> 3;
+  const unsigned xcd = id & 7u, round = s.rev ? (gridDim.x >> 3) - 1u - (id >> 3) : id >> 3;
   const unsigned j = round % (unsigned)s.G;
   const long long grp = (long long)(round / (unsigned)s.G) * 8 + xcd;
   if (s.finner) {                                 // G = batch: group grp is tile grp, j its field
@@ -565,6 +565,16 @@ template <int L, int R, int P, int E>
 __device__ __forceinline__ void col_store(const float2 (&v)[E], const ColIO& io) {
 #pragma unroll
   for (int s = 0; s < E; ++s) buf_store2(io.r, v[s], io.voff, (unsigned)slot_index<L, R, P>(s, 0) * io.step);
+}
+
+// Stores of the outputs that no later pass reads (field, sign map): non-temporal (cache policy bit 1),
+// so that they leave the half spectrum in the 256 MB memory-side cache for the next pass.
+constexpr int STREAM = 2;
+__device__ __forceinline__ void out_store2(rsrc_t r, float2 v, unsigned voff, unsigned soff) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, STREAM);
+}
+__device__ __forceinline__ void out_store4(rsrc_t r, u32x4 v, unsigned voff, unsigned soff) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, STREAM);
 }
 
 // per-field parameter and output accessors: the batch table when present, else the uniform

@@ -53,6 +53,7 @@ struct FillSpan {
 struct ColSched {
   int ntiles, ntiles_pad, G, batch;
   int finner;              // 1: the fields of one tile are consecutive (G = batch, same XCD)
+  int rev;                 // 1: the workgroups walk fields and tiles from the last to the first
 };
 
 struct RowsArgs {

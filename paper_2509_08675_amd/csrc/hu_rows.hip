@@ -484,14 +484,14 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_c2r(RowsZArgs a) {
     const float x0 = fmaf(v[s].x, scale, offset);
     const float x1 = fmaf(v[s].y, scale, offset);
     if constexpr (STAGE) lrow[slot_index<L, RL, P>(s, 0) + p] = make_float2(x0, x1);
-    else buf_store2(fo, make_float2(x0, x1), vox0 * 4u, so * 4u);
+    else out_store2(fo, make_float2(x0, x1), vox0 * 4u, so * 4u);
     if constexpr (THRESH) {
       const bool p0 = x0 >= 0.0f, p1 = x1 >= 0.0f;
       npos += (unsigned)p0 + (unsigned)p1;
       nnear += (unsigned)(fabsf(x0) < near_tol) + (unsigned)(fabsf(x1) < near_tol);
       if constexpr (!STAGE) {
         const unsigned b0 = p0 ? 0x01u : 0xFFu, b1 = p1 ? 0x0100u : 0xFF00u;
-        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(b0 | b1), to, vox0, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(b0 | b1), to, vox0, so, STREAM);
       }
       v[s] = make_float2(p0 ? 1.0f : -1.0f, p1 ? 1.0f : -1.0f);
     }
@@ -507,12 +507,12 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_c2r(RowsZArgs a) {
       const int j = (4 * q) / (2 * L), x = 4 * q - j * (2 * L);
       const float2 a0 = lw[j * RS + x / 2], a1 = lw[j * RS + x / 2 + 1];
       const unsigned vox = (unsigned)(cw * 2 * L + 4 * q);
-      buf_store4(fo, u32x4{__float_as_uint(a0.x), __float_as_uint(a0.y), __float_as_uint(a1.x), __float_as_uint(a1.y)},
+      out_store4(fo, u32x4{__float_as_uint(a0.x), __float_as_uint(a0.y), __float_as_uint(a1.x), __float_as_uint(a1.y)},
                  vox * 4u, 0u);
       if constexpr (THRESH) {
         const unsigned packed = (a0.x >= 0.0f ? 0x01u : 0xFFu) | (a0.y >= 0.0f ? 0x0100u : 0xFF00u) |
                                 (a1.x >= 0.0f ? 0x010000u : 0xFF0000u) | (a1.y >= 0.0f ? 0x01000000u : 0xFF000000u);
-        __builtin_amdgcn_raw_buffer_store_b32(packed, to, vox, 0u, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(packed, to, vox, 0u, STREAM);
       }
     }
     xchg_sync<WV>();                                 // the regions are the next transform's exchange buffer
