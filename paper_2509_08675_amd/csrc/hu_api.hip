@@ -43,9 +43,9 @@ GradLayout grad_layout(const Geom& g, int nb) {
 }
 
 // workspace of hu_window_variance: the half spectra of a chunk of fields, then the per-tile
-// partial sums for every radius
+// partial sums for every radius, then (used where the workspace has room) the form-factor table
 struct WvarLayout {
-  size_t spec, partials, total;
+  size_t spec, partials, total, tab, total_tab;
   int tiles;
 };
 WvarLayout wvar_layout(const Geom& g, int chunk) {
@@ -54,6 +54,8 @@ WvarLayout wvar_layout(const Geom& g, int chunk) {
   L.partials = up256((size_t)chunk * g.Nhp * 8);
   L.tiles = col_tiles(g.n[0], 0, axis0(g).ncol);
   L.total = L.partials + up256((size_t)chunk * L.tiles * HU_MAX_RADII * 8);
+  L.tab = L.total;
+  L.total_tab = L.tab + (wvar_table(g.nd, chunk) ? up256(wvar_table_bytes(g.n[0], L.tiles)) : 0);
   return L;
 }
 
@@ -142,7 +144,7 @@ int hu_workspace_size(int op, hu_dims dims, int32_t batch, const hu_bins* bins, 
       *bytes = fs_bytes(g, bins->n_radial * bins->n_angular + 1);
       return HU_OK;
     case HU_OP_WINDOW_VARIANCE:
-      *bytes = wvar_layout(g, chunk).total;
+      *bytes = wvar_layout(g, chunk).total_tab;
       return HU_OK;
     case HU_OP_TWO_POINT:
       HU_TRY(layout(g, chunk, true, TunePlan{}, nullptr, &lay));
@@ -459,12 +461,19 @@ int hu_window_variance(hu_dims dims, int32_t batch, const void* x, int32_t dtype
     wa.spec = spec;
     wa.Nh = g.Nhp;
     wa.gm = axis0(g);
-    wa.sc = col_sched(g.n[0], 0, wa.gm.ncol, B);
+    const bool tab = wvar_table(g.nd, B) && work_bytes >= lay.total_tab;
+    wa.sc = tab ? col_sched_fields(g.n[0], 0, wa.gm.ncol, B) : col_sched(g.n[0], 0, wa.gm.ncol, B);
     wa.tw = tw_0;
-    wa.nr = n_radii;
-    for (int j = 0; j < n_radii; ++j) wa.radii[j] = (float)radii[j];
+    wa.nr_all = n_radii;
     wa.partials = partials;
-    HU_HIP(timed("cols_wvar", st, [&] { return launch_cols_wvar(g.n[0], wa, st); }));
+    wa.tab = tab ? reinterpret_cast<const float*>(w + lay.tab) : nullptr;
+    const int group = tab ? WVAR_TAB_RADII : HU_MAX_RADII;      // radii per launch
+    for (int j0 = 0; j0 < n_radii; j0 += group) {
+      wa.j0 = j0;
+      wa.nr = n_radii - j0 < group ? n_radii - j0 : group;
+      for (int j = 0; j < wa.nr; ++j) wa.radii[j] = (float)radii[j0 + j];
+      HU_HIP(timed("cols_wvar", st, [&] { return launch_cols_wvar(g.n[0], wa, st); }));
+    }
     WvarFinalArgs fa{partials, wa.sc.ntiles, n_radii, 1.0 / ((double)g.N * (double)g.N), out + (size_t)f0 * n_radii};
     HU_HIP(timed("wvar_final", st, [&] { return launch_wvar_final(fa, B, st); }));
   }

@@ -297,9 +297,25 @@ struct WvarArgs {
   long long Nh;
   Axis0Geom gm;
   const float2* tw;        // stage twiddle table of the axis length (StageTab layout)
-  int nr;                  // radii (1..HU_MAX_RADII)
+  int nr;                  // radii of this launch (1..HU_MAX_RADII), radii j0 .. j0 + nr - 1 of the call's nr_all
+  int j0, nr_all;
   float radii[HU_MAX_RADII];
-  double* partials;        // [B][tiles][nr]
+  double* partials;        // [B][tiles][nr_all]
+  const float* tab;        // room for the form factors of nr <= WVAR_TAB_RADII radii, or null: evaluated in the pass
+};
+
+// The squared form factors of the radii of one launch, [radius][tile][pair][thread].  The table pays
+// in 2D from four fields on (its kernel takes about as long as the evaluation for two: 6 x 512^2
+// 39 -> 28 us).  In 3D a form factor is cheaper and the table as large as the spectra of four fields:
+// 4 x 256^3 took 169 us with it, the pairs evaluated in the pass about 145.
+constexpr int WVAR_TAB_RADII = 8, WVAR_TAB_BATCH = 4;
+inline bool wvar_table(int ndim, int batch) { return ndim == 2 && batch >= WVAR_TAB_BATCH; }
+struct WvarTabArgs {
+  Axis0Geom gm;
+  int ntiles, C, P, H, T;  // tiles of C columns, threads per column, pairs per thread, threads per tile
+  int nr;
+  float radii[HU_MAX_RADII];
+  float* tab;
 };
 
 struct WvarFinalArgs {
@@ -310,7 +326,9 @@ struct WvarFinalArgs {
 };
 
 hipError_t launch_cols_square(int L, const SquareArgs& a, hipStream_t st);
+// the axis-0 pass for a.nr radii (after the kernel that fills a.tab, when set)
 hipError_t launch_cols_wvar(int L, const WvarArgs& a, hipStream_t st);
+size_t wvar_table_bytes(int L, int ntiles);
 hipError_t launch_wvar_final(const WvarFinalArgs& a, int batch, hipStream_t st);
 hipError_t launch_cols_adjoint(int L, const AdjointArgs& a, hipStream_t st, int* grid);
 // workgroups of a kernel with this block size and LDS that are resident on the current device at
