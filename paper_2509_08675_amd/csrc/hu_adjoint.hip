@@ -486,11 +486,16 @@ hipError_t launch_grad_final(const GradFinalArgs& a, hipStream_t st) {
 // ---------------------------------------------------------------------------------------------
 constexpr int FS_THREADS = 256, FS_RUN = 16;
 
-template <int NDIM>
+// PAIR (3D, n0 a multiple of 32): the modes e and n0 - e of a column share H and their bin (kappa_z enters
+// squared), so a thread evaluates FS_RUN modes of the half column and counts each twice; the thread
+// of a column's first modes also takes e = n0 / 2.  Bound by the evaluation (about 60 instructions a
+// mode) and the runs' LDS atomics.  512^3: 382 us with a 64-bit division and both modes of a pair per mode.
+template <int NDIM, bool GEN, bool PAIR>
 __global__ void __launch_bounds__(FS_THREADS) k_filter_spectrum(FilterSpecArgs a) {
   extern __shared__ unsigned long long hq[];      // [nb] fixed-point sums, then [nb] int exponents
   int* hx = reinterpret_cast<int*>(hq + a.nb);
   __shared__ double red[FS_THREADS / 64];
+  constexpr int NM = PAIR ? FS_RUN + 1 : FS_RUN;
   const int tid = threadIdx.x;
   double* row = a.rows + (long long)blockIdx.x * a.nb;
   for (int i = tid; i < a.nb; i += FS_THREADS) {
@@ -498,28 +503,43 @@ __global__ void __launch_bounds__(FS_THREADS) k_filter_spectrum(FilterSpecArgs a
     hq[i] = 0ull;
     row[i] = 0.0;
   }
-  const long long n0 = a.gm.n0;
-  const long long chunk = (long long)FS_THREADS * FS_RUN;
+  const unsigned n0 = (unsigned)a.gm.n0;
+  // modes of the walk per column; a column holds whole threads' runs where FS_RUN divides it
+  const unsigned per = PAIR ? n0 / 2 : n0;
+  const unsigned nm = (unsigned)a.gm.ncol * per;
+  const unsigned chunk = FS_THREADS * FS_RUN;
   double tot = 0.0;
-  for (long long base = (long long)blockIdx.x * chunk; base < a.Nh; base += (long long)gridDim.x * chunk) {
-    const long long i0 = base + (long long)tid * FS_RUN;
-    int bin[FS_RUN];
-    double val[FS_RUN];
+  for (unsigned base = blockIdx.x * chunk; base < nm; base += gridDim.x * chunk) {
+    const unsigned i0 = base + (unsigned)tid * FS_RUN;
+    int bin[NM];
+    double val[NM];
+    unsigned g = i0 / per, e = i0 - g * per;
+    const bool first = PAIR && e == 0;
+    ColCoord cc = col_coord(a.gm, g < (unsigned)a.gm.ncol ? (int)g : 0);
+    auto mode = [&](int q, unsigned m, double count) {
+      float lnc;
+      const float H = amp_sym<NDIM, GEN>(a.filt, a.gm, cc, (int)m, lnc);
+      val[q] = count * (double)(cc.wm * H * H);
+      bin[q] = (int)a.table[g * n0 + m];
+      tot += val[q];
+    };
 #pragma unroll
     for (int q = 0; q < FS_RUN; ++q) {
-      const long long i = i0 + q;
       bin[q] = -1;
       val[q] = 0.0;
-      if (i < a.Nh) {
-        const int g = (int)(i / n0);
-        const int e = (int)(i - (long long)g * n0);
-        const ColCoord cc = col_coord(a.gm, g);
-        float lnc;
-        const float H = amp_sym<NDIM, true>(a.filt, a.gm, cc, e, lnc);
-        val[q] = (double)(cc.wm * H * H);
-        bin[q] = (int)a.table[i];
-        tot += val[q];
+      if (i0 + q < nm) {
+        mode(q, e, PAIR && e != 0 ? 2.0 : 1.0);
+        if (++e == per && !PAIR) {                 // PAIR: per is a multiple of FS_RUN
+          e = 0;
+          ++g;
+          cc = col_coord(a.gm, g < (unsigned)a.gm.ncol ? (int)g : 0);
+        }
       }
+    }
+    if constexpr (PAIR) {
+      bin[FS_RUN] = -1;
+      val[FS_RUN] = 0.0;
+      if (first && i0 < nm) mode(FS_RUN, n0 / 2, 1.0);
     }
     __syncthreads();                               // the previous chunk's flush is done
 #pragma unroll
@@ -527,7 +547,7 @@ __global__ void __launch_bounds__(FS_THREADS) k_filter_spectrum(FilterSpecArgs a
       int cur = -1;
       double run = 0.0;
 #pragma unroll
-      for (int q = 0; q < FS_RUN; ++q) {
+      for (int q = 0; q < NM; ++q) {
         if (bin[q] != cur) {
           if (cur >= 0) pass ? run_commit<true>(cur, run, hx, hq) : run_commit<false>(cur, run, hx, hq);
           cur = bin[q];
@@ -584,10 +604,12 @@ __global__ void __launch_bounds__(256) k_filter_spectrum_final(FilterSpecArgs a)
 
 hipError_t launch_filter_spectrum(const FilterSpecArgs& a, hipStream_t st) {
   const size_t lds = (size_t)a.nb * 12;
-  if (a.gm.ndim == 2)
-    hipLaunchKernelGGL(k_filter_spectrum<2>, dim3(a.nblocks), dim3(FS_THREADS), lds, st, a);
-  else
-    hipLaunchKernelGGL(k_filter_spectrum<3>, dim3(a.nblocks), dim3(FS_THREADS), lds, st, a);
+  const bool pair = a.gm.ndim == 3 && a.gm.n0 % (2 * FS_RUN) == 0;
+  const bool gen = a.filt.prec64 || a.filt.prof;
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(a.nblocks), dim3(FS_THREADS), lds, st, a); };
+  if (a.gm.ndim == 2) gen ? go(k_filter_spectrum<2, true, false>) : go(k_filter_spectrum<2, false, false>);
+  else if (pair) gen ? go(k_filter_spectrum<3, true, true>) : go(k_filter_spectrum<3, false, true>);
+  else gen ? go(k_filter_spectrum<3, true, false>) : go(k_filter_spectrum<3, false, false>);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_filter_spectrum_final, dim3((a.nb + 3) / 4), dim3(256), 0, st, a);
