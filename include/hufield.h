@@ -79,7 +79,10 @@ enum { HU_F32 = 0, HU_I8 = 1 };
 
 /* Operations for hu_workspace_size. */
 enum { HU_OP_GEN_FIELD = 0, HU_OP_PIPELINE = 1, HU_OP_POWER_SPECTRUM = 2, HU_OP_LOSS = 3, HU_OP_FILTER_SPECTRUM = 4,
-       HU_OP_WINDOW_VARIANCE = 5, HU_OP_TWO_POINT = 6 };
+       HU_OP_WINDOW_VARIANCE = 5, HU_OP_TWO_POINT = 6,
+       HU_OP_NOISE = 7,          /* the noise buffer of hu_field_spectrum */
+       HU_OP_FIELD_SPECTRUM = 8, /* its workspace */
+       HU_OP_NOISE_GRAD = 9 };   /* the workspace of hu_noise_grad */
 
 /* Most window radii of one hu_window_variance call. */
 #define HU_MAX_RADII 32
@@ -280,6 +283,19 @@ int hu_spectrum_loss(hu_bins bins, const double* sum, const uint64_t* cnt, const
 int hu_spectrum_grad(hu_dims dims, const hu_filter* filt, uint64_t seed, hu_bins bins, const double* dL_dP,
                      const double* cont_sum, const uint64_t* cont_cnt, const double* stats, double* grad,
                      void* work, size_t work_bytes, void* stream);
+
+/* The two halves of a fitting step, for callers that want a field's binned continuous spectrum and its
+ * gradient but not the field: hu_field_spectrum forms stats [4], cont_sum and cont_cnt [R*A+1] exactly as
+ * hu_gen_field with one seed does (same bits under the same plan) and leaves the noise spectrum in
+ * `noise` (device, 256-byte aligned, hu_workspace_size(HU_OP_NOISE, dims, 1, ...) bytes, caller-owned);
+ * hu_noise_grad is hu_spectrum_grad reading that buffer (unchanged) instead of regenerating it.
+ * Workspaces: hu_workspace_size(HU_OP_FIELD_SPECTRUM | HU_OP_NOISE_GRAD, dims, 1, &bins, ...).
+ * Arguments and errors otherwise as hu_gen_field / hu_spectrum_grad; no argument may be NULL. */
+int hu_field_spectrum(hu_dims dims, const hu_filter* filt, uint64_t seed, hu_bins bins, void* noise, double* stats,
+                      double* cont_sum, uint64_t* cont_cnt, void* work, size_t work_bytes, void* stream);
+int hu_noise_grad(hu_dims dims, const hu_filter* filt, const void* noise, hu_bins bins, const double* dL_dP,
+                  const double* cont_sum, const uint64_t* cont_cnt, const double* stats, double* grad, void* work,
+                  size_t work_bytes, void* stream);
 
 /* One field of a heterogeneous batch: its own grid, filter, seed, bins and outputs (device
  * pointers, each may be NULL; at least one must be set; bins are used when cont_sum or pm1_sum is

@@ -32,10 +32,10 @@ struct GradLayout {
   size_t spec, coef, partials, total;
   int tiles;
 };
-GradLayout grad_layout(const Geom& g, int nb) {
+GradLayout grad_layout(const Geom& g, int nb, bool own_spec = true) {
   GradLayout L{};
   L.spec = 0;
-  L.coef = up256((size_t)g.Nhp * 8);
+  L.coef = own_spec ? up256((size_t)g.Nhp * 8) : 0;
   L.partials = L.coef + up256((size_t)(nb + 1) * 8);
   L.tiles = col_tiles(g.n[0], 0, axis0(g).ncol);
   L.total = L.partials + up256((size_t)L.tiles * 8 * 8);
@@ -138,6 +138,18 @@ int hu_workspace_size(int op, hu_dims dims, int32_t batch, const hu_bins* bins, 
     case HU_OP_LOSS:
       if (!bins) return HU_ERR_ARG;
       *bytes = grad_layout(g, bins->n_radial * bins->n_angular + 1).total;
+      return HU_OK;
+    case HU_OP_NOISE:
+      *bytes = up256((size_t)g.Nhp * sizeof(float2));
+      return HU_OK;
+    case HU_OP_FIELD_SPECTRUM:
+      if (!bins) return HU_ERR_ARG;
+      HU_TRY(layout(g, 1, true, widest_plan(), bins, &lay));
+      *bytes = lay.total - lay.partials;
+      return HU_OK;
+    case HU_OP_NOISE_GRAD:
+      if (!bins) return HU_ERR_ARG;
+      *bytes = grad_layout(g, bins->n_radial * bins->n_angular + 1, false).total;
       return HU_OK;
     case HU_OP_FILTER_SPECTRUM:
       if (!bins) return HU_ERR_ARG;
@@ -320,39 +332,139 @@ int hu_spectrum_loss(hu_bins bins, const double* sum, const uint64_t* cnt, const
   return HU_OK;
 }
 
-int hu_spectrum_grad(hu_dims dims, const hu_filter* filt, uint64_t seed, hu_bins bins, const double* dL_dP,
-                     const double* cont_sum, const uint64_t* cont_cnt, const double* stats, double* grad, void* work,
-                     size_t work_bytes, void* stream) {
+int hu_field_spectrum(hu_dims dims, const hu_filter* filt, uint64_t seed, hu_bins bins, void* noise, double* stats,
+                      double* cont_sum, uint64_t* cont_cnt, void* work, size_t work_bytes, void* stream) {
   Geom g;
   HU_TRY(make_geom(dims, &g));
   HU_TRY(check_filter(filt, g.nd));
+  HU_TRY(check_bins(&bins, g.nd));
+  if (!noise || !stats || !cont_sum || !cont_cnt) return HU_ERR_ARG;
+  const void* ptrs[] = {stats, cont_sum, cont_cnt};
+  for (const void* p : ptrs)
+    if (!aligned(p, 16)) return HU_ERR_ALIGN;
+  if (!aligned(noise, 256)) return HU_ERR_ALIGN;
+  if (!work || !aligned(work, 256)) return work ? HU_ERR_ALIGN : HU_ERR_ARG;
+  ClassRun r{};
+  r.g = g;
+  r.B = 1;
+  r.plan = get_plan(g, &bins, 1);
+  HU_TRY(layout(g, 1, true, r.plan, &bins, &r.lay));
+  if (work_bytes < r.lay.total - r.lay.partials) return HU_ERR_WORKSPACE;
+  r.lay.fstats -= r.lay.partials;               // the spectrum lies outside: everything moves down by its size
+  r.lay.cpart -= r.lay.partials;
+  r.lay.parts_c -= r.lay.partials;
+  r.lay.parts_p -= r.lay.partials;
+  r.lay.partials = 0;
+  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  HU_TRY(prepare_tables(g, &bins, st));
+  r.bins = &bins;
+  r.filt = *filt;
+  r.seeds = &seed;
+  r.out.stats = stats;
+  r.out.cont_sum = cont_sum;
+  r.out.cont_cnt = cont_cnt;
+  r.work = reinterpret_cast<char*>(work);
+  r.noise = reinterpret_cast<float2*>(noise);
+  return enqueue_class(r, st);
+}
+
+}  // extern "C"
+
+namespace {
+
+// the adjoint over the noise spectrum W (transformed along every axis but axis 0)
+int enqueue_adjoint(const Geom& g, const hu_filter& filt, const hu_bins& bins, const float2* spec, const double* dL_dP,
+                    const double* cont_sum, const uint64_t* cont_cnt, const double* stats, double* grad, double* coef,
+                    double* partials, int tiles, hipStream_t st) {
+  const int nb = bins.n_radial * bins.n_angular + 1;
+  const float2* tw_0;
+  HU_TRY(get_tw(g.n[0], &tw_0));
+  BinDev bd{};
+  HU_TRY(make_bindev(g, bins, &bd));
+  BinGeo geo{nullptr, nullptr};
+  HU_TRY(get_bingeo(g, bins, &geo));
+  GradCoefArgs ga{};
+  ga.dL_dP = dL_dP;
+  ga.cont_sum = cont_sum;
+  ga.cont_cnt = cont_cnt;
+  ga.stats = stats;
+  ga.nb = nb;
+  ga.N = g.N;
+  ga.sigma_f = filt.sigma_f;
+  ga.coef = coef;
+  HU_HIP(timed("grad_coef", st, [&] { return launch_grad_coef(ga, st); }));
+  AdjointArgs aa{};
+  aa.gm = axis0(g);
+  aa.ntiles = tiles;
+  aa.spec = spec;
+  aa.Nh = g.Nhp;
+  aa.filt = filt_dev(filt, g);
+  aa.width = (float)filt.width;
+  aa.bd = bd;
+  aa.nb = nb;
+  aa.table = geo.table;
+  aa.tw = tw_0;
+  aa.coef = coef;
+  aa.partials = partials;
+  int rows = 0;
+  HU_HIP(timed("cols_adjoint", st, [&] { return launch_cols_adjoint(g.n[0], aa, st, &rows); }));
+  GradFinalArgs fa{partials, rows, grad};
+  HU_HIP(timed("grad_final", st, [&] { return launch_grad_final(fa, st); }));
+  return HU_OK;
+}
+
+// the checks that both forms of the gradient share
+int check_grad(hu_dims dims, const hu_filter* filt, const hu_bins& bins, const double* dL_dP, const double* cont_sum,
+               const uint64_t* cont_cnt, const double* stats, double* grad, const void* work, Geom* g) {
+  HU_TRY(make_geom(dims, g));
+  HU_TRY(check_filter(filt, g->nd));
   if (filt->offset != 0.0) return HU_ERR_UNSUPPORTED;   // the adjoint differentiates sqrt(chi) only
   if (filt->prof_n != 0) return HU_ERR_UNSUPPORTED;     // ... of Eq. (13), not of a tabulated form
-  HU_TRY(check_bins(&bins, g.nd));
+  HU_TRY(check_bins(&bins, g->nd));
   if (!dL_dP || !cont_sum || !cont_cnt || !stats || !grad) return HU_ERR_ARG;
   const void* ptrs[] = {dL_dP, cont_sum, cont_cnt, stats, grad};
   for (const void* p : ptrs)
     if (!aligned(p, 16)) return HU_ERR_ALIGN;
   if (!work || !aligned(work, 256)) return work ? HU_ERR_ALIGN : HU_ERR_ARG;
-  const int nb = bins.n_radial * bins.n_angular + 1;
-  const GradLayout lay = grad_layout(g, nb);
+  return HU_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int hu_noise_grad(hu_dims dims, const hu_filter* filt, const void* noise, hu_bins bins, const double* dL_dP,
+                  const double* cont_sum, const uint64_t* cont_cnt, const double* stats, double* grad, void* work,
+                  size_t work_bytes, void* stream) {
+  Geom g;
+  HU_TRY(check_grad(dims, filt, bins, dL_dP, cont_sum, cont_cnt, stats, grad, work, &g));
+  if (!noise) return HU_ERR_ARG;
+  if (!aligned(noise, 256)) return HU_ERR_ALIGN;
+  const GradLayout lay = grad_layout(g, bins.n_radial * bins.n_angular + 1, false);
+  if (work_bytes < lay.total) return HU_ERR_WORKSPACE;
+  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  HU_TRY(prepare_tables(g, &bins, st));
+  char* w = reinterpret_cast<char*>(work);
+  return enqueue_adjoint(g, *filt, bins, reinterpret_cast<const float2*>(noise), dL_dP, cont_sum, cont_cnt, stats, grad,
+                         reinterpret_cast<double*>(w + lay.coef), reinterpret_cast<double*>(w + lay.partials), lay.tiles, st);
+}
+
+int hu_spectrum_grad(hu_dims dims, const hu_filter* filt, uint64_t seed, hu_bins bins, const double* dL_dP,
+                     const double* cont_sum, const uint64_t* cont_cnt, const double* stats, double* grad, void* work,
+                     size_t work_bytes, void* stream) {
+  Geom g;
+  HU_TRY(check_grad(dims, filt, bins, dL_dP, cont_sum, cont_cnt, stats, grad, work, &g));
+  const GradLayout lay = grad_layout(g, bins.n_radial * bins.n_angular + 1);
   if (work_bytes < lay.total) return HU_ERR_WORKSPACE;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   HU_TRY(prepare_tables(g, &bins, st));
   const int Lrow = g.nx / 2;
-  const float2 *tw_row, *tw2_row, *tw_0, *tw_1 = nullptr;
+  const float2 *tw_row, *tw2_row, *tw_1 = nullptr;
   HU_TRY(get_tw(Lrow, &tw_row));
   HU_TRY(get_tw2(Lrow, &tw2_row));
-  HU_TRY(get_tw(g.n[0], &tw_0));
   if (g.nd == 3) HU_TRY(get_tw(g.n[1], &tw_1));
-  BinDev bd{};
-  HU_TRY(make_bindev(g, bins, &bd));
-  BinGeo geo{nullptr, nullptr};
-  HU_TRY(get_bingeo(g, bins, &geo));
   char* w = reinterpret_cast<char*>(work);
   float2* spec = reinterpret_cast<float2*>(w + lay.spec);
-  double* coef = reinterpret_cast<double*>(w + lay.coef);
-  double* partials = reinterpret_cast<double*>(w + lay.partials);
 
   // the noise spectrum W, transformed along every axis but axis 0 (as in the generator)
   RowsArgs ra{};
@@ -377,34 +489,8 @@ int hu_spectrum_grad(hu_dims dims, const hu_filter* filt, uint64_t seed, hu_bins
     cy.sc.rev = 1;
     HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, 0, cy, st); }));
   }
-  GradCoefArgs ga{};
-  ga.dL_dP = dL_dP;
-  ga.cont_sum = cont_sum;
-  ga.cont_cnt = cont_cnt;
-  ga.stats = stats;
-  ga.nb = nb;
-  ga.N = g.N;
-  ga.sigma_f = filt->sigma_f;
-  ga.coef = coef;
-  HU_HIP(timed("grad_coef", st, [&] { return launch_grad_coef(ga, st); }));
-  AdjointArgs aa{};
-  aa.gm = axis0(g);
-  aa.ntiles = lay.tiles;
-  aa.spec = spec;
-  aa.Nh = g.Nhp;
-  aa.filt = filt_dev(*filt, g);
-  aa.width = (float)filt->width;
-  aa.bd = bd;
-  aa.nb = nb;
-  aa.table = geo.table;
-  aa.tw = tw_0;
-  aa.coef = coef;
-  aa.partials = partials;
-  int rows = 0;
-  HU_HIP(timed("cols_adjoint", st, [&] { return launch_cols_adjoint(g.n[0], aa, st, &rows); }));
-  GradFinalArgs fa{partials, rows, grad};
-  HU_HIP(timed("grad_final", st, [&] { return launch_grad_final(fa, st); }));
-  return HU_OK;
+  return enqueue_adjoint(g, *filt, bins, spec, dL_dP, cont_sum, cont_cnt, stats, grad,
+                         reinterpret_cast<double*>(w + lay.coef), reinterpret_cast<double*>(w + lay.partials), lay.tiles, st);
 }
 
 int hu_window_variance(hu_dims dims, int32_t batch, const void* x, int32_t dtype, const double* radii,

@@ -84,6 +84,8 @@ __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a
     tile_bins<L, E, C, LP, T, ColTile<L, V>::PWV>(lds, a.tb, pre, (int)tile, a.gm.ncol, a.parts + (long long)b * a.tb.M, tid);
   }
 
+  if (a.read_only) return;                       // uniform
+
   // ---- inverse transform along axis 0 (first radix = last forward radix: no exchange needed)
   fft_run<L, P, E, true, false, RV>(RadI{}, v, col_region<L, V, SPLIT>(lds, c), p, a.tw);
   __builtin_amdgcn_s_setprio(2);                 // the stores out ahead of other workgroups' transforms

@@ -919,7 +919,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
 
   // small 2D grids under plan entry whole_field: the whole path in one workgroup per field, the
   // half spectrum resident in LDS (the workspace is not touched)
-  if (r.plan.v[P_WHOLE] && whole_field_ok(g, nb)) {
+  if (r.plan.v[P_WHOLE] && whole_field_ok(g, nb) && !r.noise) {
     if (!batch_mode && B > MAX_WHOLE_CHUNK) return HU_ERR_ARG;
     const float2* tw_c;
     HU_TRY(get_tw(g.n[0], &tw_c, 0));
@@ -960,7 +960,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   const bool planes = g.nd == 3 && r.plan.v[P_PLANE] && plane_ok(g);
   const float2* tw_y0 = nullptr;
   if (planes) HU_TRY(get_tw(g.n[1], &tw_y0, 0));
-  float2* spec = reinterpret_cast<float2*>(r.work + r.lay.spec);
+  float2* spec = r.noise ? r.noise : reinterpret_cast<float2*>(r.work + r.lay.spec);
   double* partials = reinterpret_cast<double*>(r.work + r.lay.partials);
   double* fstats = reinterpret_cast<double*>(r.work + r.lay.fstats);
   double* parts_c = reinterpret_cast<double*>(r.work + r.lay.parts_c);
@@ -1028,6 +1028,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   fa.parts = want_cont ? parts_c : nullptr;
   fa.tw = tw_0;
   fa.partials = partials;
+  fa.read_only = r.noise ? 1 : 0;
   fa.any_gen = (batch_mode ? r.any_gen : filt_general(r.filt, g)) ? 1 : 0;
   if (fa.sc.ntiles > r.lay.tiles) return HU_ERR_WORKSPACE;
   HU_HIP(timed("cols_filter", st, [&] { return launch_cols_filter(g.n[0], r.plan.v[P_FILTER], fa, st, rad, r.plan.v[P_FSPLIT]); }));
@@ -1041,7 +1042,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   fz.io = r.io;
   HU_HIP(timed("finalize", st, [&] { return launch_finalize(fz, B, st); }));
 
-  if (g.nd == 3 && !planes)
+  if (g.nd == 3 && !planes && !r.noise)
     HU_HIP(timed("cols_y_inv", st, [&] { return launch_cols(g.n[1], true, r.plan.v[P_COLY], cy, st, rad); }));
 
   RowsZArgs za{};
@@ -1062,7 +1063,8 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   const bool want_counts = r.thresh && (batch_mode || o.counts != nullptr);
   uint32_t* cpart = reinterpret_cast<uint32_t*>(r.work + r.lay.cpart);
   za.cpart = want_counts ? cpart : nullptr;
-  if (planes) {
+  if (r.noise) {                             // no field
+  } else if (planes) {
     za.tw_y = tw_y0;
     za.pm1_spec = want_pm1 ? 1 : 0;
     HU_HIP(timed(r.thresh ? "plane_inv_thresh" : "plane_inv", st,

@@ -143,6 +143,9 @@ struct ClassRun {
   // workspace of this class
   char* work;
   Layout lay;
+  // the noise spectrum alone: statistics and continuous bins without the field; the spectra of the
+  // noise, transformed along every axis but axis 0, are left in `noise` ([B][Nhp], outside the workspace)
+  float2* noise;
 };
 int enqueue_class(const ClassRun& r, hipStream_t st);
 

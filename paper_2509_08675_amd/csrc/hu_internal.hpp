@@ -151,6 +151,7 @@ struct FilterArgs {
   const float2* tw;        // stage twiddle table of the axis length (StageTab layout)
   double* partials;        // [B][tiles][4]: sum w |F|^2, Re F(0), max ln chi
   int any_gen;             // some field uses a tabulated radial form or the FP64 filter evaluation
+  int read_only;           // statistics and bins alone: no inverse transform, the spectrum stays the noise's
 };
 
 struct FinalizeArgs {

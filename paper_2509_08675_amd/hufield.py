@@ -27,6 +27,7 @@ HU_F32, HU_I8 = 0, 1
 HU_OP_GEN_FIELD, HU_OP_PIPELINE, HU_OP_POWER_SPECTRUM, HU_OP_LOSS, HU_OP_FILTER_SPECTRUM = 0, 1, 2, 3, 4
 HU_OP_WINDOW_VARIANCE = 5
 HU_OP_TWO_POINT = 6
+HU_OP_NOISE, HU_OP_FIELD_SPECTRUM, HU_OP_NOISE_GRAD = 7, 8, 9
 HU_MAX_RADII = 32
 HU_CLASSES = ("hyperuniform class I", "hyperuniform class II", "hyperuniform class III",
               "nonhyperuniform (standard)", "antihyperuniform", "outside the classified range")
@@ -80,6 +81,8 @@ _lib.hu_plan_query.argtypes = [hu_dims, _i32, _P(hu_bins), _P(_i32)]
 _lib.hu_plan_set.argtypes = [hu_dims, _i32, _P(hu_bins), _P(_i32)]
 _lib.hu_filter_spectrum.argtypes = [hu_dims, _P(hu_filter), hu_bins, _vp, _vp, _vp, _sz, _vp]
 _lib.hu_spectrum_grad.argtypes = [hu_dims, _P(hu_filter), _u64, hu_bins, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
+_lib.hu_field_spectrum.argtypes = [hu_dims, _P(hu_filter), _u64, hu_bins, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
+_lib.hu_noise_grad.argtypes = [hu_dims, _P(hu_filter), _vp, hu_bins, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
 _lib.hu_window_variance.argtypes = [hu_dims, _i32, _vp, _i32, _P(ctypes.c_double), _i32, _vp, _vp, _sz, _vp]
 _lib.hu_small_k_exponent.argtypes = [_P(ctypes.c_double), _P(_u64), hu_bins, _i32, _P(ctypes.c_double)]
 _lib.hu_hyperuniformity_class.argtypes = [ctypes.c_double, _i32, ctypes.c_double]
@@ -92,7 +95,8 @@ for _f in ("hu_workspace_size", "hu_gen_field", "hu_threshold", "hu_power_spectr
            "hu_debug_philox", "hu_profile_enable", "hu_profile_read", "hu_workspace_size_batch",
            "hu_pipeline_batch", "hu_autotune", "hu_plan_query", "hu_plan_set", "hu_filter_spectrum",
            "hu_spectrum_grad", "hu_window_variance", "hu_small_k_exponent", "hu_hyperuniformity_class",
-           "hu_level_threshold", "hu_level_cut", "hu_two_point", "hu_debug_bin_tables", "hu_spectrum_loss"):
+           "hu_level_threshold", "hu_level_cut", "hu_two_point", "hu_debug_bin_tables", "hu_spectrum_loss",
+           "hu_field_spectrum", "hu_noise_grad"):
     getattr(_lib, _f).restype = ctypes.c_int
 
 
@@ -588,33 +592,60 @@ def spectrum_grad(dims, filt, seed, bins, dL_dP, cont_sum, cont_cnt, stats, work
     return grad
 
 
+def _field_spectrum(dims, filt, seed, bins, device):
+    """hu_field_spectrum: (noise spectrum, cont_sum [nb], cont_cnt [nb], stats [4]) of one field."""
+    nb = _nb(bins)
+    noise = alloc_workspace(HU_OP_NOISE, dims, 1, bins, device)
+    work = alloc_workspace(HU_OP_FIELD_SPECTRUM, dims, 1, bins, device)
+    stats = torch.empty((1, 4), dtype=torch.float64, device=device)
+    cs = torch.empty(nb, dtype=torch.float64, device=device)
+    cc = torch.empty(nb, dtype=torch.int64, device=device)
+    h = make_filter(filt)
+    _check(_lib.hu_field_spectrum(make_dims(dims), ctypes.byref(h), int(seed) & 0xFFFFFFFFFFFFFFFF, make_bins(bins),
+                                  _ptr(noise), _ptr(stats), _ptr(cs), _ptr(cc), _ptr(work), work.numel(),
+                                  _stream(device)), "hu_field_spectrum")
+    return noise, cs, cc, stats
+
+
+def _noise_grad(dims, filt, noise, bins, dL, cont_sum, cont_cnt, stats):
+    """hu_noise_grad: dL/dtheta [7] from the noise spectrum that _field_spectrum left."""
+    dev = noise.device
+    grad = torch.empty(7, dtype=torch.float64, device=dev)
+    work = alloc_workspace(HU_OP_NOISE_GRAD, dims, 1, bins, dev)
+    h = make_filter(filt)
+    dL = dL.to(device=dev, dtype=torch.float64).contiguous()
+    _check(_lib.hu_noise_grad(make_dims(dims), ctypes.byref(h), _ptr(noise), make_bins(bins), _ptr(dL), _ptr(cont_sum),
+                              _ptr(cont_cnt), _ptr(stats), _ptr(grad), _ptr(work), work.numel(), _stream(dev)),
+           "hu_noise_grad")
+    return grad
+
+
 class FilterSpectrum(torch.autograd.Function):
     """theta [7] = (a, b, c, p, rot, k0, w) -> the binned continuous spectrum P [R*A] (bin means,
     0 for empty bins) of the field generated on `dims` from `seed` with those filter parameters
-    (alpha and sigma_f fixed).  Forward: hu_gen_field; backward: hu_spectrum_grad (the noise is
-    regenerated from the seed)."""
+    (alpha and sigma_f fixed).  Forward: hu_field_spectrum; backward: hu_noise_grad on the noise
+    spectrum of the forward pass, a saved tensor as large as the field."""
 
     @staticmethod
     def forward(ctx, theta, dims, seed, bins, alpha, sigma_f=1.0):
         dims = tuple(int(n) for n in dims)
         filt = filter_with_theta(theta.detach().cpu().tolist(), alpha, sigma_f)
         dev = theta.device if theta.is_cuda else torch.device("cuda")
-        out = gen_field(dims, filt, [seed], cont_bins=bins, device=dev)
-        check_degenerate(out["stats"])
-        cs, cc, st = out["cont_sum"][0], out["cont_cnt"][0], out["stats"][0]
+        noise, cs, cc, st = _field_spectrum(dims, filt, seed, bins, dev)
+        check_degenerate(st)
         cnt = cc[:-1].to(torch.float64)
         P = torch.where(cnt > 0, cs[:-1] / cnt.clamp(min=1.0), torch.zeros_like(cnt))
-        ctx.save_for_backward(cs, cc, st)
-        ctx.meta = (dims, int(seed), tuple(bins), filt, theta.device, theta.dtype)
+        ctx.save_for_backward(noise, cs, cc, st)
+        ctx.meta = (dims, tuple(bins), filt, theta.device, theta.dtype)
         return P
 
     @staticmethod
     def backward(ctx, gP):
-        cs, cc, st = ctx.saved_tensors
-        dims, seed, bins, filt, tdev, tdt = ctx.meta
+        noise, cs, cc, st = ctx.saved_tensors
+        dims, bins, filt, tdev, tdt = ctx.meta
         dL = torch.zeros(cs.shape[0], dtype=torch.float64, device=cs.device)
         dL[:-1] = gP.to(device=cs.device, dtype=torch.float64)
-        g = spectrum_grad(dims, filt, seed, bins, dL, cs, cc, st)
+        g = _noise_grad(dims, filt, noise, bins, dL, cs, cc, st)
         return g.to(device=tdev, dtype=tdt), None, None, None, None, None
 
 
@@ -631,28 +662,27 @@ def spectrum_loss_value(bins, cont_sum, cont_cnt, tsum, tcnt, eps):
 
 class SpectrumLoss(torch.autograd.Function):
     """theta [7] -> the spectrum-matching loss of the field generated from `seed` with those filter
-    parameters against the binned target spectrum (tsum, tcnt).  Forward: hu_gen_field and
-    hu_spectrum_loss; backward: hu_spectrum_grad with the library's dL/dP (the noise is regenerated
-    from the seed)."""
+    parameters against the binned target spectrum (tsum, tcnt).  Forward: hu_field_spectrum and
+    hu_spectrum_loss; backward: hu_noise_grad with the library's dL/dP, on the noise spectrum of the
+    forward pass (a saved tensor as large as the field)."""
 
     @staticmethod
     def forward(ctx, theta, dims, seed, bins, alpha, sigma_f, tsum, tcnt, eps):
         dims = tuple(int(n) for n in dims)
         filt = filter_with_theta(theta.detach().cpu().tolist(), alpha, sigma_f)
         dev = theta.device if theta.is_cuda else torch.device("cuda")
-        out = gen_field(dims, filt, [seed], cont_bins=bins, device=dev)
-        check_degenerate(out["stats"])
-        cs, cc, st = out["cont_sum"][0], out["cont_cnt"][0], out["stats"][0]
+        noise, cs, cc, st = _field_spectrum(dims, filt, seed, bins, dev)
+        check_degenerate(st)
         loss, dL = spectrum_loss_value(bins, cs, cc, tsum, tcnt, eps)
-        ctx.save_for_backward(cs, cc, st, dL)
-        ctx.meta = (dims, int(seed), tuple(bins), filt, theta.device, theta.dtype)
+        ctx.save_for_backward(noise, cs, cc, st, dL)
+        ctx.meta = (dims, tuple(bins), filt, theta.device, theta.dtype)
         return loss.to(theta.dtype) if theta.dtype != torch.float64 else loss
 
     @staticmethod
     def backward(ctx, gL):
-        cs, cc, st, dL = ctx.saved_tensors
-        dims, seed, bins, filt, tdev, tdt = ctx.meta
-        g = spectrum_grad(dims, filt, seed, bins, dL * gL.to(device=dL.device, dtype=torch.float64), cs, cc, st)
+        noise, cs, cc, st, dL = ctx.saved_tensors
+        dims, bins, filt, tdev, tdt = ctx.meta
+        g = _noise_grad(dims, filt, noise, bins, dL * gL.to(device=dL.device, dtype=torch.float64), cs, cc, st)
         return g.to(device=tdev, dtype=tdt), None, None, None, None, None, None, None, None
 
 
