@@ -110,6 +110,7 @@ int hu::run_generator(hu_dims dims, int32_t batch, const hu_filter* filt, const 
     r.io = nullptr;
     r.work = reinterpret_cast<char*>(work);
     r.lay = lay;
+    r.amp = work_bytes >= lay.total_amp ? 1 : 0;
     HU_TRY(enqueue_class(r, st));
   }
   return HU_OK;
@@ -128,7 +129,7 @@ int hu_workspace_size(int op, hu_dims dims, int32_t batch, const hu_bins* bins, 
     case HU_OP_GEN_FIELD:
     case HU_OP_PIPELINE:
       HU_TRY(layout(g, chunk, true, widest_plan(), bins, &lay));
-      *bytes = lay.total;
+      *bytes = lay.total_amp;
       return HU_OK;
     case HU_OP_POWER_SPECTRUM:
       if (!bins) return HU_ERR_ARG;

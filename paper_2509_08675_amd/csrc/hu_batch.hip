@@ -306,7 +306,7 @@ int hu_autotune(hu_dims dims, int32_t batch, const hu_bins* bins, const char* ca
   mal((void**)&ps, sizeof(double) * nb * B);
   mal((void**)&cc, sizeof(uint64_t) * nb * B);
   mal((void**)&pc, sizeof(uint64_t) * nb * B);
-  mal((void**)&work, lay.total);
+  mal((void**)&work, lay.total_amp);
   hu_filter f{};
   f.p = 2.0;
   f.semi[0] = f.semi[1] = f.semi[2] = 1.0;
@@ -346,6 +346,7 @@ int hu_autotune(hu_dims dims, int32_t batch, const hu_bins* bins, const char* ca
         r.out = oc;
         r.work = work;
         r.lay = lay;
+        r.amp = 1;
         rc = enqueue_class(r, st);
       }
     };

@@ -236,12 +236,20 @@ __device__ __forceinline__ float amp_sym64(const FiltDev& f, const Axis0Geom& gm
     kz = k0c;
     ny_y = cc.nyq_y;
   }
-  const double l1 = ln_chi64<NDIM>(f, kx, ky, kz);
-  lnc = l1 > -1.0e299 ? (float)l1 : -1.0e30f;
-  float H = amp_from_lnchi64(l1, f.doffset);
-  if (f.rotated && (cc.nyq_x || ny_y)) {
-    const double l2 = ln_chi64<NDIM>(f, cc.nyq_x ? -kx : kx, ny_y ? -ky : ky, kz);
-    H = (float)(0.5 * ((double)H + (double)amp_from_lnchi64(l2, f.doffset)));
+  // a rolled loop over the mode and, on a Nyquist plane of a rotated filter, its partner: one copy of
+  // the FP64 evaluation
+  const int n = f.rotated && (cc.nyq_x || ny_y) ? 2 : 1;
+  float H = 0.0f;
+#pragma unroll 1
+  for (int k = 0; k < n; ++k) {
+    const double l = ln_chi64<NDIM>(f, k && cc.nyq_x ? -kx : kx, k && ny_y ? -ky : ky, kz);
+    const float h = amp_from_lnchi64(l, f.doffset);
+    if (k == 0) {
+      lnc = l > -1.0e299 ? (float)l : -1.0e30f;
+      H = h;
+    } else {
+      H = (float)(0.5 * ((double)H + (double)h));
+    }
   }
   return H;
 }

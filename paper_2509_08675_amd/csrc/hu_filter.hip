@@ -8,8 +8,12 @@
 
 namespace hu {
 
+// where the filter pass takes the amplitudes from: evaluated per mode in FP32, evaluated in the
+// general form (tabulated radial form or FP64), or read from the call's table (k_amp)
+enum { AMP_FP32 = 0, AMP_GENERAL = 1, AMP_TABLE = 2 };
+
 // One tile of C columns of one field per workgroup.
-template <int L, int NDIM, int V, bool GEN, int RV, bool SPLIT>
+template <int L, int NDIM, int V, int AMP, int RV, bool SPLIT>
 __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a) {
   constexpr int P = Plan<L>::P, E = Plan<L>::E, C = ColTile<L, V>::C, T = ColTile<L, V>::T;
   constexpr int LP = ColTile<L, V>::LP;
@@ -34,32 +38,53 @@ __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a
   fft_run<L, P, E, false, false, RV>(Rad{}, v, col_region<L, V, SPLIT>(lds, c), p, a.tw);
 
   // ---- filter and per-thread statistics
-  const FiltDev filt = a.io ? a.io[b].filt : a.filt;
   const ColCoord cc = col_coord(a.gm, valid ? g : 0);
+  FiltDev filt{};
+  if constexpr (AMP != AMP_TABLE) filt = a.io ? a.io[b].filt : a.filt;
   Col3 c3a{}, c3b{};
-  if constexpr (NDIM == 3) {                       // the column's x / y terms of the filter
+  if constexpr (AMP != AMP_TABLE && NDIM == 3) {   // the column's x / y terms of the filter
     c3a = col3(filt, cc.kx_c, cc.ky);
     c3b = (filt.rotated && (cc.nyq_x || cc.nyq_y)) ? col3(filt, cc.nyq_x ? -cc.kx_c : cc.kx_c, cc.nyq_y ? -cc.ky : cc.ky)
                                                    : c3a;
   }
   double gsum = 0.0, f0 = 0.0;
-  float lmax = filt.lnoffset;             // the lattice maximum of ln(chi_rel + offset) is at least ln offset
+  // the lattice maximum of ln(chi_rel + offset) is at least ln offset
+  float lmax = AMP == AMP_TABLE ? -1.0e30f : filt.lnoffset;
+  auto amplitude = [&](int e) {
+    float lnc;
+    const float h = NDIM == 3 ? amp_sym3<AMP == AMP_GENERAL>(filt, a.gm, cc, c3a, c3b, e, lnc)
+                              : amp_sym<NDIM, AMP == AMP_GENERAL>(filt, a.gm, cc, e, lnc);
+    if (valid) lmax = fmaxf(lmax, lnc);
+    return h;
+  };
   // the exchange buffer is free once every thread has its transform in registers: the power
   // values of the continuous spectrum go to LDS as they are computed
   float* pw = reinterpret_cast<float*>(lds);
+  float H[E];
+  if constexpr (AMP == AMP_TABLE) {                // all loads at once (in groups of four the pass took 8 % longer)
+    const rsrc_t ar = make_rsrc(a.amp + tile * (long long)(E * T), (unsigned)(E * T * 4));
+#pragma unroll
+    for (int s = 0; s < E; ++s)
+      H[s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ar, (unsigned)tid * 4u, (unsigned)(s * T * 4), 0));
+  } else if constexpr (AMP == AMP_GENERAL) {
+    // a rolled loop that leaves the amplitudes in LDS: unrolled over the slots the FP64 evaluation is tens
+    // of kilobytes of code
+    __syncthreads();
+#pragma unroll 1
+    for (int s = 0; s < E; ++s) pw[s * T + tid] = amplitude(slot_index<L, RL, P>(s, p));
+#pragma unroll
+    for (int s = 0; s < E; ++s) H[s] = pw[s * T + tid];
+  }
   if (do_bins) __syncthreads();
 #pragma unroll
   for (int s = 0; s < E; ++s) {
     const int e = slot_index<L, RL, P>(s, p);
-    float lnc;
-    const float H = NDIM == 3 ? amp_sym3<GEN>(filt, a.gm, cc, c3a, c3b, e, lnc) : amp_sym<NDIM, GEN>(filt, a.gm, cc, e, lnc);
-    const float2 F = cscale(v[s], H);
+    const float2 F = cscale(v[s], AMP == AMP_FP32 ? amplitude(e) : H[s]);
     v[s] = F;
     const float m2 = cc.wm * (F.x * F.x + F.y * F.y);
     if (do_bins) pw[c * LP + pw_index(e)] = valid ? m2 : 0.0f;
     if (valid) {
       gsum += (double)m2;
-      lmax = fmaxf(lmax, lnc);
       if (g == 0 && e == 0) f0 = (double)F.x;
     }
   }
@@ -94,6 +119,68 @@ __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a
 }
 
 // ---------------------------------------------------------------------------------------------
+// The symmetrised amplitudes of one filter for every mode, in the order in which the threads of the
+// filter pass hold them ([tile][slot][thread]: a wave reads 256 consecutive bytes), and the maximum of
+// ln chi over the modes of each workgroup.  A workgroup: 256 threads of a tile, AMP_SLOTS of the slots
+// (one 1024^2 field still gives every SIMD two waves), then the next tiles.
+// ---------------------------------------------------------------------------------------------
+template <int NDIM, bool GEN>
+__global__ void __launch_bounds__(256) k_amp(AmpArgs a) {
+  __shared__ float red[4];
+  float lmax = a.filt.lnoffset;
+  const int nbt = (a.T + 255) / 256;
+  for (int blk = blockIdx.x; blk < a.ntiles * nbt; blk += gridDim.x) {
+    const int tile = blk / nbt, tid = (blk - tile * nbt) * 256 + (int)threadIdx.x;
+    if (tid >= a.T) continue;
+    const int p = tid / a.C, c = tid - p * a.C;
+    const int g = tile * a.C + c;
+    const bool valid = g < a.gm.ncol;
+    const ColCoord cc = col_coord(a.gm, valid ? g : 0);
+    Col3 c3a{}, c3b{};
+    if constexpr (NDIM == 3) {
+      c3a = col3(a.filt, cc.kx_c, cc.ky);
+      c3b = (a.filt.rotated && (cc.nyq_x || cc.nyq_y))
+                ? col3(a.filt, cc.nyq_x ? -cc.kx_c : cc.kx_c, cc.nyq_y ? -cc.ky : cc.ky) : c3a;
+    }
+    float* out = a.amp + (long long)tile * (a.E * a.T) + tid;
+#pragma unroll GEN ? 1 : AMP_SLOTS
+    for (int u = 0; u < AMP_SLOTS; ++u) {
+      const int s = (int)blockIdx.y * AMP_SLOTS + u;
+      if (s >= a.E) break;                         // uniform
+      const int e = p + a.P * (s / a.R) + (s % a.R) * (a.gm.n0 / a.R);   // slot_index
+      float lnc;
+      const float H = NDIM == 3 ? amp_sym3<GEN>(a.filt, a.gm, cc, c3a, c3b, e, lnc) : amp_sym<NDIM, GEN>(a.filt, a.gm, cc, e, lnc);
+      out[(long long)s * a.T] = H;
+      if (valid) lmax = fmaxf(lmax, lnc);
+    }
+  }
+  lmax = wave_max(lmax);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = lmax;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    a.amax[blockIdx.y * gridDim.x + blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+}
+
+hipError_t launch_amp(AmpArgs a, int L, int radix, int general, hipStream_t st, int* blocks) {
+  switch (L) {
+#define X(LL) case LL: a.R = radix ? RadInfo<Plan<LL, 1>::fwd>::last : RadInfo<Plan<LL, 0>::fwd>::last; break;
+    HU_COL_LENGTHS(X)
+#undef X
+    default: return hipErrorInvalidValue;
+  }
+  a.E = col_elems(L);
+  a.P = L / a.E;
+  a.T = a.C * a.P;
+  const long long n = (long long)a.ntiles * ((a.T + 255) / 256);
+  const dim3 grid((unsigned)(n < AMP_MAX_BLOCKS ? n : AMP_MAX_BLOCKS), (unsigned)((a.E + AMP_SLOTS - 1) / AMP_SLOTS));
+  *blocks = (int)(grid.x * grid.y);
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, a); };
+  if (a.gm.ndim == 2) general ? go(k_amp<2, true>) : go(k_amp<2, false>);
+  else general ? go(k_amp<3, true>) : go(k_amp<3, false>);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------
 // finalize: one workgroup per field turns the filter pass's partials into mu, var and the
 // normalisation constants (Eq. (15) via Parseval) with a fixed-order reduction, and the factor
 // that turns the continuous-field bins into the spectrum of the normalised field.
@@ -113,6 +200,7 @@ __global__ void __launch_bounds__(256) k_finalize(FinalizeArgs a) {
     F0 += part[4 * w + 1];
     lm = fmaxf(lm, (float)part[4 * w + 2]);
   }
+  for (int w = tid; w < a.namax; w += 256) lm = fmaxf(lm, a.amax[w]);   // the table's maxima
   sg[tid] = G;
   sf[tid] = F0;
   sm[tid] = lm;
@@ -158,14 +246,19 @@ static hipError_t launch_cols_filter_L(FilterArgs a, hipStream_t st) {
   constexpr int T = ColTile<L, V>::T;
   size_t lds = col_xchg_bytes<L, V, SPLIT>();
   if (a.parts) lds = col_bin_bytes<L, V, SPLIT>(a.tb);
-  // the tabulated-form and FP64 branches only in the instantiation launched when a field may use one
+  // with a table the pass does not depend on the dimension; the general form only in the instantiation
+  // launched when a field may use it (complex exchange alone: the exchange does not change the bits)
+  if constexpr (SPLIT) {
+    if (!a.amp && a.any_gen) return launch_cols_filter_L<L, V, RV, false>(a, st);
+  }
   const dim3 grid(sched_blocks(a.sc));
-  if (a.gm.ndim == 2) {
-    if (a.any_gen) hipLaunchKernelGGL((k_cols_filter<L, 2, V, true, RV, SPLIT>), grid, dim3(T), lds, st, a);
-    else hipLaunchKernelGGL((k_cols_filter<L, 2, V, false, RV, SPLIT>), grid, dim3(T), lds, st, a);
+  auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(T), lds, st, a); };
+  if (a.amp) go(k_cols_filter<L, 2, V, AMP_TABLE, RV, SPLIT>);
+  else if (a.any_gen) {
+    if constexpr (!SPLIT)
+      a.gm.ndim == 2 ? go(k_cols_filter<L, 2, V, AMP_GENERAL, RV, false>) : go(k_cols_filter<L, 3, V, AMP_GENERAL, RV, false>);
   } else {
-    if (a.any_gen) hipLaunchKernelGGL((k_cols_filter<L, 3, V, true, RV, SPLIT>), grid, dim3(T), lds, st, a);
-    else hipLaunchKernelGGL((k_cols_filter<L, 3, V, false, RV, SPLIT>), grid, dim3(T), lds, st, a);
+    a.gm.ndim == 2 ? go(k_cols_filter<L, 2, V, AMP_FP32, RV, SPLIT>) : go(k_cols_filter<L, 3, V, AMP_FP32, RV, SPLIT>);
   }
   return hipGetLastError();
 }

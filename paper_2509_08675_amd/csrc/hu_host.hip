@@ -423,6 +423,16 @@ int layout(const Geom& g, int batch, bool need_stats, const TunePlan& plan, cons
     off += up256((size_t)batch * M * sizeof(double));
   }
   L.total = off;
+  if (need_stats) {                               // amplitudes of every mode, for tiles of either width
+    size_t cols = 0;
+    for (int v = 0; v < NVARIANT; ++v)
+      cols = std::max(cols, (size_t)col_tiles(g.n[0], v, g.Nh / g.n[0]) * col_width(g.n[0], v));
+    L.amp = off;
+    off += up256(cols * g.n[0] * sizeof(float));
+    L.amax = off;
+    off += up256(6 * AMP_MAX_BLOCKS * sizeof(float));
+  }
+  L.total_amp = off;
   *out = L;
   return HU_OK;
 }
@@ -967,6 +977,28 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   double* parts_p = reinterpret_cast<double*>(r.work + r.lay.parts_p);
   const uint32_t* cnt_src = reinterpret_cast<const uint32_t*>(geo.counts);
 
+  // A uniform batch's amplitudes from a table where that pays, evaluated once for all fields (the fields
+  // of a tile run on one XCD in 2D, whose L2 serves it).  General forms: always (FP64 in the filter
+  // pass's few workgroups: one 1024^2 field, alpha 20, 43 us; table and pass together 26).  FP32: in 2D
+  // from 2^23 modes on (its kernel costs one launch, 6-8 us; 2048^2: 4 fields even, 8 fields 102 -> 91 us,
+  // 16 fields 190 -> 174; 8 x 512^2 1 us slower).  In 3D the evaluation is cheaper and a table's share of
+  // the traffic larger (4 x 256^3: 10 us gained for 20 spent).
+  const bool general = batch_mode ? r.any_gen : filt_general(r.filt, g);
+  const bool use_amp = !batch_mode && r.amp && (general || (g.nd == 2 && B * g.Nh >= (1LL << 23)));
+  float* amp = reinterpret_cast<float*>(r.work + r.lay.amp);
+  float* amax = reinterpret_cast<float*>(r.work + r.lay.amax);
+  int namax = 0;
+  if (use_amp) {
+    AmpArgs aa{};
+    aa.gm = axis0(g);
+    aa.filt = filt_dev(r.filt, g);
+    aa.C = col_width(g.n[0], r.plan.v[P_FILTER]);
+    aa.ntiles = col_tiles(g.n[0], r.plan.v[P_FILTER], aa.gm.ncol);
+    aa.amp = amp;
+    aa.amax = amax;
+    HU_HIP(timed("amp", st, [&] { return launch_amp(aa, g.n[0], rad, general, st, &namax); }));
+  }
+
   // pass A: noise -> R2C rows; block 0 of each field sets up that field's bin counts
   RowsArgs ra{};
   ra.spec = spec;
@@ -1029,7 +1061,8 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   fa.tw = tw_0;
   fa.partials = partials;
   fa.read_only = r.noise ? 1 : 0;
-  fa.any_gen = (batch_mode ? r.any_gen : filt_general(r.filt, g)) ? 1 : 0;
+  fa.any_gen = general ? 1 : 0;
+  fa.amp = use_amp ? amp : nullptr;
   if (fa.sc.ntiles > r.lay.tiles) return HU_ERR_WORKSPACE;
   HU_HIP(timed("cols_filter", st, [&] { return launch_cols_filter(g.n[0], r.plan.v[P_FILTER], fa, st, rad, r.plan.v[P_FSPLIT]); }));
   FinalizeArgs fz{};
@@ -1040,6 +1073,8 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   fz.fstats = fstats;
   fz.stats = batch_mode ? nullptr : o.stats;
   fz.io = r.io;
+  fz.amax = amax;
+  fz.namax = namax;
   HU_HIP(timed("finalize", st, [&] { return launch_finalize(fz, B, st); }));
 
   if (g.nd == 3 && !planes && !r.noise)

@@ -59,6 +59,7 @@ struct TunePlan {
 // +-1 (parts_p) spectra.
 struct Layout {
   size_t spec, partials, fstats, cpart, parts_c, parts_p, total;
+  size_t amp, amax, total_amp;   // after `total`: the amplitude table of a uniform batch (used where the workspace has room)
   int tiles;
   int Mc, Mp;                    // tile partials per field of each spectrum (0: none)
 };
@@ -146,6 +147,7 @@ struct ClassRun {
   // the noise spectrum alone: statistics and continuous bins without the field; the spectra of the
   // noise, transformed along every axis but axis 0, are left in `noise` ([B][Nhp], outside the workspace)
   float2* noise;
+  int amp;                 // the workspace has room for the amplitude table
 };
 int enqueue_class(const ClassRun& r, hipStream_t st);
 

@@ -152,6 +152,19 @@ struct FilterArgs {
   double* partials;        // [B][tiles][4]: sum w |F|^2, Re F(0), max ln chi
   int any_gen;             // some field uses a tabulated radial form or the FP64 filter evaluation
   int read_only;           // statistics and bins alone: no inverse transform, the spectrum stays the noise's
+  const float* amp;        // the call's amplitudes (AmpArgs), or null: evaluated in the pass
+};
+
+// The amplitudes of one filter in the layout of the filter pass: [tile][slot][thread of the tile].
+constexpr int AMP_SLOTS = 4;             // slots per thread
+constexpr int AMP_MAX_BLOCKS = 256;      // workgroups over the tiles; times up to 6 over the slots
+struct AmpArgs {
+  Axis0Geom gm;
+  FiltDev filt;
+  int ntiles, C;           // tiles of C columns
+  int P, E, R, T;          // threads per column, slots, last forward radix, threads per tile (set by the launcher)
+  float* amp;
+  float* amax;             // [workgroups]: maximum of ln chi over the workgroup's modes
 };
 
 struct FinalizeArgs {
@@ -162,6 +175,8 @@ struct FinalizeArgs {
   double* fstats;          // [B][8] mu, var, max ln chi, flag, scale, offset, spectrum factor, G
   double* stats;           // [B][4] user copy or null
   const FieldIO* io;
+  const float* amax;       // [namax] maxima of ln chi left by the amplitude table's kernel
+  int namax;
 };
 
 struct BinArgs {
@@ -344,6 +359,8 @@ hipError_t launch_rows_r2c(int L, int src, int variant, const RowsArgs& a, int b
 hipError_t launch_cols(int L, bool inv, int variant, const ColsArgs& a, hipStream_t st, int radix = 0);
 // split: the split exchange (real and imaginary parts in two rounds, half the LDS), lengths >= 192
 hipError_t launch_cols_filter(int L, int variant, const FilterArgs& a, hipStream_t st, int radix = 0, int split = 0);
+// the amplitude table for axis-0 length L under radix choice `radix`; *blocks: its workgroups (amax entries)
+hipError_t launch_amp(AmpArgs a, int L, int radix, int general, hipStream_t st, int* blocks);
 // columns per tile of the axis-0 passes with tile variant `variant`, and their elements per thread
 int col_width(int L, int variant);
 int col_elems(int L);
