@@ -86,16 +86,20 @@ int hu::run_generator(hu_dims dims, int32_t batch, const hu_filter* filt, const 
   for (const void* p : ptrs)
     if (p && !aligned(p, 16)) return HU_ERR_ALIGN;
   if (!work || !aligned(work, 256)) return work ? HU_ERR_ALIGN : HU_ERR_ARG;
-  const int chunk = batch < MAX_CHUNK ? batch : MAX_CHUNK;
+  int chunk = chunk_fields(g, batch);
   const TunePlan plan = get_plan(g, bins, batch);
   Layout lay;
   HU_TRY(layout(g, chunk, true, plan, bins, &lay));
+  if (work_bytes < lay.total && chunk > BASE_CHUNK) {          // a workspace for fewer fields at a time
+    chunk = BASE_CHUNK;
+    HU_TRY(layout(g, chunk, true, plan, bins, &lay));
+  }
   if (work_bytes < lay.total) return HU_ERR_WORKSPACE;
   const int nb = bins ? bins->n_radial * bins->n_angular + 1 : 0;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   HU_TRY(prepare_tables(g, bins, st));
   // the whole-field kernel takes more fields per launch (it uses no workspace)
-  const int step = plan.v[P_WHOLE] && whole_field_ok(g, nb) ? MAX_WHOLE_CHUNK : MAX_CHUNK;
+  const int step = plan.v[P_WHOLE] && whole_field_ok(g, nb) ? MAX_WHOLE_CHUNK : chunk;
   for (int f0 = 0; f0 < batch; f0 += step) {
     ClassRun r{};
     r.g = g;
@@ -123,7 +127,7 @@ int hu_workspace_size(int op, hu_dims dims, int32_t batch, const hu_bins* bins, 
   Geom g;
   HU_TRY(make_geom(dims, &g));
   if (bins) HU_TRY(check_bins(bins, g.nd));
-  const int chunk = batch < MAX_CHUNK ? batch : MAX_CHUNK;
+  const int chunk = chunk_fields(g, batch);
   Layout lay;
   switch (op) {
     case HU_OP_GEN_FIELD:
@@ -214,7 +218,12 @@ int hu_power_spectrum(hu_dims dims, int32_t batch, const void* x, int32_t dtype,
   if (!work || !aligned(work, 256)) return work ? HU_ERR_ALIGN : HU_ERR_ARG;
   const TunePlan plan{{0, 0, 0, 0, 0}};
   Layout lay;
-  HU_TRY(layout(g, batch < MAX_CHUNK ? batch : MAX_CHUNK, false, plan, &bins, &lay));
+  int chunk = chunk_fields(g, batch);
+  HU_TRY(layout(g, chunk, false, plan, &bins, &lay));
+  if (work_bytes < lay.total && chunk > BASE_CHUNK) {
+    chunk = BASE_CHUNK;
+    HU_TRY(layout(g, chunk, false, plan, &bins, &lay));
+  }
   if (work_bytes < lay.total) return HU_ERR_WORKSPACE;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   HU_TRY(prepare_tables(g, &bins, st));
@@ -233,8 +242,8 @@ int hu_power_spectrum(hu_dims dims, int32_t batch, const void* x, int32_t dtype,
   float2* spec = reinterpret_cast<float2*>(reinterpret_cast<char*>(work) + lay.spec);
   double* parts = reinterpret_cast<double*>(reinterpret_cast<char*>(work) + lay.parts_p);
   const size_t esz = dtype == HU_F32 ? 4 : 1;
-  for (int f0 = 0; f0 < batch; f0 += MAX_CHUNK) {
-    const int B = batch - f0 < MAX_CHUNK ? batch - f0 : MAX_CHUNK;
+  for (int f0 = 0; f0 < batch; f0 += chunk) {
+    const int B = batch - f0 < chunk ? batch - f0 : chunk;
     RowsArgs ra{};
     ra.spec = spec;
     ra.Nh = g.Nhp;
@@ -505,8 +514,9 @@ int hu_window_variance(hu_dims dims, int32_t batch, const void* x, int32_t dtype
     if (!std::isfinite(radii[j]) || radii[j] < 0.0 || radii[j] > 1e30) return HU_ERR_ARG;
   if (!aligned(x, 16) || !aligned(out, 16)) return HU_ERR_ALIGN;
   if (!work || !aligned(work, 256)) return work ? HU_ERR_ALIGN : HU_ERR_ARG;
-  const int chunk = batch < MAX_CHUNK ? batch : MAX_CHUNK;
-  const WvarLayout lay = wvar_layout(g, chunk);
+  int chunk = chunk_fields(g, batch);
+  WvarLayout lay = wvar_layout(g, chunk);
+  if (work_bytes < lay.total && chunk > BASE_CHUNK) lay = wvar_layout(g, chunk = BASE_CHUNK);
   if (work_bytes < lay.total) return HU_ERR_WORKSPACE;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const int Lrow = g.nx / 2;
@@ -519,8 +529,8 @@ int hu_window_variance(hu_dims dims, int32_t batch, const void* x, int32_t dtype
   float2* spec = reinterpret_cast<float2*>(w + lay.spec);
   double* partials = reinterpret_cast<double*>(w + lay.partials);
   const size_t esz = dtype == HU_F32 ? 4 : 1;
-  for (int f0 = 0; f0 < batch; f0 += MAX_CHUNK) {
-    const int B = batch - f0 < MAX_CHUNK ? batch - f0 : MAX_CHUNK;
+  for (int f0 = 0; f0 < batch; f0 += chunk) {
+    const int B = batch - f0 < chunk ? batch - f0 : chunk;
     RowsArgs ra{};
     ra.spec = spec;
     ra.Nh = g.Nhp;
@@ -620,9 +630,13 @@ int hu_two_point(hu_dims dims, int32_t batch, const int8_t* pm1, float* s2, void
   if (batch < 1 || !pm1 || !s2) return HU_ERR_ARG;
   if (!aligned(pm1, 16) || !aligned(s2, 16)) return HU_ERR_ALIGN;
   if (!work || !aligned(work, 256)) return work ? HU_ERR_ALIGN : HU_ERR_ARG;
-  const int chunk = batch < MAX_CHUNK ? batch : MAX_CHUNK;
+  int chunk = chunk_fields(g, batch);
   Layout lay;
   HU_TRY(layout(g, chunk, true, TunePlan{}, nullptr, &lay));
+  if (work_bytes < lay.total && chunk > BASE_CHUNK) {
+    chunk = BASE_CHUNK;
+    HU_TRY(layout(g, chunk, true, TunePlan{}, nullptr, &lay));
+  }
   if (work_bytes < lay.total) return HU_ERR_WORKSPACE;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const int Lrow = g.nx / 2;
@@ -634,8 +648,8 @@ int hu_two_point(hu_dims dims, int32_t batch, const int8_t* pm1, float* s2, void
   char* w = reinterpret_cast<char*>(work);
   float2* spec = reinterpret_cast<float2*>(w + lay.spec);
   double* fstats = reinterpret_cast<double*>(w + lay.fstats);
-  for (int f0 = 0; f0 < batch; f0 += MAX_CHUNK) {
-    const int B = batch - f0 < MAX_CHUNK ? batch - f0 : MAX_CHUNK;
+  for (int f0 = 0; f0 < batch; f0 += chunk) {
+    const int B = batch - f0 < chunk ? batch - f0 : chunk;
     RowsArgs ra{};
     ra.spec = spec;
     ra.Nh = g.Nhp;

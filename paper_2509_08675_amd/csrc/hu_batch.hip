@@ -284,7 +284,7 @@ int hu_autotune(hu_dims dims, int32_t batch, const hu_bins* bins, const char* ca
   HU_TRY(check_bins(bins, g.nd));
   const int B = batch;
   const int nb = bins->n_radial * bins->n_angular + 1;
-  const int chunk = B < MAX_CHUNK ? B : MAX_CHUNK;
+  const int chunk = chunk_fields(g, B);
   Layout lay;
   HU_TRY(layout(g, chunk, true, widest(), bins, &lay));
   hipStream_t st = nullptr;
@@ -323,7 +323,7 @@ int hu_autotune(hu_dims dims, int32_t batch, const hu_bins* bins, const char* ca
   // the summed mean kernel time of the whole pass sequence under a plan (2 untimed runs, 5 timed)
   auto time_plan = [&](const TunePlan& plan) -> double {
     auto run = [&]() {
-      const int step = plan.v[P_WHOLE] && whole_field_ok(g, nb) ? MAX_WHOLE_CHUNK : MAX_CHUNK;
+      const int step = plan.v[P_WHOLE] && whole_field_ok(g, nb) ? MAX_WHOLE_CHUNK : chunk;
       for (int f0 = 0; f0 < B && rc == HU_OK; f0 += step) {
         ClassRun r{};
         r.g = g;

@@ -383,6 +383,15 @@ bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// 64 fields of 128^2 are 4 MB of spectra and leave most of the chip idle: their six launches took 53 us, and
+// 256 fields four times that.  2D grids take up to 256 fields while their spectra stay within 128 MB, half the
+// memory-side cache (256 x 128^2: 212 -> 119 us); from 512 x 512 on 64 fields fill the chip anyway.
+int chunk_fields(const Geom& g, int batch) {
+  long long n = g.nd == 2 ? (128LL << 20) / (g.Nhp * (long long)sizeof(float2)) : 0;
+  n = n < BASE_CHUNK ? BASE_CHUNK : n > MAX_CHUNK ? MAX_CHUNK : n;
+  return batch < n ? batch : (int)n;
+}
+
 int tile_partials(const Geom& g, const hu_bins& bins, int C, int* M, int* nloc_max);
 
 int layout(const Geom& g, int batch, bool need_stats, const TunePlan& plan, const hu_bins* bins, Layout* out) {

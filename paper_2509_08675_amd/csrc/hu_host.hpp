@@ -73,6 +73,8 @@ int make_geom(const hu_dims& d, Geom* g);
 int check_filter(const hu_filter* f, int nd);
 int check_bins(const hu_bins* b, int nd);
 bool aligned(const void* p, size_t a);
+// fields that a uniform call of `batch` fields takes per launch sequence, given room for them
+int chunk_fields(const Geom& g, int batch);
 size_t up256(size_t x);
 // need_stats: the generator's layout (filter statistics, sign counts, both spectra); otherwise the
 // binning of a stored input.  bins: null when no spectrum is binned.  Builds the host bin tables of

@@ -15,7 +15,9 @@ constexpr bool split_length(int L) { return L >= 192; }
 
 
 enum { SRC_NOISE = 0, SRC_F32 = 1, SRC_I8 = 2 };
-constexpr int MAX_CHUNK = 64;   // fields per launch when seeds travel in the kernel arguments
+// fields per launch when seeds travel in the kernel arguments: 64 (what every workspace holds), of
+// small 2D grids up to 256 (chunk_fields)
+constexpr int BASE_CHUNK = 64, MAX_CHUNK = 256;
 // fields per launch of the whole-field kernel, which needs no workspace: enough to give every CU
 // a field (its arguments stay under the 4 KB kernel-argument limit)
 constexpr int MAX_WHOLE_CHUNK = 256;

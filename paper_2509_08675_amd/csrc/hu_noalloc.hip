@@ -42,7 +42,7 @@ extern "C" int hu_pipeline_noalloc(hu_dims dims, int32_t batch, const hu_filter*
   if (batch < 1 || !seeds) return HU_ERR_ARG;
   HU_TRY(check_bins(&bins, g.nd));
   // the half spectra alone beyond the fixed array: refused before anything else
-  const int chunk = batch < MAX_CHUNK ? batch : MAX_CHUNK;
+  const int chunk = batch < BASE_CHUNK ? batch : BASE_CHUNK;
   if ((size_t)chunk * (size_t)g.Nhp * 8 > HU_NOALLOC_WORK_BYTES) return HU_ERR_WORKSPACE;
   // the tables must exist already: building them would allocate
   HU_TRY(tables_ready(g, &bins));

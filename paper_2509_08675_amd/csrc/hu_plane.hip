@@ -172,7 +172,7 @@ __global__ void __launch_bounds__((PlaneShape<LR, NY>::T)) k_plane_fwd(RowsArgs 
       seed = a.io[b].seed;
     } else {
 #pragma unroll
-      for (int i = 0; i < MAX_CHUNK; ++i) seed = i == b ? a.seeds[i] : seed;
+      for (int i = 0; i < BASE_CHUNK; ++i) seed = i == b ? a.seeds[i] : seed;
     }
     seed = uniform_u64(seed);
     float2* lrow = plane + r * RSR;
