@@ -592,4 +592,67 @@ __device__ __forceinline__ T* field_ptr(T* base, long long stride, int b) {
   return base ? base + (long long)b * stride : nullptr;
 }
 
+// Eq. (15) via Parseval from the totals of the filter pass over field b: sum w |F|^2, Re F(0) and the
+// maximum of ln chi.  The constants of the last row pass are returned; `write` leaves them (with the
+// factor that turns the continuous-field bins into the spectrum of the normalised field) in fstats
+// and the statistics in the caller's output.
+__device__ __forceinline__ void finalize_field(const FinalizeArgs& a, int b, double Gt, double F0, double lmx, bool write,
+                                               float& scale, float& offset) {
+  const double sigma_f = a.io ? a.io[b].sigma_f : a.sigma_f;
+  const double N = (double)a.N;
+  const double mu = F0 / N;                     // Re F(0) / N
+  const double var = Gt / (N * N) - mu * mu;    // Parseval, population variance
+  const bool degenerate = !(lmx >= -80.0) || !(var > 0.0);
+  const double sd = degenerate ? 1.0 : sqrt(var);
+  const double sc = degenerate ? 0.0 : sigma_f / (N * sd);      // scale of the unnormalised inverse
+  const double of = degenerate ? 0.0 : -sigma_f * mu / sd;      // offset
+  scale = (float)sc;
+  offset = (float)of;
+  if (!write) return;
+  double* fs = a.fstats + (long long)b * 8;
+  fs[0] = mu;
+  fs[1] = var;
+  fs[2] = lmx;
+  fs[3] = degenerate ? 1.0 : 0.0;
+  fs[4] = sc;
+  fs[5] = of;
+  fs[6] = degenerate ? 0.0 : sigma_f * sigma_f / (N * var);   // continuous-spectrum factor
+  fs[7] = Gt;
+  double* stats_out = a.io ? a.io[b].stats : field_ptr(a.stats, 4, b);
+  if (stats_out) {
+    stats_out[0] = mu; stats_out[1] = var; stats_out[2] = lmx; stats_out[3] = fs[3];
+  }
+}
+
+// k_finalize's sums for at most FOLD_TILES = 256 tiles by one wave, added in the same order: lane l holds
+// what threads l, l + 64, l + 128 and l + 192 of its 256 do.
+struct FoldLoad {
+  double g[4], f[4];
+  float m;
+};
+__device__ __forceinline__ FoldLoad fold_load(const FinalizeArgs& a, int b, int lane) {
+  FoldLoad x;
+  x.m = -1.0e30f;
+  const double* part = a.partials + (long long)b * a.ntiles * 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int w = lane + 64 * q;
+    x.g[q] = w < a.ntiles ? part[4 * w] : 0.0;
+    x.f[q] = w < a.ntiles ? part[4 * w + 1] : 0.0;
+    if (w < a.ntiles) x.m = fmaxf(x.m, (float)part[4 * w + 2]);
+  }
+  for (int w = lane; w < a.namax; w += 64) x.m = fmaxf(x.m, a.amax[w]);
+  return x;
+}
+__device__ __forceinline__ void fold_sums(FoldLoad& x) {      // the totals in lane 0
+  x.g[0] = (x.g[0] + x.g[2]) + (x.g[1] + x.g[3]);
+  x.f[0] = (x.f[0] + x.f[2]) + (x.f[1] + x.f[3]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    x.g[0] += __shfl_down(x.g[0], o, 64);
+    x.f[0] += __shfl_down(x.f[0], o, 64);
+  }
+  x.m = wave_max(x.m);
+}
+
 }  // namespace hu

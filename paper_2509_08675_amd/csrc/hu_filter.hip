@@ -190,8 +190,6 @@ __global__ void __launch_bounds__(256) k_finalize(FinalizeArgs a) {
   __shared__ float sm[256];
   const int b = blockIdx.x, tid = threadIdx.x;
   const double* part = a.partials + (long long)b * a.ntiles * 4;
-  const double sigma_f = a.io ? a.io[b].sigma_f : a.sigma_f;
-  double* stats_out = a.io ? a.io[b].stats : field_ptr(a.stats, 4, b);
   double G = 0.0, F0 = 0.0;
   float lm = -1.0e30f;
 #pragma unroll 4
@@ -214,25 +212,8 @@ __global__ void __launch_bounds__(256) k_finalize(FinalizeArgs a) {
     __syncthreads();
   }
   if (tid == 0) {
-    const double N = (double)a.N;
-    const double Gt = sg[0];
-    const double mu = sf[0] / N;                  // Re F(0) / N
-    const double var = Gt / (N * N) - mu * mu;    // Parseval, population variance
-    const double lmx = (double)sm[0];
-    const bool degenerate = !(lmx >= -80.0) || !(var > 0.0);
-    const double sd = degenerate ? 1.0 : sqrt(var);
-    double* fs = a.fstats + (long long)b * 8;
-    fs[0] = mu;
-    fs[1] = var;
-    fs[2] = lmx;
-    fs[3] = degenerate ? 1.0 : 0.0;
-    fs[4] = degenerate ? 0.0 : sigma_f / (N * sd);             // scale of the unnormalised inverse
-    fs[5] = degenerate ? 0.0 : -sigma_f * mu / sd;              // offset
-    fs[6] = degenerate ? 0.0 : sigma_f * sigma_f / (N * var);   // continuous-spectrum factor
-    fs[7] = Gt;
-    if (stats_out) {
-      stats_out[0] = mu; stats_out[1] = var; stats_out[2] = lmx; stats_out[3] = fs[3];
-    }
+    float scale, offset;
+    finalize_field(a, b, sg[0], sf[0], (double)sm[0], true, scale, offset);
   }
 }
 

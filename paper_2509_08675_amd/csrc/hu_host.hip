@@ -1084,7 +1084,9 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   fz.io = r.io;
   fz.amax = amax;
   fz.namax = namax;
-  HU_HIP(timed("finalize", st, [&] { return launch_finalize(fz, B, st); }));
+  // few filter tiles: the last row pass forms the statistics itself
+  const bool fold = fz.ntiles <= FOLD_TILES && !planes && !r.noise;
+  if (!fold) HU_HIP(timed("finalize", st, [&] { return launch_finalize(fz, B, st); }));
 
   if (g.nd == 3 && !planes && !r.noise)
     HU_HIP(timed("cols_y_inv", st, [&] { return launch_cols(g.n[1], true, r.plan.v[P_COLY], cy, st, rad); }));
@@ -1098,6 +1100,8 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   za.tw = tw_row;
   za.tw2 = tw2_row;
   za.fstats = fstats;
+  za.fold = fold ? 1 : 0;
+  za.fin = fz;
   za.io = r.io;
   if (!batch_mode) {
     za.field = o.field;

@@ -181,6 +181,8 @@ struct FinalizeArgs {
   int namax;
 };
 
+constexpr int FOLD_TILES = 256;
+
 struct BinArgs {
   ColSched sc;
   const float2* spec;
@@ -225,6 +227,10 @@ struct RowsZArgs {
   const FieldIO* io;       // per-field outputs (batch path) or null
   const float2* tw_y;      // plane kernels (3D): stage table of n_y
   int pm1_spec;            // plane kernels: transform the +-1 plane for its spectrum
+  // the last row pass forms the statistics itself (fold_sums) instead of reading fstats: at most
+  // FOLD_TILES filter tiles; fold = 0: fstats is ready
+  int fold;
+  FinalizeArgs fin;
 };
 
 struct ThreshArgs {
