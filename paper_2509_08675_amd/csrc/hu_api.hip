@@ -237,7 +237,8 @@ int hu_power_spectrum(hu_dims dims, int32_t batch, const void* x, int32_t dtype,
   BinGeo geo{nullptr, nullptr};
   HU_TRY(get_bingeo(g, bins, &geo));
   TileBinDev tb{};
-  HU_TRY(get_tilebins(g, bins, col_width(g.n[0], 0), &tb));
+  const int vb = half_tiles(g) ? 1 : 0;
+  HU_TRY(get_tilebins(g, bins, col_width(g.n[0], vb), &tb));
   if (tb.M > lay.Mp) return HU_ERR_WORKSPACE;
   float2* spec = reinterpret_cast<float2*>(reinterpret_cast<char*>(work) + lay.spec);
   double* parts = reinterpret_cast<double*>(reinterpret_cast<char*>(work) + lay.parts_p);
@@ -271,14 +272,14 @@ int hu_power_spectrum(hu_dims dims, int32_t batch, const void* x, int32_t dtype,
       HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, 0, cy, st); }));
     }
     BinArgs ba{};
-    ba.sc = g.nd == 2 ? col_sched_fields(g.n[0], 0, g.Nh / g.n[0], B) : col_sched(g.n[0], 0, g.Nh / g.n[0], B);
+    ba.sc = g.nd == 2 ? col_sched_fields(g.n[0], vb, g.Nh / g.n[0], B) : col_sched(g.n[0], vb, g.Nh / g.n[0], B);
     ba.spec = spec;
     ba.Nh = g.Nhp;
     ba.gm = axis0(g);
     ba.tb = tb;
     ba.parts = parts;
     ba.tw = tw_0;
-    HU_HIP(timed("cols_bin", st, [&] { return launch_cols_bin(g.n[0], 0, ba, st); }));
+    HU_HIP(timed("cols_bin", st, [&] { return launch_cols_bin(g.n[0], vb, ba, st); }));
     SpecFinalArgs sf{};
     sf.nb = nb;
     sf.coff_p = tb.coff;

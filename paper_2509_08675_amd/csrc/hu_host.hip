@@ -917,11 +917,13 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   const int B = r.B;
   const bool batch_mode = r.io != nullptr;
   const hu_outputs& o = r.out;
+  TunePlan plan = r.plan;
+  if (half_tiles(g)) plan.v[P_FILTER] = plan.v[P_BIN] = 1;
   const int Lrow = g.nx / 2;
   const float2 *tw_row, *tw2_row, *tw_0, *tw_1 = nullptr;
   HU_TRY(get_tw(Lrow, &tw_row));
   HU_TRY(get_tw2(Lrow, &tw2_row));
-  const int rad = r.plan.v[P_RADIX];        // the column passes' radix lists (tables to match)
+  const int rad = plan.v[P_RADIX];        // the column passes' radix lists (tables to match)
   HU_TRY(get_tw(g.n[0], &tw_0, rad));
   if (g.nd == 3) HU_TRY(get_tw(g.n[1], &tw_1, rad));
   const int nb = r.bins ? r.bins->n_radial * r.bins->n_angular + 1 : 0;
@@ -929,8 +931,8 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   TileBinDev tb_c{}, tb_p{};
   if (r.bins) {
     HU_TRY(get_bingeo(g, *r.bins, &geo));
-    HU_TRY(get_tilebins(g, *r.bins, col_width(g.n[0], r.plan.v[P_FILTER]), &tb_c));
-    HU_TRY(get_tilebins(g, *r.bins, col_width(g.n[0], r.plan.v[P_BIN]), &tb_p));
+    HU_TRY(get_tilebins(g, *r.bins, col_width(g.n[0], plan.v[P_FILTER]), &tb_c));
+    HU_TRY(get_tilebins(g, *r.bins, col_width(g.n[0], plan.v[P_BIN]), &tb_p));
     if (tb_c.M > r.lay.Mc || tb_p.M > r.lay.Mp) return HU_ERR_WORKSPACE;
   }
   const bool want_cont = batch_mode ? (r.want_cont && r.bins) : (o.cont_sum != nullptr);
@@ -938,7 +940,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
 
   // small 2D grids under plan entry whole_field: the whole path in one workgroup per field, the
   // half spectrum resident in LDS (the workspace is not touched)
-  if (r.plan.v[P_WHOLE] && whole_field_ok(g, nb) && !r.noise) {
+  if (plan.v[P_WHOLE] && whole_field_ok(g, nb) && !r.noise) {
     if (!batch_mode && B > MAX_WHOLE_CHUNK) return HU_ERR_ARG;
     const float2* tw_c;
     HU_TRY(get_tw(g.n[0], &tw_c, 0));
@@ -976,7 +978,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
 
   if (!batch_mode && B > MAX_CHUNK) return HU_ERR_ARG;
   // 3D grids under plan entry plane: the x and y transforms of a plane in one kernel
-  const bool planes = g.nd == 3 && r.plan.v[P_PLANE] && plane_ok(g);
+  const bool planes = g.nd == 3 && plan.v[P_PLANE] && plane_ok(g);
   const float2* tw_y0 = nullptr;
   if (planes) HU_TRY(get_tw(g.n[1], &tw_y0, 0));
   float2* spec = r.noise ? r.noise : reinterpret_cast<float2*>(r.work + r.lay.spec);
@@ -1001,8 +1003,8 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
     AmpArgs aa{};
     aa.gm = axis0(g);
     aa.filt = filt_dev(r.filt, g);
-    aa.C = col_width(g.n[0], r.plan.v[P_FILTER]);
-    aa.ntiles = col_tiles(g.n[0], r.plan.v[P_FILTER], aa.gm.ncol);
+    aa.C = col_width(g.n[0], plan.v[P_FILTER]);
+    aa.ntiles = col_tiles(g.n[0], plan.v[P_FILTER], aa.gm.ncol);
     aa.amp = amp;
     aa.amax = amax;
     HU_HIP(timed("amp", st, [&] { return launch_amp(aa, g.n[0], rad, general, st, &namax); }));
@@ -1031,7 +1033,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
     ra.tw_y = tw_y0;
     HU_HIP(timed("plane_fwd", st, [&] { return launch_plane_fwd(Lrow, g.n[1], ra, g.n[0], B, st); }));
   } else {
-    HU_HIP(timed("rows_r2c_noise", st, [&] { return launch_rows_r2c(Lrow, SRC_NOISE, r.plan.v[P_R2C], ra, B, st); }));
+    HU_HIP(timed("rows_r2c_noise", st, [&] { return launch_rows_r2c(Lrow, SRC_NOISE, plan.v[P_R2C], ra, B, st); }));
   }
 
   ColsArgs cy{};
@@ -1041,7 +1043,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
     cy.ncol = g.n[0] * g.nxh;
     cy.inner = g.nxh;
     cy.tw = tw_1;
-    cy.sc = col_sched(g.n[1], r.plan.v[P_COLY], cy.ncol, B, r.plan.v[P_YGROUP] ? 4 : Y_PASS_GROUP);
+    cy.sc = col_sched(g.n[1], plan.v[P_COLY], cy.ncol, B, plan.v[P_YGROUP] ? 4 : Y_PASS_GROUP);
     // 3D: every second pass (the y passes) walks fields and planes from the last to the first, so it
     // starts with what the pass before left in the 256 MB memory-side cache.  With that and the streaming
     // stores of the outputs 4 x 256^3 (271 MB of spectra) went from 778 to 713 us (alternation alone: 5 fields
@@ -1049,10 +1051,10 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
     // 5.5 TB/s); 3 fields fit whole.  Not in 2D, whose column passes take the fields of a tile together.
     cy.sc.rev = 1;
     if (!planes)
-      HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, r.plan.v[P_COLY], cy, st, rad); }));
+      HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, plan.v[P_COLY], cy, st, rad); }));
   }
   // the fields of a tile on consecutive ids of one XCD (2D default) or field-major (3D default)
-  const bool fields_xcd = (g.nd == 2) != (r.plan.v[P_FIELDS] != 0);
+  const bool fields_xcd = (g.nd == 2) != (plan.v[P_FIELDS] != 0);
 
   FilterArgs fa{};
   fa.spec = spec;
@@ -1061,8 +1063,8 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   fa.gm = axis0(g);
   // 2D: the fields of a tile share its slice of the bin table in one XCD's L2 (the 2D binning
   // pass 111 -> 103 us at 16 x 2048^2); 3D fields, 67 MB apart at 256^3, ran 3 % slower that way
-  fa.sc = fields_xcd ? col_sched_fields(g.n[0], r.plan.v[P_FILTER], fa.gm.ncol, B)
-                     : col_sched(g.n[0], r.plan.v[P_FILTER], fa.gm.ncol, B);
+  fa.sc = fields_xcd ? col_sched_fields(g.n[0], plan.v[P_FILTER], fa.gm.ncol, B)
+                     : col_sched(g.n[0], plan.v[P_FILTER], fa.gm.ncol, B);
   if (!batch_mode) fa.filt = filt_dev(r.filt, g);
   fa.io = r.io;
   fa.tb = tb_c;
@@ -1073,7 +1075,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   fa.any_gen = general ? 1 : 0;
   fa.amp = use_amp ? amp : nullptr;
   if (fa.sc.ntiles > r.lay.tiles) return HU_ERR_WORKSPACE;
-  HU_HIP(timed("cols_filter", st, [&] { return launch_cols_filter(g.n[0], r.plan.v[P_FILTER], fa, st, rad, r.plan.v[P_FSPLIT]); }));
+  HU_HIP(timed("cols_filter", st, [&] { return launch_cols_filter(g.n[0], plan.v[P_FILTER], fa, st, rad, plan.v[P_FSPLIT]); }));
   FinalizeArgs fz{};
   fz.partials = partials;
   fz.ntiles = fa.sc.ntiles;
@@ -1089,7 +1091,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   if (!fold) HU_HIP(timed("finalize", st, [&] { return launch_finalize(fz, B, st); }));
 
   if (g.nd == 3 && !planes && !r.noise)
-    HU_HIP(timed("cols_y_inv", st, [&] { return launch_cols(g.n[1], true, r.plan.v[P_COLY], cy, st, rad); }));
+    HU_HIP(timed("cols_y_inv", st, [&] { return launch_cols(g.n[1], true, plan.v[P_COLY], cy, st, rad); }));
 
   RowsZArgs za{};
   za.spec = spec;
@@ -1119,22 +1121,22 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
                  [&] { return launch_plane_inv(Lrow, g.n[1], za, r.thresh, g.n[0], B, st); }));
   } else {
     HU_HIP(timed(r.thresh ? "rows_c2r_thresh" : "rows_c2r", st,
-                 [&] { return launch_rows_c2r(Lrow, r.thresh, r.plan.v[P_C2R], za, B, st); }));
+                 [&] { return launch_rows_c2r(Lrow, r.thresh, plan.v[P_C2R], za, B, st); }));
   }
 
   if (want_pm1) {
     if (g.nd == 3 && !planes)
-      HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, r.plan.v[P_COLY], cy, st, rad); }));
+      HU_HIP(timed("cols_y_fwd", st, [&] { return launch_cols(g.n[1], false, plan.v[P_COLY], cy, st, rad); }));
     BinArgs ba{};
-    ba.sc = fields_xcd ? col_sched_fields(g.n[0], r.plan.v[P_BIN], g.Nh / g.n[0], B)
-                       : col_sched(g.n[0], r.plan.v[P_BIN], g.Nh / g.n[0], B);
+    ba.sc = fields_xcd ? col_sched_fields(g.n[0], plan.v[P_BIN], g.Nh / g.n[0], B)
+                       : col_sched(g.n[0], plan.v[P_BIN], g.Nh / g.n[0], B);
     ba.spec = spec;
     ba.Nh = g.Nhp;
     ba.gm = axis0(g);
     ba.tb = tb_p;
     ba.parts = parts_p;
     ba.tw = tw_0;
-    HU_HIP(timed("cols_bin", st, [&] { return launch_cols_bin(g.n[0], r.plan.v[P_BIN], ba, st, rad, r.plan.v[P_BSPLIT]); }));
+    HU_HIP(timed("cols_bin", st, [&] { return launch_cols_bin(g.n[0], plan.v[P_BIN], ba, st, rad, plan.v[P_BSPLIT]); }));
   }
   if (want_cont || want_pm1 || want_counts) {
     SpecFinalArgs sf{};
@@ -1155,7 +1157,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
     }
     if (want_counts) {
       sf.cpart = cpart;
-      sf.ntc = planes ? g.n[0] : row_tiles(Lrow, r.plan.v[P_C2R], g.nrows);
+      sf.ntc = planes ? g.n[0] : row_tiles(Lrow, plan.v[P_C2R], g.nrows);
       sf.counts = batch_mode ? nullptr : o.counts;
     }
     sf.io = r.io;
