@@ -82,7 +82,11 @@ enum { HU_OP_GEN_FIELD = 0, HU_OP_PIPELINE = 1, HU_OP_POWER_SPECTRUM = 2, HU_OP_
        HU_OP_WINDOW_VARIANCE = 5, HU_OP_TWO_POINT = 6,
        HU_OP_NOISE = 7,          /* the noise buffer of hu_field_spectrum */
        HU_OP_FIELD_SPECTRUM = 8, /* its workspace */
-       HU_OP_NOISE_GRAD = 9 };   /* the workspace of hu_noise_grad */
+       HU_OP_NOISE_GRAD = 9,     /* the workspace of hu_noise_grad */
+       /* HU_OP_PIPELINE or HU_OP_GEN_FIELD with room for the faster forms (a table of the filter's
+          amplitudes; up to 256 small 2D fields at a time).  hu_pipeline and hu_gen_field use the room
+          they are given, with the same results either way. */
+       HU_OP_PIPELINE_PREFERRED = 10 };
 
 /* Most window radii of one hu_window_variance call. */
 #define HU_MAX_RADII 32
@@ -165,7 +169,7 @@ int hu_power_spectrum(hu_dims dims, int32_t batch, const void* x, int32_t dtype,
 /* The whole hot path in one call: field, sign map with counts, continuous and +-1 spectra,
  * fused so that normalisation, threshold and the first transform of the +-1 field share one
  * pass.  near_tol is relative to sigma_f (1e-5 is the parity convention).
- * Workspace: hu_workspace_size(HU_OP_PIPELINE, ...). */
+ * Workspace: hu_workspace_size(HU_OP_PIPELINE, ...); HU_OP_PIPELINE_PREFERRED for the faster forms. */
 int hu_pipeline(hu_dims dims, int32_t batch, const hu_filter* filt, const uint64_t* seeds,
                 hu_bins bins, float near_tol, const hu_outputs* out, void* work, size_t work_bytes,
                 void* stream);

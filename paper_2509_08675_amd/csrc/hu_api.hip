@@ -132,6 +132,10 @@ int hu_workspace_size(int op, hu_dims dims, int32_t batch, const hu_bins* bins, 
   switch (op) {
     case HU_OP_GEN_FIELD:
     case HU_OP_PIPELINE:
+      HU_TRY(layout(g, batch < BASE_CHUNK ? batch : BASE_CHUNK, true, widest_plan(), bins, &lay));
+      *bytes = lay.total;
+      return HU_OK;
+    case HU_OP_PIPELINE_PREFERRED:
       HU_TRY(layout(g, chunk, true, widest_plan(), bins, &lay));
       *bytes = lay.total_amp;
       return HU_OK;

@@ -27,7 +27,7 @@ HU_F32, HU_I8 = 0, 1
 HU_OP_GEN_FIELD, HU_OP_PIPELINE, HU_OP_POWER_SPECTRUM, HU_OP_LOSS, HU_OP_FILTER_SPECTRUM = 0, 1, 2, 3, 4
 HU_OP_WINDOW_VARIANCE = 5
 HU_OP_TWO_POINT = 6
-HU_OP_NOISE, HU_OP_FIELD_SPECTRUM, HU_OP_NOISE_GRAD = 7, 8, 9
+HU_OP_NOISE, HU_OP_FIELD_SPECTRUM, HU_OP_NOISE_GRAD, HU_OP_PIPELINE_PREFERRED = 7, 8, 9, 10
 HU_MAX_RADII = 32
 HU_CLASSES = ("hyperuniform class I", "hyperuniform class II", "hyperuniform class III",
               "nonhyperuniform (standard)", "antihyperuniform", "outside the classified range")
@@ -228,7 +228,7 @@ def gen_field(dims, filt, seeds, cont_bins=None, device="cuda", work=None, out=N
         cc = torch.empty((B, nb), dtype=torch.int64, device=device)
         b = make_bins(cont_bins)
     if work is None:
-        work = alloc_workspace(HU_OP_GEN_FIELD, dims, B, cont_bins, device)
+        work = alloc_workspace(HU_OP_PIPELINE_PREFERRED, dims, B, cont_bins, device)
     h = make_filter(filt)
     _check(_lib.hu_gen_field(make_dims(dims), B, ctypes.byref(h), _seeds(seeds), _ptr(field), _ptr(stats),
                              ctypes.byref(b) if b else None, _ptr(cs), _ptr(cc), _ptr(work), work.numel(),
@@ -367,7 +367,7 @@ class PipelineBuffers:
             self.pm1_cnt = torch.empty((batch, nb), dtype=torch.int64, device=dev)
         else:
             self.pm1_sum = self.pm1_cnt = None
-        self.work = alloc_workspace(HU_OP_PIPELINE, dims, batch, bins, dev)
+        self.work = alloc_workspace(HU_OP_PIPELINE_PREFERRED, dims, batch, bins, dev)
         o = hu_outputs()
         for name in ("field", "pm1", "stats", "counts", "cont_sum", "cont_cnt", "pm1_sum", "pm1_cnt"):
             setattr(o, name, None if getattr(self, name) is None else getattr(self, name).data_ptr())
