@@ -1,0 +1,147 @@
+"""Paths that a rule on sizes, types or room chooses, against the path that other sizes take (same
+bits where only the launches differ) or against the oracle: through the C-ABI, on the GPU."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2509_08675_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+BAND = W.filt(p=3, semi=(2, 1, 1.5), rot=0.4, alpha=4, k0=0.3, width=0.08)
+STEEP = W.filt(p=1.5, semi=(1, 0.5, 0.8), rot=0.3, alpha=20, k0=0.0, width=0.12)   # evaluated in FP64
+
+
+@pytest.fixture(scope="module")
+def hf():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2509_08675_amd import hufield
+    return hufield
+
+
+def _say(*a):
+    print(*a, flush=True)
+
+
+def _outputs(b):
+    return dict(field=b.field, pm1=b.pm1, stats=b.stats, counts=b.counts, cont_sum=b.cont_sum, cont_cnt=b.cont_cnt,
+                pm1_sum=b.pm1_sum, pm1_cnt=b.pm1_cnt)
+
+
+def _same(a, b, at=slice(None)):
+    for k, x in _outputs(a).items():
+        assert torch.equal(x[at], _outputs(b)[k]), k
+
+
+# Binning by run lists: one tile, tiles of one column more than a multiple, all modes in one bin, more
+# bins than threads, columns of one to 2048 modes (pairs of modes and angular bins).  The sums are FP64
+# over |X|^2 of an FP32 transform, whose error is a few 1e-7 of a mode's amplitude.
+@pytest.mark.parametrize("dims,bins", [((4, 8), (1, 1)), ((6, 12), (7, 5)), ((1024, 16), (1, 1)), ((2048, 32), (100, 60)),
+                                       ((768, 24), (24, 90)), ((24, 6, 12), (5, 1)), ((4, 4, 8), (200, 1)),
+                                       ((256, 64, 8), (300, 1)), ((64, 64), (8, 1000)), ((12, 2048), (64, 3))])
+def test_binning_edges(hf, dims, bins):
+    _say("binning", dims, bins)
+    x = np.stack([W.random_field(dims, s) for s in (3, 4, 5)])
+    s, c = hf.power_spectrum(torch.from_numpy(x).cuda(), bins)
+    torch.cuda.synchronize()
+    for i in range(3):
+        rs, rc = O.power_spectrum(x[i].astype(np.float64), *bins)
+        np.testing.assert_array_equal(hf.u64_view(c[i]), rc)
+        np.testing.assert_allclose(s[i].cpu().numpy(), rs, rtol=1e-5, atol=1e-6 * rs.max())
+
+
+# The amplitude table (general forms; FP32 in 2D from 2^23 modes) and the amplitudes evaluated in the
+# pass, which a workspace without room for the table takes: the same bits.
+@pytest.mark.parametrize("dims,batch,filt", [((96, 64), 3, STEEP), ((128, 16), 1, STEEP), ((32, 24, 48), 2, STEEP),
+                                             ((512, 32), 2, dict(STEEP, rot=0.0)), ((48, 32, 16), 1, dict(STEEP, alpha=100.0)),
+                                             ((2048, 2048), 4, BAND), ((768, 384), 57, BAND)])
+def test_amplitude_table_matches_evaluation_in_the_pass(hf, dims, batch, filt):
+    _say("amplitude table", dims, batch)
+    bins, seeds = (16, 1), list(range(50, 50 + batch))
+    a = hf.PipelineBuffers(dims, batch, bins)
+    hf.pipeline(a, filt, seeds)
+    b = hf.PipelineBuffers(dims, batch, bins)
+    b.work = b.work[:b.work.numel() - 256]
+    hf.pipeline(b, filt, seeds)
+    torch.cuda.synchronize()
+    _same(a, b)
+    hf.profile_enable(True)
+    hf.pipeline(a, filt, seeds)
+    hf.pipeline(b, filt, seeds)
+    torch.cuda.synchronize()
+    prof = hf.profile_read()
+    hf.profile_enable(False)
+    assert prof["amp"][0] == 1                       # with the full workspace only
+
+
+# Up to 256 fields of a small 2D grid per launch sequence, 64 where the workspace was sized for 64:
+# every field as on its own.
+@pytest.mark.parametrize("dims,batch", [((32, 48), 65), ((64, 64), 257), ((128, 16), 130)])
+def test_many_small_fields_match_single_ones(hf, dims, batch):
+    _say("many fields", dims, batch)
+    bins, seeds = (12, 4), list(range(1000, 1000 + batch))
+    a = hf.PipelineBuffers(dims, batch, bins)
+    hf.pipeline(a, BAND, seeds)
+    b = hf.PipelineBuffers(dims, batch, bins)
+    b.work = hf.alloc_workspace(hf.HU_OP_PIPELINE, dims, 64, bins)
+    hf.pipeline(b, BAND, seeds)
+    torch.cuda.synchronize()
+    _same(a, b)
+    for i in (0, 63, 64, batch - 1):
+        s = hf.PipelineBuffers(dims, 1, bins)
+        hf.pipeline(s, BAND, [seeds[i]])
+        torch.cuda.synchronize()
+        _same(a, s, slice(i, i + 1))
+
+
+# The form-factor table (2D from four fields on, eight radii at a time) against fields taken one by one
+# (evaluated in the pass): the same FP32 products in FP64 sums of another order.
+@pytest.mark.parametrize("dims,batch,kind", [((64, 96), 5, "f32"), ((48, 32), 4, "i8"), ((2048, 16), 4, "f32"),
+                                             ((24, 48), 9, "f32"), ((16, 24, 32), 5, "f32"), ((8, 16), 4, "f32")])
+def test_window_variance_table_matches_single_fields(hf, dims, batch, kind):
+    _say("variance", dims, batch, kind)
+    make = W.random_pm1 if kind == "i8" else W.random_field
+    x = torch.from_numpy(np.stack([make(dims, s) for s in range(batch)])).cuda()
+    radii = [0.0, 0.5, 1.0, 2.0, 3.0, 4.5, 8.0, 11.0, 16.0, 20.0, 33.0]
+    a = hf.window_variance(x, radii)
+    b = torch.cat([hf.window_variance(x[i:i + 1], radii) for i in range(batch)])
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(a.cpu().numpy(), b.cpu().numpy(), rtol=1e-13, atol=0.0)
+    ref = O.window_variance(x[0].double().cpu().numpy(), radii)
+    np.testing.assert_allclose(a[0].cpu().numpy(), ref, rtol=2e-5, atol=0.0)
+
+
+# Expected spectrum: 3D columns of a multiple of 32 modes (pairs), other columns, FP64 filter.
+@pytest.mark.parametrize("dims,filt", [((32, 12, 16), BAND), ((64, 16, 24), STEEP), ((48, 24, 32), BAND), ((16, 8, 8), BAND),
+                                       ((4, 6, 8), BAND), ((96, 12, 16), dict(BAND, rot=0.0)), ((24, 2048), BAND)])
+def test_expected_spectrum_walks(hf, dims, filt):
+    _say("expected spectrum", dims)
+    nr = 10
+    s, c = hf.filter_spectrum(dims, filt, (nr, 1))
+    torch.cuda.synchronize()
+    ref, rc = O.target_bins(dims, O.FilterParams(**filt), nr)
+    cnt = hf.u64_view(c)
+    np.testing.assert_array_equal(cnt[:nr], rc.astype(np.uint64))
+    got = s.cpu().numpy()[:nr] / np.maximum(cnt[:nr], 1)
+    np.testing.assert_allclose(got[rc > 0], ref[rc > 0], rtol=1e-5, atol=1e-9 * ref.max())
+
+
+# The fitting step's spectrum without the field, and its gradient from the kept noise spectrum: the
+# bits of hu_gen_field and hu_spectrum_grad, also on a second pass over the same buffer.
+@pytest.mark.parametrize("dims,filt,nr", [((32, 24, 48), BAND, 16), ((64, 96), BAND, 24), ((512, 64), BAND, 24),
+                                          ((4, 6, 8), BAND, 2), ((64, 32, 32), STEEP, 16)])
+def test_field_spectrum_and_noise_grad(hf, dims, filt, nr):
+    _say("fitting step", dims)
+    bins, seed = (nr, 1), 77
+    full = hf.gen_field(dims, filt, [seed], cont_bins=bins)
+    noise, cs, cc, st = hf._field_spectrum(dims, filt, seed, bins, torch.device("cuda"))
+    dL = torch.linspace(-1.0, 1.0, nr + 1, dtype=torch.float64, device="cuda")
+    ref = hf.spectrum_grad(dims, filt, seed, bins, dL, cs, cc, st)
+    got = [hf._noise_grad(dims, filt, noise, bins, dL, cs, cc, st) for _ in range(2)]
+    torch.cuda.synchronize()
+    assert torch.equal(cs, full["cont_sum"][0]) and torch.equal(cc, full["cont_cnt"][0])
+    assert torch.equal(st[0], full["stats"][0])
+    assert torch.equal(got[0], ref) and torch.equal(got[1], ref)
