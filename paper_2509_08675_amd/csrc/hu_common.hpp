@@ -578,11 +578,13 @@ __device__ __forceinline__ void col_store(const float2 (&v)[E], const ColIO& io)
 // Stores of the outputs that no later pass reads (field, sign map): non-temporal (cache policy bit 1),
 // so that they leave the half spectrum in the 256 MB memory-side cache for the next pass.
 constexpr int STREAM = 2;
+template <int POLICY>
 __device__ __forceinline__ void out_store2(rsrc_t r, float2 v, unsigned voff, unsigned soff) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, STREAM);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, POLICY);
 }
+template <int POLICY>
 __device__ __forceinline__ void out_store4(rsrc_t r, u32x4 v, unsigned voff, unsigned soff) {
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, STREAM);
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, POLICY);
 }
 
 // per-field parameter and output accessors: the batch table when present, else the uniform

@@ -1087,7 +1087,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   fz.amax = amax;
   fz.namax = namax;
   // few filter tiles: the last row pass forms the statistics itself
-  const bool fold = fz.ntiles <= FOLD_TILES && !planes && !r.noise;
+  const bool fold = fz.ntiles <= FOLD_TILES && !planes && !r.noise && (r.thresh || !streams_out(g.Nhp, g.N, B));
   if (!fold) HU_HIP(timed("finalize", st, [&] { return launch_finalize(fz, B, st); }));
 
   if (g.nd == 3 && !planes && !r.noise)

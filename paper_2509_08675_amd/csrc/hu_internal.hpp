@@ -374,6 +374,10 @@ int col_width(int L, int variant);
 int col_elems(int L);
 hipError_t launch_finalize(const FinalizeArgs& a, int batch, hipStream_t st);
 hipError_t launch_cols_bin(int L, int variant, const BinArgs& a, hipStream_t st, int radix = 0, int complex_x = 0);
+// A pass that only writes fields streams them (past the 256 MB memory-side cache) where they and the
+// spectra do not fit there together: 4 x 256^3 two-point fields 104 us plain, 87 streamed; below that
+// plain stores are the faster ones (3 x 96 x 192 x 384, 170 MB: the call 229.6 us against 232.3).
+inline bool streams_out(long long Nh, long long N, int batch) { return batch * (8 * Nh + 4 * N) > (256LL << 20); }
 hipError_t launch_rows_c2r(int L, bool thresh, int variant, const RowsZArgs& a, int batch, hipStream_t st);
 int row_tiles(int L, int variant, long long nrows);
 hipError_t launch_spec_final(const SpecFinalArgs& a, int batch, hipStream_t st);

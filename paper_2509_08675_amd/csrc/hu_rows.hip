@@ -397,11 +397,16 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_r2c(RowsArgs a) {
   twist_store_rows<L, C, T, TILED, RS, false>(lds, tw2, a.tw2, spec, tile_off, run_stride, rows_here, tid);
 }
 
-// C2R along x -> normalise -> field, sign map, counts -> R2C of the +-1 row (THRESH).
-template <int L, bool THRESH, bool TILED, int V>
+// C2R along x -> normalise -> field, sign map, counts -> R2C of the +-1 row (THRESH).  OUT, without
+// THRESH: streaming stores; or plain ones with the statistics formed here or without that code (its
+// registers and the stores' way past the cache cost 3 x 96 x 192 x 384 48 us against 45).
+enum { OUT_STREAM = 0, OUT_FOLD = 1, OUT_PLAIN = 2 };
+template <int L, bool THRESH, bool TILED, int V, int OUT>
 __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_c2r(RowsZArgs a) {
   constexpr int P = Plan<L>::P, E = Plan<L>::E, C = RowTile<L, V>::C, T = RowTile<L, V>::T;
   constexpr int RS = RowTile<L, V>::RS;
+  constexpr int POLICY = THRESH || OUT == OUT_STREAM ? STREAM : 0;
+  constexpr bool FOLD = THRESH || OUT == OUT_FOLD;
   using Rad = typename Plan<L>::fwd;
   using RadF = Reverse<Rad>;
   constexpr int R1 = RadInfo<Rad>::first, RL = RadInfo<Rad>::last;
@@ -425,7 +430,7 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_c2r(RowsZArgs a) {
   // a.fold: the first wave forms the field's statistics from the filter pass's partials (its loads ahead
   // of the tile's): one launch less per call (128^2 42 -> 38 us)
   FoldLoad fl;
-  const bool folds = a.fold && tid < 64;
+  const bool folds = FOLD && a.fold && tid < 64;
   if (folds) fl = fold_load(a.fin, b, tid);
   __builtin_amdgcn_s_setprio(2);
   load_rows<L, C, T, TILED, RS>(lds, spec, tile_off, run_stride, rows_here, tid);
@@ -460,7 +465,7 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_c2r(RowsZArgs a) {
   //      elements, i.e. 2P consecutive voxels, so each store instruction writes contiguous memory
   //      (with several rows per wave, see STAGE below).
   float scale, offset;
-  if (a.fold) {
+  if (FOLD && a.fold) {
     scale = fin[0];
     offset = fin[1];
   } else {
@@ -501,7 +506,7 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_c2r(RowsZArgs a) {
     const float x0 = fmaf(v[s].x, scale, offset);
     const float x1 = fmaf(v[s].y, scale, offset);
     if constexpr (STAGE) lrow[slot_index<L, RL, P>(s, 0) + p] = make_float2(x0, x1);
-    else out_store2(fo, make_float2(x0, x1), vox0 * 4u, so * 4u);
+    else out_store2<POLICY>(fo, make_float2(x0, x1), vox0 * 4u, so * 4u);
     if constexpr (THRESH) {
       const bool p0 = x0 >= 0.0f, p1 = x1 >= 0.0f;
       npos += (unsigned)p0 + (unsigned)p1;
@@ -524,7 +529,7 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_c2r(RowsZArgs a) {
       const int j = (4 * q) / (2 * L), x = 4 * q - j * (2 * L);
       const float2 a0 = lw[j * RS + x / 2], a1 = lw[j * RS + x / 2 + 1];
       const unsigned vox = (unsigned)(cw * 2 * L + 4 * q);
-      out_store4(fo, u32x4{__float_as_uint(a0.x), __float_as_uint(a0.y), __float_as_uint(a1.x), __float_as_uint(a1.y)},
+      out_store4<POLICY>(fo, u32x4{__float_as_uint(a0.x), __float_as_uint(a0.y), __float_as_uint(a1.x), __float_as_uint(a1.y)},
                  vox * 4u, 0u);
       if constexpr (THRESH) {
         const unsigned packed = (a0.x >= 0.0f ? 0x01u : 0xFFu) | (a0.y >= 0.0f ? 0x0100u : 0xFF00u) |
@@ -589,20 +594,28 @@ hipError_t launch_rows_r2c(int L, int src, int variant, const RowsArgs& a, int b
   }
 }
 
-template <int L, bool THRESH, bool TILED, int V>
+template <int L, bool THRESH, bool TILED, int V, int OUT>
 static hipError_t launch_rows_c2r_L(const RowsZArgs& a, int batch, hipStream_t st) {
   constexpr int C = RowTile<L, V>::C, T = RowTile<L, V>::T;
   dim3 grid(ceil_div_u(a.nrows, C), batch);
   constexpr size_t lds = (size_t)C * RowTile<L, V>::RS * sizeof(float2);
-  hipLaunchKernelGGL((k_rows_c2r<L, THRESH, TILED, V>), grid, dim3(T), lds, st, a);
+  hipLaunchKernelGGL((k_rows_c2r<L, THRESH, TILED, V, OUT>), grid, dim3(T), lds, st, a);
   return hipGetLastError();
 }
 
 template <int L, int V>
 static hipError_t launch_rows_c2r_V(bool thresh, const RowsZArgs& a, int batch, hipStream_t st) {
-  if (a.tiled)
-    return thresh ? launch_rows_c2r_L<L, true, true, V>(a, batch, st) : launch_rows_c2r_L<L, false, true, V>(a, batch, st);
-  return thresh ? launch_rows_c2r_L<L, true, false, V>(a, batch, st) : launch_rows_c2r_L<L, false, false, V>(a, batch, st);
+  auto go = [&](auto out) {
+    constexpr int OUT = decltype(out)::value;
+    return a.tiled ? launch_rows_c2r_L<L, false, true, V, OUT>(a, batch, st)
+                   : launch_rows_c2r_L<L, false, false, V, OUT>(a, batch, st);
+  };
+  if (thresh)
+    return a.tiled ? launch_rows_c2r_L<L, true, true, V, OUT_STREAM>(a, batch, st)
+                   : launch_rows_c2r_L<L, true, false, V, OUT_STREAM>(a, batch, st);
+  if (a.fold) return go(std::integral_constant<int, OUT_FOLD>{});
+  if (streams_out(a.Nh, a.N, batch)) return go(std::integral_constant<int, OUT_STREAM>{});
+  return go(std::integral_constant<int, OUT_PLAIN>{});
 }
 
 // workgroups (row tiles) per field of a row pass
