@@ -460,10 +460,9 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_c2r(RowsZArgs a) {
   constexpr bool WV = (64 % P) == 0;             // each row inside one wave
   fft_run<L, P, E, true, WV>(Rad{}, v, lrow, p, a.tw);
 
-  // ---- normalise (Eq. (15)) in registers.  With one row per wave the field and the sign map go
-  //      out straight from the slots: in slot s the P threads of a row hold P consecutive complex
-  //      elements, i.e. 2P consecutive voxels, so each store instruction writes contiguous memory
-  //      (with several rows per wave, see STAGE below).
+  // ---- normalise (Eq. (15)) in registers.  With whole rows per wave the field and the sign map go
+  //      out through LDS (STAGE) or, with a row over several waves, straight from the slots: in slot s the
+  //      P threads of a row hold P consecutive complex elements, i.e. 2P consecutive voxels.
   float scale, offset;
   if (FOLD && a.fold) {
     scale = fin[0];
@@ -496,10 +495,11 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_c2r(RowsZArgs a) {
   unsigned npos = 0, nnear = 0;
   // STAGE: the rows of a wave are contiguous in the field and the sign map, so the wave writes its
   // normalised values to its own LDS regions and stores them back in address order, 16 bytes of
-  // the field and 4 of the map per lane (rather than 2P-voxel pieces of 64 / P rows per store)
+  // the field and 4 of the map per lane (rather than 2P-voxel pieces of 64 / P rows per store; with one
+  // row per wave half the store instructions: 16 x 2048^2 544 -> 529 us with the streaming stores)
   constexpr int NRW = 64 / P;                        // rows per wave
   constexpr int NQW = NRW * 2 * L / 4;               // four-voxel groups per wave
-  constexpr bool STAGE = WV && NRW > 1 && (L % 2) == 0 && (NQW % 64) == 0 && (RS >= L);
+  constexpr bool STAGE = WV && (L % 2) == 0 && (NQW % 64) == 0 && (RS >= L);
 #pragma unroll
   for (int s = 0; s < E; ++s) {
     const unsigned so = 2u * (unsigned)slot_index<L, RL, P>(s, 0);
