@@ -626,7 +626,7 @@ __device__ __forceinline__ void finalize_field(const FinalizeArgs& a, int b, dou
   }
 }
 
-// k_finalize's sums for at most FOLD_TILES = 256 tiles by one wave, added in the same order: lane l holds
+// k_finalize's sums for at most FOLD_TILES = 512 tiles by one wave, added in the same order: lane l holds
 // what threads l, l + 64, l + 128 and l + 192 of its 256 do.
 struct FoldLoad {
   double g[4], f[4];
@@ -642,6 +642,15 @@ __device__ __forceinline__ FoldLoad fold_load(const FinalizeArgs& a, int b, int 
     x.g[q] = w < a.ntiles ? part[4 * w] : 0.0;
     x.f[q] = w < a.ntiles ? part[4 * w + 1] : 0.0;
     if (w < a.ntiles) x.m = fmaxf(x.m, (float)part[4 * w + 2]);
+  }
+  if (a.ntiles > 256) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int w = lane + 64 * q + 256;
+      x.g[q] += w < a.ntiles ? part[4 * w] : 0.0;
+      x.f[q] += w < a.ntiles ? part[4 * w + 1] : 0.0;
+      if (w < a.ntiles) x.m = fmaxf(x.m, (float)part[4 * w + 2]);
+    }
   }
   for (int w = lane; w < a.namax; w += 64) x.m = fmaxf(x.m, a.amax[w]);
   return x;

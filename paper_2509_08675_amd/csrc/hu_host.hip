@@ -1086,8 +1086,9 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   fz.io = r.io;
   fz.amax = amax;
   fz.namax = namax;
-  // few filter tiles: the last row pass forms the statistics itself
-  const bool fold = fz.ntiles <= FOLD_TILES && !planes && !r.noise && (r.thresh || !streams_out(g.Nhp, g.N, B));
+  // few filter tiles: the last row pass forms the statistics itself.  With the maxima of an amplitude table
+  // to read as well, up to half as many (2048^2: 257 tiles, 1536 maxima in each of 512 workgroups a field)
+  const bool fold = fz.ntiles <= (namax ? FOLD_TILES / 2 : FOLD_TILES) && !planes && !r.noise && (r.thresh || !streams_out(g.Nhp, g.N, B));
   if (!fold) HU_HIP(timed("finalize", st, [&] { return launch_finalize(fz, B, st); }));
 
   if (g.nd == 3 && !planes && !r.noise)

@@ -181,7 +181,7 @@ struct FinalizeArgs {
   int namax;
 };
 
-constexpr int FOLD_TILES = 256;
+constexpr int FOLD_TILES = 512;
 
 struct BinArgs {
   ColSched sc;

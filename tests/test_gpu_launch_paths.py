@@ -145,3 +145,24 @@ def test_field_spectrum_and_noise_grad(hf, dims, filt, nr):
     assert torch.equal(cs, full["cont_sum"][0]) and torch.equal(cc, full["cont_cnt"][0])
     assert torch.equal(st[0], full["stats"][0])
     assert torch.equal(got[0], ref) and torch.equal(got[1], ref)
+
+
+# Statistics formed by the last row pass (up to 512 filter tiles; 258, 260 and 387 here) and by their own
+# kernel (a batch whose fields stream past the cache): the same sums in the same order, the same bits.
+@pytest.mark.parametrize("dims,batch", [((32, 64, 256), 64), ((64, 128, 128), 34), ((32, 96, 256), 44)])
+def test_folded_statistics_match_their_own_kernel(hf, dims, batch):
+    _say("folded statistics", dims, batch)
+    seeds = list(range(7, 7 + batch))
+    hf.profile_enable(True)
+    a = hf.gen_field(dims, BAND, seeds)
+    torch.cuda.synchronize()
+    assert hf.profile_read()["finalize"][0] == 1
+    hf.profile_enable(True)                          # counts from here
+    for i in (0, 1, batch - 1):
+        b = hf.gen_field(dims, BAND, [seeds[i]])
+        torch.cuda.synchronize()
+        assert torch.equal(b["field"][0], a["field"][i])
+        assert torch.equal(b["stats"][0], a["stats"][i])
+    prof = hf.profile_read()
+    hf.profile_enable(False)
+    assert "finalize" not in prof
