@@ -337,10 +337,10 @@ int hu_pipeline_batch(const hu_job* jobs, int32_t njobs, float near_tol, int32_t
                       size_t work_bytes, void* stream);
 
 /* Plan autotuner.  A plan has 13 entries, each 0 or 1: the tile width of the kernel families
- * rows_r2c, cols_y, cols_filter, rows_c2r, cols_bin (0 the default, 1 half of it), then
- * (cols_filter and cols_bin take the half width under either value in 2D with n[0] <= 1024), then
- * bin_schedule (reserved: accepted, without effect), two schedules (0 the default, 1 the other one): field_placement (the fields of an
- * axis-0 tile on consecutive workgroup ids of one XCD, sharing the tile's bin-table slice in its
+ * rows_r2c, cols_y, cols_filter, rows_c2r, cols_bin (0 the default, 1 half of it; cols_filter and
+ * cols_bin take the half width under either value in 2D with n[0] <= 1024), then bin_schedule
+ * (reserved: accepted, without effect), two schedules (0 the default, 1 the other one):
+ * field_placement (the fields of an axis-0 tile on consecutive workgroup ids of one XCD, sharing the tile's bin-table slice in its
  * L2, or field-major; default the former in 2D, the latter in 3D) and y_group (the 3D y passes give
  * groups of 16 or of 4 neighbouring tiles to one XCD); last `radix`, the radix lists of the
  * column passes (y, filter, binning): 0 each length's default Stockham plan, 1 its alternative
