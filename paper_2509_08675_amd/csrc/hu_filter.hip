@@ -30,26 +30,24 @@ __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a
   const int c = tid % C, p = tid / C;
   const int g = (int)tile * C + c;
   const bool valid = g < a.gm.ncol;
-  const ColIO io = col_io<L>(a.spec + (long long)b * a.Nh, a.Nh, a.gm.inner0, g, p);
-  float2 v[E];
-  col_load<L, R1, P, E>(v, io);
-  const bool do_bins = a.parts != nullptr;
-  const TileBinPre pre = do_bins ? tile_bins_pre<T>(a.tb, (int)tile, tid) : TileBinPre{};
-  fft_run<L, P, E, false, false, RV>(Rad{}, v, col_region<L, V, SPLIT>(lds, c), p, a.tw);
-
-  // ---- filter and per-thread statistics
-  const ColCoord cc = col_coord(a.gm, valid ? g : 0);
+  // the filter's view of the column and the amplitude of its mode e
+  ColCoord cc;
   FiltDev filt{};
-  if constexpr (AMP != AMP_TABLE) filt = a.io ? a.io[b].filt : a.filt;
   Col3 c3a{}, c3b{};
-  if constexpr (AMP != AMP_TABLE && NDIM == 3) {   // the column's x / y terms of the filter
-    c3a = col3(filt, cc.kx_c, cc.ky);
-    c3b = (filt.rotated && (cc.nyq_x || cc.nyq_y)) ? col3(filt, cc.nyq_x ? -cc.kx_c : cc.kx_c, cc.nyq_y ? -cc.ky : cc.ky)
-                                                   : c3a;
-  }
-  double gsum = 0.0, f0 = 0.0;
   // the lattice maximum of ln(chi_rel + offset) is at least ln offset
-  float lmax = AMP == AMP_TABLE ? -1.0e30f : filt.lnoffset;
+  float lmax = -1.0e30f;
+  auto column = [&]() {
+    cc = col_coord(a.gm, valid ? g : 0);
+    if constexpr (AMP != AMP_TABLE) {
+      filt = a.io ? a.io[b].filt : a.filt;
+      lmax = filt.lnoffset;
+      if constexpr (NDIM == 3) {                   // the column's x / y terms of the filter
+        c3a = col3(filt, cc.kx_c, cc.ky);
+        c3b = (filt.rotated && (cc.nyq_x || cc.nyq_y))
+                  ? col3(filt, cc.nyq_x ? -cc.kx_c : cc.kx_c, cc.nyq_y ? -cc.ky : cc.ky) : c3a;
+      }
+    }
+  };
   auto amplitude = [&](int e) {
     float lnc;
     const float h = NDIM == 3 ? amp_sym3<AMP == AMP_GENERAL>(filt, a.gm, cc, c3a, c3b, e, lnc)
@@ -57,23 +55,35 @@ __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a
     if (valid) lmax = fmaxf(lmax, lnc);
     return h;
   };
-  // the exchange buffer is free once every thread has its transform in registers: the power
-  // values of the continuous spectrum go to LDS as they are computed
   float* pw = reinterpret_cast<float*>(lds);
   float H[E];
+  if constexpr (AMP == AMP_GENERAL) {
+    // Before the columns are loaded: one register per amplitude crosses the transform instead of two per
+    // column value crossing the FP64 evaluation, and the pass keeps four waves per SIMD (186-230 registers and two
+    // waves the other way round; alpha 20: 16 x 2048^2 730 -> 483 us, 512^3 1709 -> 1214, 512^2 x 20 98 -> 81).  A
+    // rolled loop that leaves the amplitudes in LDS: unrolled it is tens of kilobytes of code (1024^2 68 us for 43)
+    column();
+#pragma unroll 1
+    for (int s = 0; s < E; ++s) pw[s * T + tid] = amplitude(slot_index<L, RL, P>(s, p));
+#pragma unroll
+    for (int s = 0; s < E; ++s) H[s] = pw[s * T + tid];
+  }
+  const ColIO io = col_io<L>(a.spec + (long long)b * a.Nh, a.Nh, a.gm.inner0, g, p);
+  float2 v[E];
+  col_load<L, R1, P, E>(v, io);
+  const bool do_bins = a.parts != nullptr;
+  const TileBinPre pre = do_bins ? tile_bins_pre<T>(a.tb, (int)tile, tid) : TileBinPre{};
+  fft_run<L, P, E, false, false, RV>(Rad{}, v, col_region<L, V, SPLIT>(lds, c), p, a.tw);
+  // ---- filter and per-thread statistics
+  if constexpr (AMP != AMP_GENERAL) column();
+  double gsum = 0.0, f0 = 0.0;
+  // the exchange buffer is free once every thread has its transform in registers: the power
+  // values of the continuous spectrum go to LDS as they are computed
   if constexpr (AMP == AMP_TABLE) {                // all loads at once (in groups of four the pass took 8 % longer)
     const rsrc_t ar = make_rsrc(a.amp + tile * (long long)(E * T), (unsigned)(E * T * 4));
 #pragma unroll
     for (int s = 0; s < E; ++s)
       H[s] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ar, (unsigned)tid * 4u, (unsigned)(s * T * 4), 0));
-  } else if constexpr (AMP == AMP_GENERAL) {
-    // a rolled loop that leaves the amplitudes in LDS: unrolled over the slots the FP64 evaluation is tens
-    // of kilobytes of code
-    __syncthreads();
-#pragma unroll 1
-    for (int s = 0; s < E; ++s) pw[s * T + tid] = amplitude(slot_index<L, RL, P>(s, p));
-#pragma unroll
-    for (int s = 0; s < E; ++s) H[s] = pw[s * T + tid];
   }
   if (do_bins) __syncthreads();
 #pragma unroll

@@ -392,6 +392,18 @@ int chunk_fields(const Geom& g, int batch) {
   return batch < n ? batch : (int)n;
 }
 
+// General forms (FP64 in the filter pass's few workgroups): in 2D always (one 1024^2 field, alpha 20: the pass
+// 43 us, table and pass together 35; 2048^2 89 and 80).  In 3D for several fields (two of 256^3: 372 and 294) and
+// for a small one; a large one hides the evaluation behind its memory traffic (64^3 52 and 34, 192 x 128^2
+// 103 and 88; 256^2 x 128 170 and 193, 512^3 1214 and 1610; 128^3 is 8 us the other way).  FP32: in 2D from
+// 2^23 modes on (the table's kernel costs one launch, 6-8 us; 2048^2: 4 fields even, 8 fields 102 -> 91 us, 16
+// fields 190 -> 174; 8 x 512^2 1 us slower).  In 3D the evaluation is cheaper and a table's share of the
+// traffic larger (4 x 256^3: 10 us gained for 20 spent).
+bool amp_table(const Geom& g, int B, bool general) {
+  if (general) return g.nd == 2 || B > 1 || g.Nh < (1LL << 21);
+  return g.nd == 2 && B * g.Nh >= (1LL << 23);
+}
+
 int tile_partials(const Geom& g, const hu_bins& bins, int C, int* M, int* nloc_max);
 
 int layout(const Geom& g, int batch, bool need_stats, const TunePlan& plan, const hu_bins* bins, Layout* out) {
@@ -988,14 +1000,10 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   double* parts_p = reinterpret_cast<double*>(r.work + r.lay.parts_p);
   const uint32_t* cnt_src = reinterpret_cast<const uint32_t*>(geo.counts);
 
-  // A uniform batch's amplitudes from a table where that pays, evaluated once for all fields (the fields
-  // of a tile run on one XCD in 2D, whose L2 serves it).  General forms: always (FP64 in the filter
-  // pass's few workgroups: one 1024^2 field, alpha 20, 43 us; table and pass together 26).  FP32: in 2D
-  // from 2^23 modes on (its kernel costs one launch, 6-8 us; 2048^2: 4 fields even, 8 fields 102 -> 91 us,
-  // 16 fields 190 -> 174; 8 x 512^2 1 us slower).  In 3D the evaluation is cheaper and a table's share of
-  // the traffic larger (4 x 256^3: 10 us gained for 20 spent).
+  // A uniform batch's amplitudes from a table where that pays, evaluated once for the fields of a launch sequence
+  // (those of a tile run on one XCD in 2D, whose L2 serves it): amp_table.
   const bool general = batch_mode ? r.any_gen : filt_general(r.filt, g);
-  const bool use_amp = !batch_mode && r.amp && (general || (g.nd == 2 && B * g.Nh >= (1LL << 23)));
+  const bool use_amp = !batch_mode && r.amp && amp_table(g, B, general);
   float* amp = reinterpret_cast<float*>(r.work + r.lay.amp);
   float* amax = reinterpret_cast<float*>(r.work + r.lay.amax);
   int namax = 0;

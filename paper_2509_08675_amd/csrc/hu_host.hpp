@@ -81,6 +81,8 @@ bool aligned(const void* p, size_t a);
 inline bool half_tiles(const Geom& g) { return g.nd == 2 && g.n[0] <= 1024; }
 // fields that a uniform call of `batch` fields takes per launch sequence, given room for them
 int chunk_fields(const Geom& g, int batch);
+// whether a uniform launch sequence of B fields reads its amplitudes from a table, given room for it
+bool amp_table(const Geom& g, int B, bool general);
 size_t up256(size_t x);
 // need_stats: the generator's layout (filter statistics, sign counts, both spectra); otherwise the
 // binning of a stored input.  bins: null when no spectrum is binned.  Builds the host bin tables of
