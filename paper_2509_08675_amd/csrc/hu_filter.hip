@@ -12,9 +12,17 @@ namespace hu {
 // general form (tabulated radial form or FP64), or read from the call's table (k_amp)
 enum { AMP_FP32 = 0, AMP_GENERAL = 1, AMP_TABLE = 2 };
 
+// Waves per SIMD asked of the compiler.  A tile of five waves (384 and 768, 24 elements a thread) doubles up on
+// one SIMD, so two workgroups are resident only where four waves fit: 128 registers.  Left alone the FP32 form
+// takes 132-143 of them (384 x 128 x 256 x 3: 217 us against 165; 768 x 128^2 x 4: 330 against 259); the 2 and 4
+// waves of 96 and 192 lose by the same cap (66 -> 68, 126 -> 129).
+template <int L, int V, int AMP>
+constexpr int filter_waves() { return AMP == AMP_FP32 && Plan<L>::E > 16 && ColTile<L, V>::T > 256 ? 4 : 1; }
+
 // One tile of C columns of one field per workgroup.
 template <int L, int NDIM, int V, int AMP, int RV, bool SPLIT>
-__global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_filter(FilterArgs a) {
+__global__ void __launch_bounds__((ColTile<L, V>::T)) __attribute__((amdgpu_waves_per_eu(filter_waves<L, V, AMP>())))
+k_cols_filter(FilterArgs a) {
   constexpr int P = Plan<L>::P, E = Plan<L>::E, C = ColTile<L, V>::C, T = ColTile<L, V>::T;
   constexpr int LP = ColTile<L, V>::LP;
   using Rad = typename Plan<L, RV>::fwd;

@@ -72,3 +72,11 @@ def test_general_filter_form_keeps_its_waves(kernels):
     for (length, nd, width), (regs, scratch) in filter_kernels(kernels, 1).items():
         most = 168 if length % 3 == 0 else 128
         assert regs <= most and scratch == 0, (length, nd, width, regs, scratch)
+
+
+def test_five_wave_filter_tiles_leave_room_for_two_workgroups(kernels):
+    # 384 and 768, full width: two workgroups of five waves need a SIMD with room for four
+    found = filter_kernels(kernels, 0)
+    for length in (384, 768):
+        regs, scratch = found[length, 3, 0]
+        assert regs <= 128 and scratch <= 64, (length, regs, scratch)
