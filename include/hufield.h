@@ -404,6 +404,22 @@ int hu_debug_philox(uint64_t seed, uint64_t first, uint64_t count, uint32_t* wor
 int hu_debug_bin_tables(hu_dims dims, hu_bins bins, int32_t variant, int32_t* sizes, uint16_t* table,
                         uint16_t* ltab, uint32_t* toff, uint32_t* coff, uint32_t* cpos);
 
+/* The run tables by which a workgroup sums a tile's bins, for tests (host only, no device work).  Thread t = c P + p
+ * of a tile (P = n0 / E threads per column) sums each run of equal bin among E consecutive modes of
+ * column c from p E on -- radial bins alone (sym): of E / 2 pairs e, n0 - e from p E / 2 on, the column's last
+ * thread also e = n0 / 2 -- and the tile's runs are numbered thread by thread.
+ *   sizes [8] (host): ntiles, threads per tile, E, summing lanes (of all tiles), runs (of all tiles), most runs in
+ *         a tile, sym, 1 where `dst` is used
+ *   seg   [ntiles][threads][2]: bit i set where entry i starts a run; the thread's first run
+ *   info  [ntiles][4]: the tile's first run in list and dst, its first lane in slot and ent, its lanes
+ *   slot  [lanes][2]: first entry in the tile's list | entries << 16 | log2 of the bin's lanes << 29; the place of
+ *         the partial (the bin's first lane) or 2^32 - 1.  ent [lanes][4]: the lane's first four runs
+ *   list  [runs]: the runs of each bin of the tile, bin after bin
+ *   dst   [runs]: where used, the place of the partial of a run alone in its bin (such a bin has no lane), or 2^32 - 1
+ * Each array may be NULL (host arrays). */
+int hu_debug_bin_runs(hu_dims dims, hu_bins bins, int32_t variant, int32_t* sizes, uint32_t* seg, uint32_t* info,
+                      uint32_t* slot, uint16_t* ent, uint16_t* list, uint32_t* dst);
+
 /* Kernel timing with HIP events recorded on the launch stream around every kernel the library
  * enqueues.  hu_profile_enable(1) resets the counters and starts recording; hu_profile_read
  * fills up to `cap` entries (host arrays) with each kernel family's name, launch count and

@@ -15,7 +15,7 @@ namespace hu {
 // tile in 3D too: a persistent form over a work counter, which loaded the next tile's columns during
 // the binning, needs 95 and more registers and took 43 us for 24 x 64^3 and 64 us for 16 x 128^3,
 // against 12 and 30 us here.
-template <int L, int V, int RV, bool SPLIT>
+template <int L, int V, int RV, bool SPLIT, bool ANG>
 __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_bin(BinArgs a) {
   constexpr int P = Plan<L>::P, E = Plan<L>::E, C = ColTile<L, V>::C, T = ColTile<L, V>::T;
   constexpr int LP = ColTile<L, V>::LP;
@@ -40,14 +40,15 @@ __global__ void __launch_bounds__((ColTile<L, V>::T)) k_cols_bin(BinArgs a) {
   for (int s = 0; s < E; ++s)
     pw[c * LP + pw_index(slot_index<L, RL, P>(s, p))] = valid ? wm * (v[s].x * v[s].x + v[s].y * v[s].y) : 0.0f;
   __syncthreads();
-  tile_bins<L, E, C, LP, T, ColTile<L, V>::PWV>(lds, a.tb, pre, (int)tile, a.gm.ncol, a.parts + (long long)b * a.tb.M, tid);
+  tile_bins<L, E, C, LP, T, ColTile<L, V>::PWV, ANG>(lds, a.tb, pre, (int)tile, a.gm.ncol, a.parts + (long long)b * a.tb.M, tid);
 }
 
 template <int L, int V, int RV, bool SPLIT>
 static hipError_t launch_cols_bin_L(const BinArgs& a, hipStream_t st) {
   constexpr int T = ColTile<L, V>::T;
   const size_t lds = col_bin_bytes<L, V, SPLIT>(a.tb);
-  hipLaunchKernelGGL((k_cols_bin<L, V, RV, SPLIT>), dim3(sched_blocks(a.sc)), dim3(T), lds, st, a);
+  if (a.gm.ndim == 2) hipLaunchKernelGGL((k_cols_bin<L, V, RV, SPLIT, true>), dim3(sched_blocks(a.sc)), dim3(T), lds, st, a);
+  else hipLaunchKernelGGL((k_cols_bin<L, V, RV, SPLIT, false>), dim3(sched_blocks(a.sc)), dim3(T), lds, st, a);
   return hipGetLastError();
 }
 

@@ -372,11 +372,14 @@ __device__ __forceinline__ void run_commit(int j, double s, int* hx, unsigned lo
 // boundaries are a bit mask per thread, the runs numbered thread by thread: no bin numbers, no
 // atomics).  Then a lane -- for bins of many runs a group of lanes -- adds a bin's runs in the order
 // of the tile's list and stores the partial.  The order is fixed by the tables, so the partials are
-// the same bits for every schedule.  The runs reuse the storage of the power values.  (An integer
-// combination of the runs by LDS atomics, two passes over them, took the binning pass 91 us at
-// 4 x 256^3 and 88 us at 16 x 2048^2; this form 78 and 85-88 us.)
+// the same bits for every schedule.  The runs reuse the storage of the power values.  A lane's record names its
+// first runs, and the next lane's record is loaded during this one's sum: a thread with several lanes waits
+// once for each (16 x 2048^2, angular bins, 509 -> 495 us; through the list alone twice).  Where many runs are
+// alone in their bin the threads store those themselves (TileBinDev::dst).  (An integer combination of the
+// runs by LDS atomics, two passes over them, took the binning pass 88 us at 4 x 256^3 and at 16 x 2048^2; this
+// form 60 and 66.)
 // ---------------------------------------------------------------------------------------------
-constexpr int LIST_AHEAD = 8;             // list entries of a lane loaded before the runs are complete
+constexpr int ENT = 4, LIST_AHEAD = 8;    // entries of a slot in its own record, and with those loaded ahead from the list
 
 template <int N, class V>
 __device__ __forceinline__ void runs_store(const V (&v)[N], uint2 sg, double* runs) {
@@ -391,6 +394,29 @@ __device__ __forceinline__ void runs_store(const V (&v)[N], uint2 sg, double* ru
     acc += (double)v[i];
   }
   *r = acc;
+}
+
+// The same where many runs are alone in their bin (many bins per mode): such a run is the tile's partial and goes
+// straight to its place, the dst of its modes; the others (~0) go to LDS.
+template <int N>
+__device__ __forceinline__ void runs_store_direct(const float (&v)[N], uint2 sg, const unsigned (&dst)[N], double* runs,
+                                                double* __restrict__ out) {
+  double* r = runs + sg.y;
+  double acc = (double)v[0];
+  auto put = [&](unsigned d) {
+    if (d != ~0u) out[d] = acc;
+    else *r = acc;
+    ++r;
+  };
+#pragma unroll
+  for (int i = 1; i < N; ++i) {
+    if ((sg.x >> i) & 1u) {
+      put(dst[i - 1]);
+      acc = 0.0;
+    }
+    acc += (double)v[i];
+  }
+  put(dst[N - 1]);
 }
 
 // The thread's entries of the tile tables, loaded at the start of the kernel: their latency (the slot's
@@ -417,7 +443,8 @@ __device__ __forceinline__ TileBinPre tile_bins_pre(const TileBinDev& tb, int ti
 // depends on the axis-0 index e only through its square, so e and n0 - e share it, and thread
 // (cb, pb) takes the pairs q = pb E/2 .. pb E/2 + E/2 - 1 of its column with the value pw[q] + pw[n0 - q]
 // (pw[q] alone for q = 0), the last thread also q = n0 / 2 (its own partner): half the runs.
-template <int L, int E, int C, int LP, int T, bool PWV>
+// ANG: the launch may have angular bins (2D).
+template <int L, int E, int C, int LP, int T, bool PWV, bool ANG>
 __device__ __forceinline__ void tile_bins(float2* lds, const TileBinDev& tb, const TileBinPre& pre, int tile, int ncol,
                                           double* __restrict__ out, int tid) {
   constexpr int P = Plan<L>::P, H = E / 2;
@@ -430,15 +457,16 @@ __device__ __forceinline__ void tile_bins(float2* lds, const TileBinDev& tb, con
   const uint2 sg = pre.sg;
   uint2 sl = pre.sl;
   const uint16_t* list = tb.list + pre.list;
-  unsigned idx[LIST_AHEAD];
-  // the first list entries of the lane's slot, on their way while the runs are formed
+  uint2 en = tid < nslots ? tb.ent[pre.slot + tid] : make_uint2(0u, 0u);
+  unsigned idx[LIST_AHEAD - ENT];
+  // the slot's entries from the list up to LIST_AHEAD, on their way while the runs are formed
   auto ahead = [&]() {
 #pragma unroll
-    for (int q = 0; q < LIST_AHEAD; ++q)
-      idx[q] = (unsigned)q < (sl.x >> 16 & 0x1FFFu) ? (unsigned)list[(sl.x & 0xFFFFu) + ((unsigned)q << (sl.x >> 29))] : 0u;
+    for (int q = ENT; q < LIST_AHEAD; ++q)
+      idx[q - ENT] = (unsigned)q < (sl.x >> 16 & 0x1FFFu) ? (unsigned)list[(sl.x & 0xFFFFu) + ((unsigned)q << (sl.x >> 29))] : 0u;
   };
   ahead();
-  if (tb.sym) {                                      // uniform over the launch
+  if (!ANG || tb.sym) {                              // uniform over the launch
     double v[H + 1];
     if (act) {
 #pragma unroll
@@ -451,8 +479,17 @@ __device__ __forceinline__ void tile_bins(float2* lds, const TileBinDev& tb, con
     __syncthreads();
     if (act) runs_store<H + 1>(v, sg, runs);
   } else {
+    constexpr bool DIRECT = direct_length(L);
     float v[E];
+    unsigned dst[DIRECT ? E : 1];
+    const bool direct = DIRECT && tb.dst != nullptr;  // uniform over the launch
     if (act) {
+      if constexpr (DIRECT) {
+        if (direct) {
+#pragma unroll
+          for (int i = 0; i < E; ++i) dst[i] = tb.dst[pre.list + sg.y + __popc(sg.x & ((2u << i) - 1u))];
+        }
+      }
       if constexpr (PWV) {
         const float4* p4 = reinterpret_cast<const float4*>(pwc + pw_index(pb * E));
 #pragma unroll
@@ -469,14 +506,24 @@ __device__ __forceinline__ void tile_bins(float2* lds, const TileBinDev& tb, con
       }
     }
     __syncthreads();
-    if (act) runs_store<E>(v, sg, runs);
+    if (act) {
+      if (!direct) runs_store<E>(v, sg, runs);
+      else if constexpr (DIRECT) runs_store_direct<E>(v, sg, dst, runs, out);
+    }
   }
   __syncthreads();                                   // the runs are complete
   for (int i = tid; i < nslots;) {                   // uniform over a wave: nslots and T are multiples of 64
+    i += T;
+    uint2 sl2 = make_uint2(0u, ~0u), en2 = make_uint2(0u, 0u);
+    if (i < nslots) {                                // the next slot on its way during this one's sum
+      sl2 = tb.slot[pre.slot + i];
+      en2 = tb.ent[pre.slot + i];
+    }
     const unsigned first = sl.x & 0xFFFFu, n = (sl.x >> 16) & 0x1FFFu, lg = sl.x >> 29;
+    const unsigned r[LIST_AHEAD] = {en.x & 0xFFFFu, en.x >> 16, en.y & 0xFFFFu, en.y >> 16, idx[0], idx[1], idx[2], idx[3]};
     double s = 0.0;
 #pragma unroll
-    for (int q = 0; q < LIST_AHEAD; ++q) s += (unsigned)q < n ? runs[idx[q]] : 0.0;
+    for (int q = 0; q < LIST_AHEAD; ++q) s += (unsigned)q < n ? runs[r[q]] : 0.0;
     for (unsigned q = LIST_AHEAD; q < n; ++q) s += runs[list[first + (q << lg)]];
     // the slots are sorted by lanes per bin, most first, so the wave's first lane has the largest
     const int lgw = __builtin_amdgcn_readfirstlane((int)lg);
@@ -485,11 +532,9 @@ __device__ __forceinline__ void tile_bins(float2* lds, const TileBinDev& tb, con
       if (o < (1 << lg)) s += t;
     }
     if (sl.y != ~0u) out[sl.y] = s;
-    i += T;
-    if (i < nslots) {
-      sl = tb.slot[pre.slot + i];
-      ahead();
-    }
+    sl = sl2;
+    en = en2;
+    if (i < nslots) ahead();
   }
 }
 

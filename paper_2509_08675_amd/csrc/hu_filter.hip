@@ -124,7 +124,7 @@ k_cols_filter(FilterArgs a) {
   }
   // ---- continuous-spectrum bins of the tile -> its partials in parts[b] (deterministic)
   if (do_bins) {
-    tile_bins<L, E, C, LP, T, ColTile<L, V>::PWV>(lds, a.tb, pre, (int)tile, a.gm.ncol, a.parts + (long long)b * a.tb.M, tid);
+    tile_bins<L, E, C, LP, T, ColTile<L, V>::PWV, (NDIM == 2)>(lds, a.tb, pre, (int)tile, a.gm.ncol, a.parts + (long long)b * a.tb.M, tid);
   }
 
   if (a.read_only) return;                       // uniform

@@ -32,9 +32,10 @@ struct TileHost {
   std::vector<uint32_t> toff, coff, cpos, wpos;   // wpos: the inverse of cpos
   int nloc_max = 0;
   // the device tables of TileBinDev
-  std::vector<uint2> seg, slot;
+  std::vector<uint2> seg, slot, ent;
   std::vector<uint4> info;
   std::vector<uint16_t> list;
+  std::vector<uint32_t> dst;
   int runs_max = 0;
 };
 std::map<std::vector<long long>, std::shared_ptr<BinHost>> g_binhost;    // {nd, n0, n1, n2, nr, na}
@@ -657,17 +658,19 @@ void tile_runs(const Axis0Geom& a, int C, bool sym, TileHost* th) {
   const int ntiles = (int)th->toff.size() - 1;
   th->seg.assign((size_t)ntiles * T, make_uint2(0u, 0u));
   th->info.resize(ntiles);
-  std::vector<int> rbin, cnt, off;
+  std::vector<uint16_t> rbin;                      // the runs' bins, tile after tile
+  std::vector<size_t> roff(ntiles + 1, 0);
+  std::vector<int> cnt, off;
+  long long alone = 0;                             // runs that are the only one of their bin in the tile
   for (int t = 0; t < ntiles; ++t) {
-    const int nloc = (int)(th->toff[t + 1] - th->toff[t]);
-    rbin.clear();
+    const size_t r0 = rbin.size();
     for (int cb = 0; cb < C && t * C + cb < a.ncol; ++cb) {
       const uint16_t* col = th->ltab.data() + (size_t)(t * C + cb) * a.n0;
       for (int pb = 0; pb < P; ++pb) {
         const uint16_t* e = col + pb * (sym ? H : E);
         const int n = sym ? H : E;
         uint2& sg = th->seg[(size_t)t * T + cb * P + pb];
-        sg.y = (uint32_t)rbin.size();
+        sg.y = (uint32_t)(rbin.size() - r0);
         rbin.push_back(e[0]);
         for (int i = 1; i < n; ++i)
           if (e[i] != e[i - 1]) {
@@ -680,29 +683,51 @@ void tile_runs(const Axis0Geom& a, int C, bool sym, TileHost* th) {
         }
       }
     }
-    const int nr = (int)rbin.size();
-    th->runs_max = std::max(th->runs_max, nr);
+    roff[t + 1] = rbin.size();
+    th->runs_max = std::max(th->runs_max, (int)(rbin.size() - r0));
+    cnt.assign(th->toff[t + 1] - th->toff[t], 0);
+    for (size_t r = r0; r < rbin.size(); ++r) cnt[rbin[r]]++;
+    for (int c : cnt) alone += c == 1;
+  }
+  // Many bins per mode (angular ones on a small grid): the runs alone in their bin are stored by the threads that
+  // form them, where that saves a thread one slot or more.  With a slot for every bin a thread walked ten and more,
+  // each two loads after the last: 64^2, 64 x 36 bins: filter and binning pass 20 and 14.5 us, 14 and 8.4 so; 16 x
+  // 96^2, 128 x 36 bins: 29 and 21, 19 and 12.5.
+  const bool direct = !sym && direct_length(a.n0) && alone >= (long long)ntiles * T;
+  if (direct) th->dst.assign(rbin.size(), ~0u);
+  th->list.resize(rbin.size());
+  for (int t = 0; t < ntiles; ++t) {
+    const size_t l0 = roff[t], s0 = th->slot.size();
+    const int nr = (int)(roff[t + 1] - l0), nloc = (int)(th->toff[t + 1] - th->toff[t]);
     cnt.assign(nloc, 0);
     off.assign(nloc + 1, 0);
-    for (int r = 0; r < nr; ++r) cnt[rbin[r]]++;
+    for (int r = 0; r < nr; ++r) cnt[rbin[l0 + r]]++;
     for (int j = 0; j < nloc; ++j) off[j + 1] = off[j] + cnt[j];
-    const size_t l0 = th->list.size(), s0 = th->slot.size();
-    th->list.resize(l0 + nr);
     std::vector<int> cur(off.begin(), off.end() - 1);
-    for (int r = 0; r < nr; ++r) th->list[l0 + cur[rbin[r]]++] = (uint16_t)r;
+    for (int r = 0; r < nr; ++r) th->list[l0 + cur[rbin[l0 + r]]++] = (uint16_t)r;
     for (int lg = 6; lg >= 0; --lg)
       for (int j = 0; j < nloc; ++j) {
         int need = 0;
         while (need < 6 && cnt[j] > (LANE_RUNS << need)) ++need;
         if (need != lg) continue;
+        const uint32_t place = th->wpos[th->toff[t] + j];
+        if (direct && cnt[j] == 1) {
+          th->dst[l0 + th->list[l0 + off[j]]] = place;
+          continue;
+        }
         const int G = 1 << lg;
         for (int u = 0; u < G; ++u) {
           const int n = cnt[j] > u ? (cnt[j] - u + G - 1) / G : 0;
-          th->slot.push_back(make_uint2((uint32_t)(off[j] + u) | (uint32_t)n << 16 | (uint32_t)lg << 29,
-                                        u == 0 ? th->wpos[th->toff[t] + j] : ~0u));
+          th->slot.push_back(make_uint2((uint32_t)(off[j] + u) | (uint32_t)n << 16 | (uint32_t)lg << 29, u == 0 ? place : ~0u));
+          uint32_t q[4] = {0u, 0u, 0u, 0u};
+          for (int i = 0; i < 4 && i < n; ++i) q[i] = th->list[l0 + off[j] + u + i * G];
+          th->ent.push_back(make_uint2(q[0] | q[1] << 16, q[2] | q[3] << 16));
         }
       }
-    while ((th->slot.size() - s0) % 64) th->slot.push_back(make_uint2(0u, ~0u));
+    while ((th->slot.size() - s0) % 64) {
+      th->slot.push_back(make_uint2(0u, ~0u));
+      th->ent.push_back(make_uint2(0u, 0u));
+    }
     th->info[t] = make_uint4((uint32_t)l0, (uint32_t)s0, (uint32_t)(th->slot.size() - s0), 0u);
   }
 }
@@ -816,20 +841,22 @@ int get_tilebins(const Geom& g, const hu_bins& bins, int C, TileBinDev* out) {
   }
   if (C < 1) return HU_ERR_SIZE;
   const std::shared_ptr<TileHost> th = tile_host(g, bins, C);
-  uint2 *seg = nullptr, *slot = nullptr;
+  uint2 *seg = nullptr, *slot = nullptr, *ent = nullptr;
   uint4* info = nullptr;
   uint16_t* list = nullptr;
-  uint32_t* coff = nullptr;
+  uint32_t *coff = nullptr, *dst = nullptr;
   HU_TRY(upload(th->seg, &seg));
   HU_TRY(upload(th->slot, &slot));
+  HU_TRY(upload(th->ent, &ent));
   HU_TRY(upload(th->info, &info));
   HU_TRY(upload(th->list, &list));
+  if (!th->dst.empty()) HU_TRY(upload(th->dst, &dst));
   HU_TRY(upload(th->coff, &coff));
-  TileBinDev d{seg, info, slot, list, coff, th->runs_max, (int)th->toff.back(), bins.n_angular == 1 ? 1 : 0};
+  TileBinDev d{seg, info, slot, ent, list, dst, coff, th->runs_max, (int)th->toff.back(), bins.n_angular == 1 ? 1 : 0};
   std::lock_guard<std::mutex> lk(g_mu);
   auto it = g_tiledev.find(key);
   if (it != g_tiledev.end()) {
-    void* own[] = {seg, slot, info, list, coff};
+    void* own[] = {seg, slot, ent, info, list, dst, coff};
     for (void* p : own) (void)hipFree(p);
     *out = it->second;
     return HU_OK;
@@ -1202,5 +1229,33 @@ extern "C" int hu_debug_bin_tables(hu_dims dims, hu_bins bins, int32_t variant, 
   if (toff) std::memcpy(toff, th->toff.data(), th->toff.size() * sizeof(uint32_t));
   if (coff) std::memcpy(coff, th->coff.data(), th->coff.size() * sizeof(uint32_t));
   if (cpos) std::memcpy(cpos, th->cpos.data(), th->cpos.size() * sizeof(uint32_t));
+  return HU_OK;
+}
+
+extern "C" int hu_debug_bin_runs(hu_dims dims, hu_bins bins, int32_t variant, int32_t* sizes, uint32_t* seg, uint32_t* info,
+                                 uint32_t* slot, uint16_t* ent, uint16_t* list, uint32_t* dst) {
+  using namespace hu;
+  Geom g;
+  HU_TRY(make_geom(dims, &g));
+  HU_TRY(check_bins(&bins, g.nd));
+  if (variant != 0 && variant != 1) return HU_ERR_ARG;
+  const int C = col_width(g.n[0], variant);
+  if (C < 1) return HU_ERR_SIZE;
+  const std::shared_ptr<TileHost> th = tile_host(g, bins, C);
+  const int ntiles = (int)th->info.size(), E = col_elems(g.n[0]);
+  if (sizes) {
+    const int32_t v[8] = {ntiles, C * (g.n[0] / E), E, (int32_t)th->slot.size(), (int32_t)th->list.size(), th->runs_max,
+                          bins.n_angular == 1 ? 1 : 0, th->dst.empty() ? 0 : 1};
+    std::memcpy(sizes, v, sizeof v);
+  }
+  auto copy = [](void* to, const auto& from) {
+    if (to && !from.empty()) std::memcpy(to, from.data(), from.size() * sizeof(from[0]));
+  };
+  copy(seg, th->seg);
+  copy(info, th->info);
+  copy(slot, th->slot);
+  copy(ent, th->ent);
+  copy(list, th->list);
+  copy(dst, th->dst);
   return HU_OK;
 }

@@ -13,6 +13,10 @@ namespace hu {
 // (shorter columns have small exchange buffers)
 constexpr bool split_length(int L) { return L >= 192; }
 
+// column lengths whose binning threads may store a run that is alone in its bin themselves (TileBinDev::dst).
+// Not the longer ones: their runs are longer, and the code alone costs 16 x 2048^2 488 -> 496 us.
+constexpr bool direct_length(int L) { return L <= 512; }
+
 
 enum { SRC_NOISE = 0, SRC_F32 = 1, SRC_I8 = 2 };
 // fields per launch when seeds travel in the kernel arguments: 64 (what every workspace holds), of
@@ -134,7 +138,10 @@ struct TileBinDev {
   const uint2* slot;       // one per summing lane: x: first entry (relative to the tile) | entries << 16 | log2 lanes << 29,
                            // y: where the partial is stored (the bin's first lane), or ~0; a bin's lanes are adjacent and
                            // aligned, take every (lanes)-th entry and add up by a fixed butterfly
+  const uint2* ent;        // the slot's first four entries, 16 bits each: known without a look at the list
   const uint16_t* list;    // runs of each bin of the tile, bin after bin
+  const uint32_t* dst;     // where many runs are alone in their bin: of every run the place of its partial, or ~0 (the bin
+                           // has slots, which sum it); null: every bin has slots
   const uint32_t* coff;    // [nb + 1]: the stored partials of bin k are coff[k] .. coff[k+1]-1
   int runs_max;            // most runs in one tile
   int M;                   // partials per field

@@ -90,12 +90,13 @@ _lib.hu_level_threshold.argtypes = [ctypes.c_double, ctypes.c_double, _P(ctypes.
 _lib.hu_level_cut.argtypes = [hu_dims, _i32, _vp, ctypes.c_double, ctypes.c_double, _vp, _vp, _f32, _vp]
 _lib.hu_two_point.argtypes = [hu_dims, _i32, _vp, _vp, _vp, _sz, _vp]
 _lib.hu_debug_bin_tables.argtypes = [hu_dims, hu_bins, _i32, _vp, _vp, _vp, _vp, _vp, _vp]
+_lib.hu_debug_bin_runs.argtypes = [hu_dims, hu_bins, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
 _lib.hu_spectrum_loss.argtypes = [hu_bins, _vp, _vp, _vp, _vp, ctypes.c_double, _vp, _vp, _vp]
 for _f in ("hu_workspace_size", "hu_gen_field", "hu_threshold", "hu_power_spectrum", "hu_pipeline", "hu_pipeline_noalloc",
            "hu_debug_philox", "hu_profile_enable", "hu_profile_read", "hu_workspace_size_batch",
            "hu_pipeline_batch", "hu_autotune", "hu_plan_query", "hu_plan_set", "hu_filter_spectrum",
            "hu_spectrum_grad", "hu_window_variance", "hu_small_k_exponent", "hu_hyperuniformity_class",
-           "hu_level_threshold", "hu_level_cut", "hu_two_point", "hu_debug_bin_tables", "hu_spectrum_loss",
+           "hu_level_threshold", "hu_level_cut", "hu_two_point", "hu_debug_bin_tables", "hu_debug_bin_runs", "hu_spectrum_loss",
            "hu_field_spectrum", "hu_noise_grad"):
     getattr(_lib, _f).restype = ctypes.c_int
 
@@ -438,6 +439,29 @@ def debug_bin_tables(dims, bins, variant=0):
                                     toff.ctypes.data, coff.ctypes.data, cpos.ctypes.data), "hu_debug_bin_tables")
     return dict(ncol=ncol, n0=n0, ntiles=ntiles, M=M, nloc_max=nloc_max, width=width, table=table, ltab=ltab,
                 toff=toff, coff=coff, cpos=cpos[:M])
+
+
+def debug_bin_runs(dims, bins, variant=0):
+    """The host-built run tables of the binning (no device work): dict with ntiles, threads, E, runs_max, sym and the
+    arrays seg [ntiles, threads, 2], info [ntiles, 4], slot [lanes, 2], ent [lanes, 4], list [runs], dst [runs] or
+    None (layout: hu_debug_bin_runs in hufield.h)."""
+    import numpy as np
+    d, b = make_dims(dims), make_bins(bins)
+    sz = (ctypes.c_int32 * 8)()
+    _check(_lib.hu_debug_bin_runs(d, b, int(variant), ctypes.addressof(sz), None, None, None, None, None, None),
+           "hu_debug_bin_runs")
+    ntiles, threads, E, lanes, runs, runs_max, sym, direct = list(sz)
+    seg = np.empty((ntiles, threads, 2), np.uint32)
+    info = np.empty((ntiles, 4), np.uint32)
+    slot = np.empty((lanes, 2), np.uint32)
+    ent = np.empty((lanes, 4), np.uint16)
+    lst = np.empty(runs, np.uint16)
+    dst = np.empty(runs, np.uint32) if direct else None
+    _check(_lib.hu_debug_bin_runs(d, b, int(variant), None, seg.ctypes.data, info.ctypes.data, slot.ctypes.data,
+                                  ent.ctypes.data, lst.ctypes.data, None if dst is None else dst.ctypes.data),
+           "hu_debug_bin_runs")
+    return dict(ntiles=ntiles, threads=threads, E=E, runs_max=runs_max, sym=bool(sym), seg=seg, info=info, slot=slot,
+                ent=ent, list=lst, dst=dst)
 
 
 def profile_enable(on=True):

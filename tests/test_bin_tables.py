@@ -149,3 +149,13 @@ def test_integer_combination(hf, dims, bins):
         spec[k] = s
     direct = np.bincount(t["table"].ravel().astype(np.int64), weights=P.ravel().astype(np.float64), minlength=nb)
     np.testing.assert_allclose(spec, direct, rtol=1e-13, atol=0.0)
+
+
+# ---- the run tables of the axis-0 passes
+@pytest.mark.parametrize("dims,bins", [((48, 48), (64, 36)), ((64, 64), (64, 36)), ((96, 96), (128, 36)), ((128, 128), (128, 36))])
+def test_short_runs_leave_few_lanes_to_a_thread(hf, dims, bins):
+    # many bins per mode: the threads store most runs themselves, so none walks a chain of lanes (ten and more
+    # with one for every bin)
+    r = hf.debug_bin_runs(dims, bins, 1)
+    assert r["info"][:, 2].mean() <= 4 * r["threads"]
+    assert len(r["list"]) >= 5 * r["ntiles"] * r["threads"]       # short runs indeed

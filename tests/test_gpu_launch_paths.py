@@ -53,6 +53,22 @@ def test_binning_edges(hf, dims, bins):
         np.testing.assert_allclose(s[i].cpu().numpy(), rs, rtol=1e-5, atol=1e-6 * rs.max())
 
 
+# Runs alone in their bin, stored by the threads that form them (2D, angular bins, columns up to 512): every mode
+# a run of its own, columns of each element count, a tile's last columns missing, and the first length without.
+@pytest.mark.parametrize("dims,bins", [((4, 32), (64, 36)), ((12, 24), (40, 60)), ((24, 48), (64, 36)), ((48, 16), (128, 36)),
+                                       ((64, 6), (90, 91)), ((96, 96), (128, 36)), ((256, 64), (128, 60)), ((512, 24), (128, 63)),
+                                       ((768, 16), (128, 63))])
+def test_binning_of_short_runs(hf, dims, bins):
+    _say("binning, short runs", dims, bins)
+    x = np.stack([W.random_field(dims, s) for s in (6, 7)])
+    s, c = hf.power_spectrum(torch.from_numpy(x).cuda(), bins)
+    torch.cuda.synchronize()
+    for i in range(2):
+        rs, rc = O.power_spectrum(x[i].astype(np.float64), *bins)
+        np.testing.assert_array_equal(hf.u64_view(c[i]), rc)
+        np.testing.assert_allclose(s[i].cpu().numpy(), rs, rtol=1e-5, atol=1e-6 * rs.max())
+
+
 # The amplitude table (general forms; FP32 in 2D from 2^23 modes) and the amplitudes evaluated in the
 # pass, which a workspace without room for the table takes: the same bits.
 @pytest.mark.parametrize("dims,batch,filt", [((96, 64), 3, STEEP), ((128, 16), 1, STEEP), ((32, 24, 48), 2, STEEP),
