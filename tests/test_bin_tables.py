@@ -159,3 +159,107 @@ def test_short_runs_leave_few_lanes_to_a_thread(hf, dims, bins):
     r = hf.debug_bin_runs(dims, bins, 1)
     assert r["info"][:, 2].mean() <= 4 * r["threads"]
     assert len(r["list"]) >= 5 * r["ntiles"] * r["threads"]       # short runs indeed
+
+
+RUN_CASES = [((4, 8), (1, 1)), ((6, 12), (7, 5)), ((24, 48), (64, 36)), ((64, 64), (64, 36)), ((96, 32), (16, 4)),
+             ((48, 64), (12, 1)), ((2048, 16), (3, 1)), ((768, 24), (24, 90)), ((24, 6, 12), (5, 1)), ((64, 16, 8), (200, 1))]
+NONE = 0xFFFFFFFF
+
+
+def thread_entries(r, column, c, p, E):
+    """The entries that thread (c, p) of a tile sums: lists of modes of its column, in the kernels' order."""
+    n0 = len(column)
+    if not r["sym"]:
+        return [[p * E + i] for i in range(E)]
+    h = E // 2
+    out = [[q] if q == 0 else [q, n0 - q] for q in range(p * h, p * h + h)]
+    return out + [[n0 // 2]] if (p + 1) * h == n0 // 2 else out
+
+
+@pytest.mark.parametrize("dims,bins", RUN_CASES)
+@pytest.mark.parametrize("variant", [0, 1])
+def test_run_tables(hf, dims, bins, variant):
+    """Every run is listed once under its bin, a bin's lanes are adjacent, aligned and sorted by their number, and the
+    kernels' walk over the tables (runs, direct stores, lanes, butterflies) stores each partial once, as the sum
+    over the bin's modes."""
+    t = hf.debug_bin_tables(dims, bins, variant)
+    r = hf.debug_bin_runs(dims, bins, variant)
+    E, T, w, n0 = r["E"], r["threads"], t["width"], t["n0"]
+    assert E == EPT[n0] and T == w * (n0 // E) and T % 64 == 0 and r["sym"] == (bins[1] == 1)
+    wpos = np.empty(t["M"], np.int64)                # where partial i of the tile order is stored: grouped by bin
+    wpos[t["cpos"]] = np.arange(t["M"])
+    P = np.exp(np.random.default_rng(3).normal(0.0, 4.0, size=t["table"].shape)).astype(np.float32)
+    out = np.full(t["M"], np.nan)
+    most = 0
+
+    def store(place, value):
+        assert np.isnan(out[place])
+        out[place] = value
+
+    for k in range(r["ntiles"]):
+        l0, s0, lanes, _ = (int(x) for x in r["info"][k])
+        l1 = int(r["info"][k + 1][0]) if k + 1 < r["ntiles"] else len(r["list"])
+        nr, lst = l1 - l0, r["list"][l0:l1].astype(np.int64)
+        most = max(most, nr)
+        assert lanes % 64 == 0 and np.array_equal(np.sort(lst), np.arange(nr))
+        runs, rbin = np.full(nr, np.nan), np.empty(nr, np.int64)
+        for c in range(min(w, t["ncol"] - k * w)):
+            loc, pw = t["ltab"][k * w + c].astype(np.int64), P[k * w + c].astype(np.float64)
+            for p in range(n0 // E):
+                starts, run = (int(x) for x in r["seg"][k, c * (n0 // E) + p])
+                ent = thread_entries(r, loc, c, p, E)
+                assert starts >> len(ent) == 0 and starts & 1 == 0
+                cur, acc = loc[ent[0][0]], 0.0
+                for i, modes in enumerate(ent):
+                    assert all(loc[m] == loc[modes[0]] for m in modes)
+                    if starts >> i & 1:
+                        runs[run], rbin[run] = acc, cur
+                        run, cur, acc = run + 1, loc[modes[0]], 0.0
+                    assert loc[modes[0]] == cur
+                    acc += sum(pw[m] for m in modes)
+                runs[run], rbin[run] = acc, cur
+        assert not np.isnan(runs).any()              # numbered without a gap
+        j0 = int(t["toff"][k])
+        done = np.zeros(int(t["toff"][k + 1]) - j0, bool)
+        if r["dst"] is not None:
+            for run, place in enumerate(r["dst"][l0:l1]):
+                if place != NONE:
+                    assert place == wpos[j0 + rbin[run]] and not done[rbin[run]]
+                    done[rbin[run]] = True
+                    store(place, runs[run])
+        last, i = 6, 0
+        while i < lanes:
+            x, place = (int(v) for v in r["slot"][s0 + i])
+            lg, n = x >> 29, x >> 16 & 0x1FFF
+            if n == 0:                               # padding up to whole waves
+                assert all(int(v[0]) == 0 and int(v[1]) == NONE for v in r["slot"][s0 + i:s0 + lanes])
+                break
+            G = 1 << lg
+            assert lg <= last and i % G == 0
+            last = lg
+            part = np.zeros(G)
+            seen = []
+            for u in range(G):
+                xu, pu = (int(v) for v in r["slot"][s0 + i + u])
+                assert xu >> 29 == lg and (u == 0 or pu == NONE)
+                mine = [int(lst[(xu & 0xFFFF) + (q << lg)]) for q in range(xu >> 16 & 0x1FFF)]
+                assert [int(v) for v in r["ent"][s0 + i + u][:len(mine)]] == mine[:4]
+                seen += mine
+                for m in mine:
+                    part[u] += runs[m]
+            o = G >> 1
+            while o:
+                part = part + part[np.arange(G) ^ o]
+                o >>= 1
+            j = rbin[seen[0]]
+            assert sorted(seen) == [m for m in range(nr) if rbin[m] == j] and not done[j]
+            assert place == wpos[j0 + j]
+            done[j] = True
+            store(place, part[0])
+            i += G
+        assert done.all()
+    assert most == r["runs_max"] and not np.isnan(out).any()
+    nb = bins[0] * bins[1] + 1
+    spec = [out[t["coff"][b]:t["coff"][b + 1]].sum() for b in range(nb)]
+    direct = np.bincount(t["table"].ravel().astype(np.int64), weights=P.ravel().astype(np.float64), minlength=nb)
+    np.testing.assert_allclose(spec, direct, rtol=1e-12, atol=0.0)
