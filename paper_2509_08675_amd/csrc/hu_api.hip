@@ -563,11 +563,11 @@ int hu_window_variance(hu_dims dims, int32_t batch, const void* x, int32_t dtype
     wa.spec = spec;
     wa.Nh = g.Nhp;
     wa.gm = axis0(g);
-    const bool tab = wvar_table(g.nd, B) && work_bytes >= lay.total_tab;
-    wa.sc = tab ? col_sched_fields(g.n[0], 0, wa.gm.ncol, B) : col_sched(g.n[0], 0, wa.gm.ncol, B);
     wa.tw = tw_0;
     wa.nr_all = n_radii;
     wa.partials = partials;
+    const bool tab = wvar_table(g.nd, B) && work_bytes >= lay.total_tab && wvar_table_pays(B * g.Nh, n_radii);
+    wa.sc = tab ? col_sched_fields(g.n[0], 0, wa.gm.ncol, B) : col_sched(g.n[0], 0, wa.gm.ncol, B);
     wa.tab = tab ? reinterpret_cast<const float*>(w + lay.tab) : nullptr;
     const int group = tab ? WVAR_TAB_RADII : HU_MAX_RADII;      // radii per launch
     for (int j0 = 0; j0 < n_radii; j0 += group) {

@@ -67,7 +67,7 @@ __device__ __forceinline__ float mode_k(const Axis0Geom& gm, const ColCoord& cc,
   return PI * sqrtf(fmaf(k0, k0, kfix2));
 }
 
-// The squared form factors of a call's radii, in the order in which the threads of the axis-0 pass use
+// The squared form factors of a launch's radii, in the order in which the threads of the axis-0 pass use
 // them: [radius][tile][pair][thread].  One workgroup: 256 threads of a tile, one of the pairs.
 template <int NDIM>
 __global__ void __launch_bounds__(256) k_wvar_table(WvarTabArgs a) {
@@ -86,9 +86,10 @@ __global__ void __launch_bounds__(256) k_wvar_table(WvarTabArgs a) {
 // The modes q and n0 - q of a column share |k|, so their powers meet in LDS and a thread takes pairs
 // (q = p + P k, k < E/2; thread p = 0 of a column also q = n0 / 2; q = 0 and q = n0 / 2 stand alone): half
 // the form factors.  Those, not memory, bound the pass (about 50 instructions each): evaluated per
-// mode it took 290 us for 16 x 2048^2 and 8 radii.  TAB: read from the call's table instead, evaluated
-// once for all fields; the fields of a tile run on one XCD, whose L2 then serves the table (both
-// kernels 113 us).
+// mode it took 290 us for 16 x 2048^2 and 8 radii.  TAB: read from a table instead, evaluated once for
+// the fields of the launch; the fields of a tile run on one XCD, whose L2 then serves the table (both
+// kernels 113 us).  Each further eight radii are a table and a launch more, the transform with them (16 radii
+// 322 us for the call, where one launch that evaluated all of them took 637).
 template <int L, int NDIM, bool TAB>
 __global__ void __launch_bounds__((ColTile<L, 0>::T)) k_cols_wvar(WvarArgs a) {
   constexpr int P = Plan<L>::P, E = Plan<L>::E, C = ColTile<L, 0>::C, T = ColTile<L, 0>::T, H = E / 2;

@@ -335,12 +335,17 @@ struct WvarArgs {
   const float* tab;        // room for the form factors of nr <= WVAR_TAB_RADII radii, or null: evaluated in the pass
 };
 
-// The squared form factors of the radii of one launch, [radius][tile][pair][thread].  The table pays
-// in 2D from four fields on (its kernel takes about as long as the evaluation for two: 6 x 512^2
-// 39 -> 28 us).  In 3D a form factor is cheaper and the table as large as the spectra of four fields:
-// 4 x 256^3 took 169 us with it, the pairs evaluated in the pass about 145.
+// The squared form factors of the radii of one launch, [radius][tile][pair][thread].  Where the table pays, in
+// 2D: from four fields on (its kernel takes about as long as the evaluation for two: 6 x 512^2, 8 radii, 39 ->
+// 28 us), and for fewer than 2^23 modes of all fields from a few radii on, since its kernel is a launch of 2-5 us
+// (5 x 1024^2: 1 radius 30.1 us with it, 28.6 without, 3 radii 32.5 and 34.4; 12 x 384 x 768: 1 radius 37.5 and 32.9,
+// 4 radii even; 5 x 128^2: 20.3 and 17.0, even from 5 on).  In 3D a form factor is cheaper and the table as large
+// as the spectra of four fields: 4 x 256^3 took 169 us with it, the pairs evaluated in the pass about 145.
 constexpr int WVAR_TAB_RADII = 8, WVAR_TAB_BATCH = 4;
 inline bool wvar_table(int ndim, int batch) { return ndim == 2 && batch >= WVAR_TAB_BATCH; }
+inline bool wvar_table_pays(long long modes, int radii) {
+  return modes >= (1LL << 23) || radii >= (modes >= (1LL << 21) ? 3 : 4);
+}
 struct WvarTabArgs {
   Axis0Geom gm;
   int ntiles, C, P, H, T;  // tiles of C columns, threads per column, pairs per thread, threads per tile

@@ -130,6 +130,22 @@ def test_window_variance_table_matches_single_fields(hf, dims, batch, kind):
     np.testing.assert_allclose(a[0].cpu().numpy(), ref, rtol=2e-5, atol=0.0)
 
 
+# Few radii are evaluated in the pass; a workspace without room for the table takes that path for any number.
+@pytest.mark.parametrize("dims,batch", [((64, 96), 5), ((24, 48), 9), ((1024, 512), 9)])
+def test_window_variance_of_few_radii(hf, dims, batch):
+    _say("variance, few radii", dims, batch)
+    x = torch.from_numpy(np.stack([W.random_field(dims, s) for s in range(batch)])).cuda()
+    full = hf.alloc_workspace(hf.HU_OP_WINDOW_VARIANCE, dims, batch)
+    radii = [1.0, 0.5, 3.0, 7.5, 2.0, 4.0, 6.0, 9.0, 11.0]
+    ref = O.window_variance(x[0].double().cpu().numpy(), radii)
+    for n in (1, 2, 3, 4, 8, 9):
+        a = hf.window_variance(x, radii[:n], work=full)
+        b = hf.window_variance(x, radii[:n], work=full[:full.numel() - 256])
+        torch.cuda.synchronize()
+        assert torch.equal(a, b), n
+        np.testing.assert_allclose(a[0].cpu().numpy(), ref[:n], rtol=2e-5, atol=0.0)
+
+
 # Expected spectrum: 3D columns of a multiple of 32 modes (pairs), other columns, FP64 filter.
 @pytest.mark.parametrize("dims,filt", [((32, 12, 16), BAND), ((64, 16, 24), STEEP), ((48, 24, 32), BAND), ((16, 8, 8), BAND),
                                        ((4, 6, 8), BAND), ((96, 12, 16), dict(BAND, rot=0.0)), ((24, 2048), BAND)])
