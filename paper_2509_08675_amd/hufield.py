@@ -5,8 +5,11 @@ PyTorch supplies device memory and the current stream.  There is no CPU fallback
 library is not built, importing this module raises ImportError.
 """
 
+import collections
 import ctypes
 import os
+import threading
+import weakref
 
 import numpy as np
 import torch
@@ -644,11 +647,48 @@ def _noise_grad(dims, filt, noise, bins, dL, cont_sum, cont_cnt, stats):
     return grad
 
 
+# Bytes of noise spectra that fitting steps may hold between forward and backward, per device (16 steps at 512^3).
+# A step beyond them forms its noise spectrum again in backward, the same bits.
+NOISE_KEEP_BYTES = 8 << 30
+
+
+class _KeptNoise:
+    """Counts the noise spectra that are alive between forward and backward: a loss summed over many seeds
+    would otherwise hold one as large as a field for each."""
+
+    def __init__(self):
+        self._lock = threading.Lock()
+        self._bytes = {}
+        self._freed = collections.deque()            # filled by finalizers, which take no lock
+
+    def held(self, device):
+        with self._lock:
+            while self._freed:
+                dev, n = self._freed.popleft()
+                self._bytes[dev] -= n
+            return self._bytes.get(device, 0)
+
+    def keep(self, noise):
+        """Whether `noise` may be kept; it then counts until the tensor is released."""
+        n = noise.numel() * noise.element_size()
+        self.held(noise.device)
+        with self._lock:
+            if self._bytes.get(noise.device, 0) + n > NOISE_KEEP_BYTES:
+                return False
+            self._bytes[noise.device] = self._bytes.get(noise.device, 0) + n
+        weakref.finalize(noise, self._freed.append, (noise.device, n)).atexit = False
+        return True
+
+
+_kept_noise = _KeptNoise()
+
+
 class FilterSpectrum(torch.autograd.Function):
     """theta [7] = (a, b, c, p, rot, k0, w) -> the binned continuous spectrum P [R*A] (bin means,
     0 for empty bins) of the field generated on `dims` from `seed` with those filter parameters
     (alpha and sigma_f fixed).  Forward: hu_field_spectrum; backward: hu_noise_grad on the noise
-    spectrum of the forward pass, a saved tensor as large as the field."""
+    spectrum of the forward pass, a saved tensor as large as the field (up to NOISE_KEEP_BYTES of them
+    at a time; formed again beyond)."""
 
     @staticmethod
     def forward(ctx, theta, dims, seed, bins, alpha, sigma_f=1.0):
@@ -659,14 +699,17 @@ class FilterSpectrum(torch.autograd.Function):
         check_degenerate(st)
         cnt = cc[:-1].to(torch.float64)
         P = torch.where(cnt > 0, cs[:-1] / cnt.clamp(min=1.0), torch.zeros_like(cnt))
-        ctx.save_for_backward(noise, cs, cc, st)
-        ctx.meta = (dims, tuple(bins), filt, theta.device, theta.dtype)
+        keep = ctx.needs_input_grad[0] and _kept_noise.keep(noise)
+        ctx.save_for_backward(noise if keep else None, cs, cc, st)
+        ctx.meta = (dims, int(seed), tuple(bins), filt, theta.device, theta.dtype)
         return P
 
     @staticmethod
     def backward(ctx, gP):
         noise, cs, cc, st = ctx.saved_tensors
-        dims, bins, filt, tdev, tdt = ctx.meta
+        dims, seed, bins, filt, tdev, tdt = ctx.meta
+        if noise is None:
+            noise = _field_spectrum(dims, filt, seed, bins, cs.device)[0]
         dL = torch.zeros(cs.shape[0], dtype=torch.float64, device=cs.device)
         dL[:-1] = gP.to(device=cs.device, dtype=torch.float64)
         g = _noise_grad(dims, filt, noise, bins, dL, cs, cc, st)
@@ -688,7 +731,7 @@ class SpectrumLoss(torch.autograd.Function):
     """theta [7] -> the spectrum-matching loss of the field generated from `seed` with those filter
     parameters against the binned target spectrum (tsum, tcnt).  Forward: hu_field_spectrum and
     hu_spectrum_loss; backward: hu_noise_grad with the library's dL/dP, on the noise spectrum of the
-    forward pass (a saved tensor as large as the field)."""
+    forward pass (kept as in FilterSpectrum)."""
 
     @staticmethod
     def forward(ctx, theta, dims, seed, bins, alpha, sigma_f, tsum, tcnt, eps):
@@ -698,14 +741,17 @@ class SpectrumLoss(torch.autograd.Function):
         noise, cs, cc, st = _field_spectrum(dims, filt, seed, bins, dev)
         check_degenerate(st)
         loss, dL = spectrum_loss_value(bins, cs, cc, tsum, tcnt, eps)
-        ctx.save_for_backward(noise, cs, cc, st, dL)
-        ctx.meta = (dims, tuple(bins), filt, theta.device, theta.dtype)
+        keep = ctx.needs_input_grad[0] and _kept_noise.keep(noise)
+        ctx.save_for_backward(noise if keep else None, cs, cc, st, dL)
+        ctx.meta = (dims, int(seed), tuple(bins), filt, theta.device, theta.dtype)
         return loss.to(theta.dtype) if theta.dtype != torch.float64 else loss
 
     @staticmethod
     def backward(ctx, gL):
         noise, cs, cc, st, dL = ctx.saved_tensors
-        dims, bins, filt, tdev, tdt = ctx.meta
+        dims, seed, bins, filt, tdev, tdt = ctx.meta
+        if noise is None:
+            noise = _field_spectrum(dims, filt, seed, bins, cs.device)[0]
         g = _noise_grad(dims, filt, noise, bins, dL * gL.to(device=dL.device, dtype=torch.float64), cs, cc, st)
         return g.to(device=tdev, dtype=tdt), None, None, None, None, None, None, None, None
 
@@ -714,7 +760,7 @@ def spectrum_loss(theta, dims, seed, n_radial, target, alpha, sigma_f=1.0, eps_r
     """Spectrum-matching loss L = mean over radial bins 1..R-1 with modes of
     (ln(P_b + eps) - ln(T_b + eps))^2, eps = eps_rel sigma_f^2, P the field's radial continuous
     spectrum and T the expected spectrum of the `target` filter, both binned by the library and
-    the loss and its gradient computed by it (hu_spectrum_loss, hu_spectrum_grad); returns a scalar
+    the loss and its gradient computed by it (hu_spectrum_loss, hu_noise_grad); returns a scalar
     tensor differentiable in theta."""
     bins = (int(n_radial), 1)
     dev = theta.device if theta.is_cuda else torch.device("cuda")
