@@ -84,7 +84,7 @@ enum { HU_OP_GEN_FIELD = 0, HU_OP_PIPELINE = 1, HU_OP_POWER_SPECTRUM = 2, HU_OP_
        HU_OP_FIELD_SPECTRUM = 8, /* its workspace */
        HU_OP_NOISE_GRAD = 9,     /* the workspace of hu_noise_grad */
        /* HU_OP_PIPELINE or HU_OP_GEN_FIELD with room for the faster forms (a table of the filter's
-          amplitudes; up to 256 small 2D fields at a time).  hu_pipeline and hu_gen_field use the room
+          amplitudes, where a filter may have one read; up to 256 small 2D fields at a time).  hu_pipeline and hu_gen_field use the room
           they are given, with the same results either way. */
        HU_OP_PIPELINE_PREFERRED = 10 };
 

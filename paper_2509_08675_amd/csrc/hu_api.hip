@@ -137,7 +137,7 @@ int hu_workspace_size(int op, hu_dims dims, int32_t batch, const hu_bins* bins, 
       return HU_OK;
     case HU_OP_PIPELINE_PREFERRED:
       HU_TRY(layout(g, chunk, true, widest_plan(), bins, &lay));
-      *bytes = lay.total_amp;
+      *bytes = amp_table(g, chunk, true) || amp_table(g, chunk, false) ? lay.total_amp : lay.total;
       return HU_OK;
     case HU_OP_POWER_SPECTRUM:
       if (!bins) return HU_ERR_ARG;

@@ -205,6 +205,14 @@ def alloc_workspace(op, dims, batch, bins=None, device="cuda"):
     return torch.empty(max(n, 256), dtype=torch.uint8, device=device)
 
 
+def _alloc_generator_workspace(op, dims, batch, bins, device):
+    """A workspace with room for the faster forms, or the plain one of `op` where memory is short of that."""
+    try:
+        return alloc_workspace(HU_OP_PIPELINE_PREFERRED, dims, batch, bins, device)
+    except torch.OutOfMemoryError:
+        return alloc_workspace(op, dims, batch, bins, device)
+
+
 def _nb(bins):
     return int(bins[0]) * (int(bins[1]) if len(bins) > 1 else 1) + 1
 
@@ -232,7 +240,7 @@ def gen_field(dims, filt, seeds, cont_bins=None, device="cuda", work=None, out=N
         cc = torch.empty((B, nb), dtype=torch.int64, device=device)
         b = make_bins(cont_bins)
     if work is None:
-        work = alloc_workspace(HU_OP_PIPELINE_PREFERRED, dims, B, cont_bins, device)
+        work = _alloc_generator_workspace(HU_OP_GEN_FIELD, dims, B, cont_bins, device)
     h = make_filter(filt)
     _check(_lib.hu_gen_field(make_dims(dims), B, ctypes.byref(h), _seeds(seeds), _ptr(field), _ptr(stats),
                              ctypes.byref(b) if b else None, _ptr(cs), _ptr(cc), _ptr(work), work.numel(),
@@ -371,7 +379,7 @@ class PipelineBuffers:
             self.pm1_cnt = torch.empty((batch, nb), dtype=torch.int64, device=dev)
         else:
             self.pm1_sum = self.pm1_cnt = None
-        self.work = alloc_workspace(HU_OP_PIPELINE_PREFERRED, dims, batch, bins, dev)
+        self.work = _alloc_generator_workspace(HU_OP_PIPELINE, dims, batch, bins, dev)
         o = hu_outputs()
         for name in ("field", "pm1", "stats", "counts", "cont_sum", "cont_cnt", "pm1_sum", "pm1_cnt"):
             setattr(o, name, None if getattr(self, name) is None else getattr(self, name).data_ptr())

@@ -244,3 +244,32 @@ def test_spectrum_loss_validation(hf):
     assert lib.hu_spectrum_loss(b, p, p, p, p, float("nan"), p, p, None) == hf.HU_ERR_ARG
     assert lib.hu_spectrum_loss(hf.make_bins((0, 1)), p, p, p, p, 1e-12, p, p, None) == hf.HU_ERR_ARG
     assert lib.hu_spectrum_loss(b, odd, p, p, p, 1e-12, p, p, None) == hf.HU_ERR_ALIGN
+
+
+def test_preferred_workspace_has_a_table_only_where_one_may_be_read(hf):
+    # the table: a float for every mode of the half spectrum
+    def extra(dims, batch):
+        return (hf.workspace_size(hf.HU_OP_PIPELINE_PREFERRED, dims, batch, (16, 1)) -
+                hf.workspace_size(hf.HU_OP_PIPELINE, dims, batch, (16, 1)))
+    for dims, batch in (((512, 512, 512), 1), ((768, 1024, 1024), 1), ((256, 256, 128), 1)):
+        assert extra(dims, batch) == 0
+    for dims, batch in (((1024, 1024), 1), ((2048, 2048), 16), ((64, 64, 64), 1), ((256, 256, 256), 2)):
+        modes = dims[0] * (dims[1] if len(dims) == 3 else 1) * (dims[-1] // 2 + 1)
+        assert modes * 4 <= extra(dims, batch) <= modes * 4 * 1.1 + (1 << 16)
+    # up to 256 small 2D fields at a time
+    assert extra((64, 64), 200) > 130 * 64 * 36 * 8
+
+
+def test_short_memory_takes_the_plain_workspace(hf, monkeypatch):
+    import torch
+    taken = []
+
+    def alloc(op, dims, batch, bins=None, device="cuda"):
+        taken.append(op)
+        if op == hf.HU_OP_PIPELINE_PREFERRED:
+            raise torch.OutOfMemoryError("no room")
+        return op
+
+    monkeypatch.setattr(hf, "alloc_workspace", alloc)
+    assert hf._alloc_generator_workspace(hf.HU_OP_GEN_FIELD, (64, 64), 1, None, "cpu") == hf.HU_OP_GEN_FIELD
+    assert taken == [hf.HU_OP_PIPELINE_PREFERRED, hf.HU_OP_GEN_FIELD]
