@@ -290,7 +290,8 @@ int hu_spectrum_grad(hu_dims dims, const hu_filter* filt, uint64_t seed, hu_bins
 
 /* The two halves of a fitting step, for callers that want a field's binned continuous spectrum and its
  * gradient but not the field: hu_field_spectrum forms stats [4], cont_sum and cont_cnt [R*A+1] exactly as
- * hu_gen_field with one seed does (same bits under the same plan) and leaves the noise spectrum in
+ * hu_gen_field with one seed does (same bits under the same plan, except whole_field: it always runs the
+ * pass sequence, whose sums have another order) and leaves the noise spectrum in
  * `noise` (device, 256-byte aligned, hu_workspace_size(HU_OP_NOISE, dims, 1, ...) bytes, caller-owned);
  * hu_noise_grad is hu_spectrum_grad reading that buffer (unchanged) instead of regenerating it.
  * Workspaces: hu_workspace_size(HU_OP_FIELD_SPECTRUM | HU_OP_NOISE_GRAD, dims, 1, &bins, ...).
@@ -349,7 +350,8 @@ int hu_pipeline_batch(const hu_job* jobs, int32_t njobs, float near_tol, int32_t
  * and filter_exchange, the exchange of the axis-0 binning and filter passes: complex values
  * through LDS, or split (real and imaginary parts in two rounds through half the LDS, so more
  * workgroups are resident, at two more barriers per exchange; axis-0 lengths of 192 and more);
- * default the binning pass split, the filter pass complex, 1 the other one; last whole_field (2D grids with n_x / 2 in 8 .. 64 and n0 in 16 .. 128, powers of two, whose
+ * default the binning pass split, the filter pass complex (its FP64 and tabulated form evaluated in the pass
+ * under either value), 1 the other one; last whole_field (2D grids with n_x / 2 in 8 .. 64 and n0 in 16 .. 128, powers of two, whose
  * half spectrum and bins fit in one workgroup's LDS): 1 runs the whole path as one kernel, one
  * workgroup per field, the spectrum never leaving LDS (HBM traffic: the outputs only); and plane
  * (3D grids with n_x / 2 in {16, 24, 32, 48, 64} and n_y in {32, 48, 64, 96, 128}): 1 runs the x

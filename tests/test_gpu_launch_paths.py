@@ -179,6 +179,35 @@ def test_field_spectrum_and_noise_grad(hf, dims, filt, nr):
     assert torch.equal(got[0], ref) and torch.equal(got[1], ref)
 
 
+# ... under the plans with kernels of their own.  plane: the noise spectrum of the plane kernel, the bits of
+# hu_gen_field.  whole_field: hu_gen_field takes the whole-field kernel, another transform and order of sums
+# (FP32 transforms: a few 1e-7 of a mode's amplitude); hu_field_spectrum stays with the passes.
+@pytest.mark.parametrize("dims,entry", [((16, 32, 32), 12), ((48, 96, 64), 12), ((32, 16), 11), ((128, 128), 11)])
+def test_field_spectrum_under_other_plans(hf, dims, entry):
+    _say("fitting step, plan entry", dims, entry)
+    bins, seed = (12, 1), 31
+    base = hf._field_spectrum(dims, BAND, seed, bins, torch.device("cuda"))
+    dL = torch.linspace(-1.0, 1.0, 13, dtype=torch.float64, device="cuda")
+    gbase = hf._noise_grad(dims, BAND, base[0], bins, dL, *base[1:])
+    hf.plan_set(dims, 1, bins, [1 if i == entry else 0 for i in range(13)])
+    try:
+        full = hf.gen_field(dims, BAND, [seed], cont_bins=bins)
+        noise, cs, cc, st = hf._field_spectrum(dims, BAND, seed, bins, torch.device("cuda"))
+        g = hf._noise_grad(dims, BAND, noise, bins, dL, cs, cc, st)
+        torch.cuda.synchronize()
+    finally:
+        hf.plan_set(dims, 1, bins, [0] * 13)
+    assert torch.equal(cc, full["cont_cnt"][0])
+    want, got = full["cont_sum"][0].cpu().numpy(), cs.cpu().numpy()
+    if entry == 12:
+        assert torch.equal(cs, full["cont_sum"][0]) and torch.equal(st[0], full["stats"][0])
+    else:
+        assert torch.equal(cs, base[1]) and torch.equal(st, base[3])
+        np.testing.assert_allclose(got, want, rtol=1e-5, atol=1e-6 * want.max())
+    np.testing.assert_allclose(got, base[1].cpu().numpy(), rtol=1e-5, atol=1e-6 * want.max())
+    np.testing.assert_allclose(g.cpu().numpy(), gbase.cpu().numpy(), rtol=1e-4, atol=1e-5 * float(gbase.abs().max()))
+
+
 # Statistics formed by the last row pass (up to 512 filter tiles; 258, 260 and 387 here) and by their own
 # kernel (a batch whose fields stream past the cache): the same sums in the same order, the same bits.
 @pytest.mark.parametrize("dims,batch", [((32, 64, 256), 64), ((64, 128, 128), 34), ((32, 96, 256), 44)])

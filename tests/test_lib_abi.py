@@ -273,3 +273,60 @@ def test_short_memory_takes_the_plain_workspace(hf, monkeypatch):
     monkeypatch.setattr(hf, "alloc_workspace", alloc)
     assert hf._alloc_generator_workspace(hf.HU_OP_GEN_FIELD, (64, 64), 1, None, "cpu") == hf.HU_OP_GEN_FIELD
     assert taken == [hf.HU_OP_PIPELINE_PREFERRED, hf.HU_OP_GEN_FIELD]
+
+
+def test_fitting_step_argument_errors_and_workspaces(hf):
+    lib = hf.lib_handle()
+    dims, bins = (64, 32, 16), (16, 1)
+    d, b = hf.make_dims(dims), hf.make_bins(bins)
+    f = hf.make_filter(dict(p=2, semi=(1, 1, 1), rot=0, alpha=2, k0=0.2, width=0.05))
+    fake, off = ctypes.c_void_p(1 << 20), ctypes.c_void_p((1 << 20) + 8)   # never dereferenced: validation fails first
+
+    # sizes: the noise as the field's half spectrum; the workspaces without one
+    spec = 64 * 32 * 9 * 8
+    size = {op: hf.workspace_size(op, dims, 1, bins) for op in
+            (hf.HU_OP_NOISE, hf.HU_OP_FIELD_SPECTRUM, hf.HU_OP_NOISE_GRAD, hf.HU_OP_PIPELINE, hf.HU_OP_LOSS)}
+    assert size[hf.HU_OP_NOISE] == spec
+    assert size[hf.HU_OP_FIELD_SPECTRUM] == size[hf.HU_OP_PIPELINE] - spec
+    assert size[hf.HU_OP_NOISE_GRAD] == size[hf.HU_OP_LOSS] - spec
+    out = ctypes.c_size_t()
+    for op in (hf.HU_OP_FIELD_SPECTRUM, hf.HU_OP_NOISE_GRAD):
+        assert lib.hu_workspace_size(op, d, 1, None, ctypes.byref(out)) == hf.HU_ERR_ARG
+    assert lib.hu_workspace_size(11, d, 1, ctypes.byref(b), ctypes.byref(out)) == hf.HU_ERR_ARG
+
+    def forward(filt=f, ptrs=(fake,) * 4, work=fake, nbytes=1 << 40, bb=b):
+        noise, stats, cs, cc = ptrs
+        return lib.hu_field_spectrum(d, ctypes.byref(filt), 1, bb, noise, stats, cs, cc, work, nbytes, None)
+
+    def gradient(filt=f, ptrs=(fake,) * 6, work=fake, nbytes=1 << 40, bb=b):
+        noise, dl, cs, cc, st, g = ptrs
+        return lib.hu_noise_grad(d, ctypes.byref(filt), noise, bb, dl, cs, cc, st, g, work, nbytes, None)
+
+    for call, n, op in ((forward, 4, hf.HU_OP_FIELD_SPECTRUM), (gradient, 6, hf.HU_OP_NOISE_GRAD)):
+        for i in range(n):
+            ptrs = [fake] * n
+            ptrs[i] = None
+            assert call(ptrs=ptrs) == hf.HU_ERR_ARG
+            ptrs[i] = off
+            assert call(ptrs=ptrs) == hf.HU_ERR_ALIGN
+        assert call(work=None) == hf.HU_ERR_ARG
+        assert call(work=off) == hf.HU_ERR_ALIGN
+        assert call(nbytes=size[op] - 1) == hf.HU_ERR_WORKSPACE
+        assert call(bb=hf.make_bins((16, 4))) == hf.HU_ERR_ARG          # angular bins are 2D only
+        bad = hf.make_filter(dict(p=0.0, semi=(1, 1, 1), rot=0, alpha=2, k0=0.2, width=0.05))
+        assert call(filt=bad) == hf.HU_ERR_ARG
+    # the gradient is that of sqrt(chi) of the analytic form alone
+    lifted = hf.make_filter(dict(p=2, semi=(1, 1, 1), rot=0, alpha=2, k0=0.2, width=0.05, offset=1e-3))
+    assert gradient(filt=lifted) == hf.HU_ERR_UNSUPPORTED
+    tab = hf.make_filter(dict(p=2, semi=(1, 1, 1), rot=0, alpha=2, k0=0.2, width=0.05))
+    tab.prof, tab.prof_n, tab.prof_dk = 1 << 20, 64, 0.05
+    assert gradient(filt=tab) == hf.HU_ERR_UNSUPPORTED
+
+
+def test_debug_bin_runs_argument_errors(hf):
+    lib = hf.lib_handle()
+    none = [None] * 7
+    assert lib.hu_debug_bin_runs(hf.make_dims((100, 64)), hf.make_bins((8, 1)), 0, *none) == hf.HU_ERR_SIZE
+    assert lib.hu_debug_bin_runs(hf.make_dims((64, 64)), hf.make_bins((0, 1)), 0, *none) == hf.HU_ERR_ARG
+    assert lib.hu_debug_bin_runs(hf.make_dims((64, 64)), hf.make_bins((8, 1)), 2, *none) == hf.HU_ERR_ARG
+    assert lib.hu_debug_bin_runs(hf.make_dims((64, 64)), hf.make_bins((8, 1)), 1, *none) == hf.HU_OK
