@@ -368,7 +368,7 @@ int hu_pipeline_batch(const hu_job* jobs, int32_t njobs, float near_tol, int32_t
  * if cache_path is non-NULL, all tuned plans are written as JSON there (read back at start-up from
  * $HUFIELD_TUNE_CACHE).  ms_out (host, optional) receives 15 values: the default plan's time and
  * the tuned plan's (timed side by side after the search), and for each entry the time with it
- * flipped during the search (0 where not tried), in ms.  Allocates and frees its own device
+ * flipped during the search (0 where not tried; an entry without effect on this grid: the plan's own), in ms.  Allocates and frees its own device
  * buffers and synchronises.  The tile-width, schedule and exchange entries leave fields and sign
  * maps the same bit for bit (the spectra to FP64 rounding: the tile width changes how the bins' partials
  * are grouped); the radix, whole_field and plane entries change the FP32 rounding (other transforms,

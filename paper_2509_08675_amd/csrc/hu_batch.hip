@@ -396,6 +396,10 @@ int hu_autotune(hu_dims dims, int32_t batch, const hu_bins* bins, const char* ca
       if ((k == P_BSPLIT || k == P_FSPLIT) && !split_length(g.n[0])) continue;
       if (k == P_WHOLE && !whole_field_ok(g, nb)) continue;
       if (k == P_PLANE && !plane_ok(g)) continue;
+      if (half_tiles(g) && (k == P_FILTER || k == P_BIN)) {  // the same launches under either value
+        if (sweep == 0) tried[k] = time_plan(best);
+        continue;
+      }
       TunePlan cand = best;
       cand.v[k] ^= 1;
       double tb = 0.0, tc = 0.0;

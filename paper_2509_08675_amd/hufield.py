@@ -560,7 +560,7 @@ def pipeline_batch(bufs, near_tol=1e-5):
 def autotune(dims, batch, bins, cache_path=None):
     """Search the plan of this shape class (hu_autotune); returns ({entry: 0 or 1}, dict of the
     default plan's and the tuned plan's summed kernel ms and, per entry, the ms with it flipped
-    during the search (0 where not tried))."""
+    during the search (0 where not tried, the plan's own for an entry without effect on the grid))."""
     ms = (ctypes.c_double * (2 + len(PASS_NAMES)))()
     b = make_bins(bins)
     _check(_lib.hu_autotune(make_dims(dims), int(batch), ctypes.byref(b),

@@ -230,6 +230,17 @@ def test_half_width_variants_match(hf, dims, bins):
     hf.plan_set(dims, 2, bins, [0] * 13)
 
 
+# 2D columns up to 1024 take half-width filter and binning tiles under either value of the plan's entries: the
+# search has nothing to choose there, whatever the timings say.
+def test_autotune_leaves_entries_without_effect(hf):
+    dims, bins = (64, 48), (16, 4)
+    _say("autotune, entries without effect", dims)
+    plan, ms = hf.autotune(dims, 2, bins, None)
+    hf.plan_set(dims, 2, bins, [0] * 13)
+    assert plan["cols_filter"] == 0 and plan["cols_bin"] == 0 and plan["bin_schedule"] == 0
+    assert ms["flipped_ms"]["cols_filter"] > 0 and ms["flipped_ms"]["cols_bin"] > 0
+
+
 def test_autotune_writes_plan(hf, tmp_path):
     dims, bins = (256, 256), (32, 6)
     path = str(tmp_path / "tune.json")
