@@ -47,8 +47,10 @@ template <int L, int V, int RV, bool SPLIT>
 static hipError_t launch_cols_bin_L(const BinArgs& a, hipStream_t st) {
   constexpr int T = ColTile<L, V>::T;
   const size_t lds = col_bin_bytes<L, V, SPLIT>(a.tb);
-  if (a.gm.ndim == 2) hipLaunchKernelGGL((k_cols_bin<L, V, RV, SPLIT, true>), dim3(sched_blocks(a.sc)), dim3(T), lds, st, a);
-  else hipLaunchKernelGGL((k_cols_bin<L, V, RV, SPLIT, false>), dim3(sched_blocks(a.sc)), dim3(T), lds, st, a);
+  const dim3 grid(sched_blocks(a.sc));
+  if (a.gm.ndim == 3) hipLaunchKernelGGL((k_cols_bin<L, V, RV, SPLIT, false>), grid, dim3(T), lds, st, a);
+  else if constexpr (V == 1 || !half_tile_length(L)) hipLaunchKernelGGL((k_cols_bin<L, V, RV, SPLIT, true>), grid, dim3(T), lds, st, a);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

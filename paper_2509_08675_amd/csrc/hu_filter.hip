@@ -252,13 +252,16 @@ static hipError_t launch_cols_filter_L(FilterArgs a, hipStream_t st) {
   }
   const dim3 grid(sched_blocks(a.sc));
   auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(T), lds, st, a); };
+  auto evaluated = [&](auto amp) {
+    constexpr int AMP = decltype(amp)::value;
+    if (a.gm.ndim == 3) go(k_cols_filter<L, 3, V, AMP, RV, SPLIT>);
+    else if constexpr (V == 1 || !half_tile_length(L)) go(k_cols_filter<L, 2, V, AMP, RV, SPLIT>);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+  };
   if (a.amp) go(k_cols_filter<L, 2, V, AMP_TABLE, RV, SPLIT>);
-  else if (a.any_gen) {
-    if constexpr (!SPLIT)
-      a.gm.ndim == 2 ? go(k_cols_filter<L, 2, V, AMP_GENERAL, RV, false>) : go(k_cols_filter<L, 3, V, AMP_GENERAL, RV, false>);
-  } else {
-    a.gm.ndim == 2 ? go(k_cols_filter<L, 2, V, AMP_FP32, RV, SPLIT>) : go(k_cols_filter<L, 3, V, AMP_FP32, RV, SPLIT>);
-  }
+  else if (!a.any_gen) return evaluated(std::integral_constant<int, AMP_FP32>{});
+  else if constexpr (!SPLIT) return evaluated(std::integral_constant<int, AMP_GENERAL>{});
   return hipGetLastError();
 }
 

@@ -78,7 +78,7 @@ bool aligned(const void* p, size_t a);
 // 512^2 164 -> 151, one of 1024^2 55 -> 50, of 384 x 192 69 -> 62 (every size from 64^2 gains).  Not at 2048,
 // where two columns would use 16 of every 32 bytes of the layout (one field 80 -> 89 us), nor in 3D (even).
 // A rule of the grid alone, so that the bins stay the same bits over all batch sizes.
-inline bool half_tiles(const Geom& g) { return g.nd == 2 && g.n[0] <= 1024; }
+inline bool half_tiles(const Geom& g) { return g.nd == 2 && half_tile_length(g.n[0]); }
 // fields that a uniform call of `batch` fields takes per launch sequence, given room for them
 int chunk_fields(const Geom& g, int batch);
 // whether a uniform launch sequence of B fields reads its amplitudes from a table, given room for it

@@ -13,6 +13,9 @@ namespace hu {
 // (shorter columns have small exchange buffers)
 constexpr bool split_length(int L) { return L >= 192; }
 
+// 2D grids whose filter and binning passes take half-width tiles under either plan entry (half_tiles)
+constexpr bool half_tile_length(int L) { return L <= 1024; }
+
 // column lengths whose binning threads may store a run that is alone in its bin themselves (TileBinDev::dst).
 // Not the longer ones: their runs are longer, and the code alone costs 16 x 2048^2 488 -> 496 us.
 constexpr bool direct_length(int L) { return L <= 512; }

@@ -80,3 +80,12 @@ def test_five_wave_filter_tiles_leave_room_for_two_workgroups(kernels):
     for length in (384, 768):
         regs, scratch = found[length, 3, 0]
         assert regs <= 128 and scratch <= 64, (length, regs, scratch)
+
+
+def test_no_kernel_that_nothing_launches(kernels):
+    # 2D columns up to 1024 always take half-width filter and binning tiles
+    rx = [re.compile(r"k_cols_filterILi(\d+)ELi2ELi0ELi[01]E"), re.compile(r"k_cols_binILi(\d+)ELi0ELi\dELb\dELb1E")]
+    for name in kernels:
+        for r in rx:
+            m = r.search(name)
+            assert m is None or int(m.group(1)) > 1024, name
