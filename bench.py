@@ -660,7 +660,33 @@ def kernel_family(name):
         return "plane_inv_thresh" if args[2] == "true" else "plane_inv"
     if k in ("k_field_lds", "k_plane_fwd"):
         return k[2:]
-    return {"k_cols_filter": "cols_filter", "k_cols_bin": "cols_bin", "k_cols_bin_tile": "cols_bin"}.get(k)
+    return {"k_cols_filter": "cols_filter", "k_cols_bin": "cols_bin", "k_amp": "amp"}.get(k)
+
+
+def kernel_shape_class(name):
+    """Shape class ("2D 512^2") of a rocprofv3 kernel name, its grid taken as a square or cube: the row passes
+    name n_x / 2 (2D: tiled layout), the axis-0 and y passes n along that axis, cols_filter also the dimension and
+    cols_bin whether bins may be angular (2D).  None for kernels that name no grid."""
+    import re
+    m = re.search(r"hu::k_(\w+)<([^>]*)>", name)
+    if not m:
+        return None
+    k, a = m.group(1), [t.strip() for t in m.group(2).split(",")]
+    if k in ("rows_r2c", "rows_c2r"):
+        n, d = 2 * int(a[0]), 2 if a[2] == "true" else 3
+    elif k == "cols_filter":
+        n, d = int(a[0]), int(a[1])
+    elif k == "cols_bin":
+        n, d = int(a[0]), 2 if a[4] == "true" else 3
+    elif k == "cols":
+        n, d = int(a[0]), 3
+    elif k == "field_lds":                         # <n_x / 2, n0, GEN>
+        n, d = int(a[1]), 2
+    elif k in ("plane_fwd", "plane_inv"):          # <n_x / 2, n_y, ...>
+        n, d = int(a[1]), 3
+    else:
+        return None
+    return "%dD %d^%d" % (d, n, d)
 
 
 def _csv_rows(d, suffix):
@@ -834,40 +860,14 @@ def summarize_c4_trace(td, replays=10):
     for f, (n, t) in sorted(fam.items(), key=lambda kv: -kv[1][1]):
         md.append("| %s | %d | %.1f | %.2f |" % (f, n // replays, t / replays, t / n))
 
-    # the shape class of a dispatch from its template arguments: the row passes take n_x / 2 (2D:
-    # tiled layout), the axis-0 and y passes n along that axis (cols_filter names the dimension)
-    def shape_class(name):
-        import re
-        m = re.search(r"hu::k_(\w+)<([^>]*)>", name)
-        if not m:
-            return None
-        k, a = m.group(1), [t.strip() for t in m.group(2).split(",")]
-        if k in ("rows_r2c", "rows_c2r"):
-            n, d = 2 * int(a[0]), 2 if a[2] == "true" else 3
-        elif k == "cols_filter":
-            n, d = int(a[0]), int(a[1])
-        elif k in ("cols", "cols_bin"):
-            n, d = int(a[0]), 3
-        elif k == "cols_bin_tile":                 # 2D by default (see the table's caption)
-            n, d = int(a[0]), 2
-        elif k == "field_lds":                     # <n_x / 2, n0, GEN>: the C4 grids are square
-            n, d = int(a[1]), 2
-        elif k in ("plane_fwd", "plane_inv"):      # <n_x / 2, n_y, ...>: cubes
-            n, d = int(a[1]), 3
-        else:
-            return None
-        return "%dD %d^%d" % (d, n, d)
     cls = {}
     for i in range(replays):
         for r in rows[len(rows) - (i + 1) * period:len(rows) - i * period]:
-            c = shape_class(r["Kernel_Name"])
+            c = kernel_shape_class(r["Kernel_Name"])
             if c:
                 cls[c] = cls.get(c, 0.0) + (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-3
     md += ["", "Summed kernel time per shape class (the axis passes and the whole-field and plane kernels; "
-           "finalize and the final reduction left out).  The one-item-per-workgroup binning kernel's "
-           "template arguments do not name the dimension: its dispatches count as 2D, so a 3D class "
-           "tuned to it (bin_schedule) shows part of its time under a 2D row of the same length "
-           "(here 96 and 128).", "", "| class | summed us per launch |", "|---|---|"]
+           "finalize and the final reduction left out).", "", "| class | summed us per launch |", "|---|---|"]
     for c, t in sorted(cls.items(), key=lambda kv: -kv[1]):
         md.append("| %s | %.1f |" % (c, t / replays))
     with open(os.path.join(ROOT, "profiles", "batch_kernels_c4_uneven_512.md"), "w") as fh:
