@@ -479,8 +479,7 @@ hipError_t launch_grad_final(const GradFinalArgs& a, hipStream_t st) {
 // c mod gridDim.x; thread t of a chunk evaluates w H_sym^2 of its FS_RUN consecutive modes (FP32,
 // widened to FP64) and sums each run of equal bins in FP64 in mode order.  The runs of a chunk are
 // combined per bin in integer arithmetic (largest binary exponent, then fixed-point adds at
-// 2^(exponent - 48), as in the tile binning of the axis-0 passes), so the chunk's bin sums do not
-// depend on the order of the atomics; each bin's slot of the workgroup's partial row is owned by
+// 2^(exponent - 48): run_commit), so the chunk's bin sums do not depend on the order of the atomics; each bin's slot of the workgroup's partial row is owned by
 // one thread, which adds the chunk sums in chunk order.  k_filter_spectrum_final then sums the
 // rows in workgroup order and scales by sigma_f^2 N / sum w H^2.
 // ---------------------------------------------------------------------------------------------

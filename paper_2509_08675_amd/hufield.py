@@ -666,25 +666,31 @@ class _KeptNoise:
 
     def __init__(self):
         self._lock = threading.Lock()
-        self._bytes = {}
-        self._freed = collections.deque()            # filled by finalizers, which take no lock
+        self._bytes = {}                             # per device
+        self._refs = {}
+        self._gone = collections.deque()             # filled by the weak references, which take no lock
+
+    def _settle(self):
+        while self._gone:
+            _, device, n = self._refs.pop(id(self._gone.popleft()))
+            self._bytes[device] -= n
 
     def held(self, device):
         with self._lock:
-            while self._freed:
-                dev, n = self._freed.popleft()
-                self._bytes[dev] -= n
+            self._settle()
             return self._bytes.get(device, 0)
 
     def keep(self, noise):
         """Whether `noise` may be kept; it then counts until the tensor is released."""
-        n = noise.numel() * noise.element_size()
-        self.held(noise.device)
+        device, n = noise.device, noise.numel() * noise.element_size()
         with self._lock:
-            if self._bytes.get(noise.device, 0) + n > NOISE_KEEP_BYTES:
+            self._settle()
+            total = self._bytes.get(device, 0) + n
+            if total > NOISE_KEEP_BYTES:
                 return False
-            self._bytes[noise.device] = self._bytes.get(noise.device, 0) + n
-        weakref.finalize(noise, self._freed.append, (noise.device, n)).atexit = False
+            self._bytes[device] = total
+            ref = weakref.ref(noise, self._gone.append)
+            self._refs[id(ref)] = (ref, device, n)
         return True
 
 
