@@ -660,7 +660,7 @@ void tile_runs(const Axis0Geom& a, int C, bool sym, TileHost* th) {
   th->info.resize(ntiles);
   std::vector<uint16_t> rbin;                      // the runs' bins, tile after tile
   std::vector<size_t> roff(ntiles + 1, 0);
-  std::vector<int> cnt, off;
+  std::vector<int> cnt, off, cur;
   long long alone = 0;                             // runs that are the only one of their bin in the tile
   for (int t = 0; t < ntiles; ++t) {
     const size_t r0 = rbin.size();
@@ -685,6 +685,7 @@ void tile_runs(const Axis0Geom& a, int C, bool sym, TileHost* th) {
     }
     roff[t + 1] = rbin.size();
     th->runs_max = std::max(th->runs_max, (int)(rbin.size() - r0));
+    if (sym || !direct_length(a.n0)) continue;
     cnt.assign(th->toff[t + 1] - th->toff[t], 0);
     for (size_t r = r0; r < rbin.size(); ++r) cnt[rbin[r]]++;
     for (int c : cnt) alone += c == 1;
@@ -699,31 +700,35 @@ void tile_runs(const Axis0Geom& a, int C, bool sym, TileHost* th) {
   for (int t = 0; t < ntiles; ++t) {
     const size_t l0 = roff[t], s0 = th->slot.size();
     const int nr = (int)(roff[t + 1] - l0), nloc = (int)(th->toff[t + 1] - th->toff[t]);
+    const uint16_t* rb = rbin.data() + l0;
+    const uint32_t* wp = th->wpos.data() + th->toff[t];
+    uint16_t* lst = th->list.data() + l0;
     cnt.assign(nloc, 0);
     off.assign(nloc + 1, 0);
-    for (int r = 0; r < nr; ++r) cnt[rbin[l0 + r]]++;
+    for (int r = 0; r < nr; ++r) cnt[rb[r]]++;
     for (int j = 0; j < nloc; ++j) off[j + 1] = off[j] + cnt[j];
-    std::vector<int> cur(off.begin(), off.end() - 1);
-    for (int r = 0; r < nr; ++r) th->list[l0 + cur[rbin[l0 + r]]++] = (uint16_t)r;
-    for (int lg = 6; lg >= 0; --lg)
+    cur.assign(off.begin(), off.end() - 1);
+    for (int r = 0; r < nr; ++r) lst[cur[rb[r]]++] = (uint16_t)r;
+    for (int lg = 6; lg >= 0; --lg) {
+      // the bins of 2^lg lanes: the most of a lane, up to a wave of them for any number of runs
+      const int least = lg ? (LANE_RUNS << (lg - 1)) + 1 : 1, most = lg < 6 ? LANE_RUNS << lg : nr;
       for (int j = 0; j < nloc; ++j) {
-        int need = 0;
-        while (need < 6 && cnt[j] > (LANE_RUNS << need)) ++need;
-        if (need != lg) continue;
-        const uint32_t place = th->wpos[th->toff[t] + j];
+        if (cnt[j] < least || cnt[j] > most) continue;
         if (direct && cnt[j] == 1) {
-          th->dst[l0 + th->list[l0 + off[j]]] = place;
+          th->dst[l0 + lst[off[j]]] = wp[j];
           continue;
         }
         const int G = 1 << lg;
         for (int u = 0; u < G; ++u) {
           const int n = cnt[j] > u ? (cnt[j] - u + G - 1) / G : 0;
-          th->slot.push_back(make_uint2((uint32_t)(off[j] + u) | (uint32_t)n << 16 | (uint32_t)lg << 29, u == 0 ? place : ~0u));
+          const uint16_t* e = lst + off[j] + u;
+          th->slot.push_back(make_uint2((uint32_t)(off[j] + u) | (uint32_t)n << 16 | (uint32_t)lg << 29, u == 0 ? wp[j] : ~0u));
           uint32_t q[4] = {0u, 0u, 0u, 0u};
-          for (int i = 0; i < 4 && i < n; ++i) q[i] = th->list[l0 + off[j] + u + i * G];
+          for (int i = 0; i < 4 && i < n; ++i) q[i] = e[i * G];
           th->ent.push_back(make_uint2(q[0] | q[1] << 16, q[2] | q[3] << 16));
         }
       }
+    }
     while ((th->slot.size() - s0) % 64) {
       th->slot.push_back(make_uint2(0u, ~0u));
       th->ent.push_back(make_uint2(0u, 0u));
