@@ -415,7 +415,7 @@ int hu_debug_bin_tables(hu_dims dims, hu_bins bins, int32_t variant, int32_t* si
  *   seg   [ntiles][threads][2]: bit i set where entry i starts a run; the thread's first run
  *   info  [ntiles][4]: the tile's first run in list and dst, its first lane in slot and ent, its lanes
  *   slot  [lanes][2]: first entry in the tile's list | entries << 16 | log2 of the bin's lanes << 29; the place of
- *         the partial (the bin's first lane) or 2^32 - 1.  ent [lanes][4]: the lane's first four runs
+ *         the partial (the bin's first lane) or 2^32 - 1.  ent [lanes][8]: the lane's first eight runs
  *   list  [runs]: the runs of each bin of the tile, bin after bin
  *   dst   [runs]: where used, the place of the partial of a run alone in its bin (such a bin has no lane), or 2^32 - 1
  * Each array may be NULL (host arrays). */

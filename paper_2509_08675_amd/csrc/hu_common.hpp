@@ -379,7 +379,7 @@ __device__ __forceinline__ void run_commit(int j, double s, int* hx, unsigned lo
 // runs by LDS atomics, two passes over them, took the binning pass 88 us at 4 x 256^3 and at 16 x 2048^2; this
 // form 60 and 66.)
 // ---------------------------------------------------------------------------------------------
-constexpr int ENT = 4, LIST_AHEAD = 8;    // entries of a slot in its own record, and with those loaded ahead from the list
+constexpr int ENT = 8;                    // entries in a lane's record
 
 template <int N, class V>
 __device__ __forceinline__ void runs_store(const V (&v)[N], uint2 sg, double* runs) {
@@ -457,15 +457,7 @@ __device__ __forceinline__ void tile_bins(float2* lds, const TileBinDev& tb, con
   const uint2 sg = pre.sg;
   uint2 sl = pre.sl;
   const uint16_t* list = tb.list + pre.list;
-  uint2 en = tid < nslots ? tb.ent[pre.slot + tid] : make_uint2(0u, 0u);
-  unsigned idx[LIST_AHEAD - ENT];
-  // the slot's entries from the list up to LIST_AHEAD, on their way while the runs are formed
-  auto ahead = [&]() {
-#pragma unroll
-    for (int q = ENT; q < LIST_AHEAD; ++q)
-      idx[q - ENT] = (unsigned)q < (sl.x >> 16 & 0x1FFFu) ? (unsigned)list[(sl.x & 0xFFFFu) + ((unsigned)q << (sl.x >> 29))] : 0u;
-  };
-  ahead();
+  uint4 en = tid < nslots ? tb.ent[pre.slot + tid] : make_uint4(0u, 0u, 0u, 0u);
   if (!ANG || tb.sym) {                              // uniform over the launch
     double v[H + 1];
     if (act) {
@@ -514,17 +506,18 @@ __device__ __forceinline__ void tile_bins(float2* lds, const TileBinDev& tb, con
   __syncthreads();                                   // the runs are complete
   for (int i = tid; i < nslots;) {                   // uniform over a wave: nslots and T are multiples of 64
     i += T;
-    uint2 sl2 = make_uint2(0u, ~0u), en2 = make_uint2(0u, 0u);
+    uint2 sl2 = make_uint2(0u, ~0u);
+    uint4 en2 = make_uint4(0u, 0u, 0u, 0u);
     if (i < nslots) {                                // the next slot on its way during this one's sum
       sl2 = tb.slot[pre.slot + i];
       en2 = tb.ent[pre.slot + i];
     }
     const unsigned first = sl.x & 0xFFFFu, n = (sl.x >> 16) & 0x1FFFu, lg = sl.x >> 29;
-    const unsigned r[LIST_AHEAD] = {en.x & 0xFFFFu, en.x >> 16, en.y & 0xFFFFu, en.y >> 16, idx[0], idx[1], idx[2], idx[3]};
+    const unsigned e[ENT / 2] = {en.x, en.y, en.z, en.w};
     double s = 0.0;
 #pragma unroll
-    for (int q = 0; q < LIST_AHEAD; ++q) s += (unsigned)q < n ? runs[r[q]] : 0.0;
-    for (unsigned q = LIST_AHEAD; q < n; ++q) s += runs[list[first + (q << lg)]];
+    for (int q = 0; q < ENT; ++q) s += (unsigned)q < n ? runs[q & 1 ? e[q / 2] >> 16 : e[q / 2] & 0xFFFFu] : 0.0;
+    for (unsigned q = ENT; q < n; ++q) s += runs[list[first + (q << lg)]];
     // the slots are sorted by lanes per bin, most first, so the wave's first lane has the largest
     const int lgw = __builtin_amdgcn_readfirstlane((int)lg);
     for (int o = 1 << lgw >> 1; o > 0; o >>= 1) {
@@ -534,7 +527,6 @@ __device__ __forceinline__ void tile_bins(float2* lds, const TileBinDev& tb, con
     if (sl.y != ~0u) out[sl.y] = s;
     sl = sl2;
     en = en2;
-    if (i < nslots) ahead();
   }
 }
 

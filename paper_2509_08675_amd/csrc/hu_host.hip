@@ -32,8 +32,8 @@ struct TileHost {
   std::vector<uint32_t> toff, coff, cpos, wpos;   // wpos: the inverse of cpos
   int nloc_max = 0;
   // the device tables of TileBinDev
-  std::vector<uint2> seg, slot, ent;
-  std::vector<uint4> info;
+  std::vector<uint2> seg, slot;
+  std::vector<uint4> info, ent;
   std::vector<uint16_t> list;
   std::vector<uint32_t> dst;
   int runs_max = 0;
@@ -724,14 +724,14 @@ void tile_runs(const Axis0Geom& a, int C, bool sym, TileHost* th) {
           const uint16_t* e = lst + off[j] + u;
           th->slot.push_back(make_uint2((uint32_t)(off[j] + u) | (uint32_t)n << 16 | (uint32_t)lg << 29, u == 0 ? wp[j] : ~0u));
           uint32_t q[4] = {0u, 0u, 0u, 0u};
-          for (int i = 0; i < 4 && i < n; ++i) q[i] = e[i * G];
-          th->ent.push_back(make_uint2(q[0] | q[1] << 16, q[2] | q[3] << 16));
+          for (int i = 0; i < 8 && i < n; ++i) q[i / 2] |= (uint32_t)e[i * G] << (16 * (i & 1));
+          th->ent.push_back(make_uint4(q[0], q[1], q[2], q[3]));
         }
       }
     }
     while ((th->slot.size() - s0) % 64) {
       th->slot.push_back(make_uint2(0u, ~0u));
-      th->ent.push_back(make_uint2(0u, 0u));
+      th->ent.push_back(make_uint4(0u, 0u, 0u, 0u));
     }
     th->info[t] = make_uint4((uint32_t)l0, (uint32_t)s0, (uint32_t)(th->slot.size() - s0), 0u);
   }
@@ -846,8 +846,8 @@ int get_tilebins(const Geom& g, const hu_bins& bins, int C, TileBinDev* out) {
   }
   if (C < 1) return HU_ERR_SIZE;
   const std::shared_ptr<TileHost> th = tile_host(g, bins, C);
-  uint2 *seg = nullptr, *slot = nullptr, *ent = nullptr;
-  uint4* info = nullptr;
+  uint2 *seg = nullptr, *slot = nullptr;
+  uint4 *info = nullptr, *ent = nullptr;
   uint16_t* list = nullptr;
   uint32_t *coff = nullptr, *dst = nullptr;
   HU_TRY(upload(th->seg, &seg));

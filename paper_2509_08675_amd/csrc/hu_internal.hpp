@@ -141,7 +141,7 @@ struct TileBinDev {
   const uint2* slot;       // one per summing lane: x: first entry (relative to the tile) | entries << 16 | log2 lanes << 29,
                            // y: where the partial is stored (the bin's first lane), or ~0; a bin's lanes are adjacent and
                            // aligned, take every (lanes)-th entry and add up by a fixed butterfly
-  const uint2* ent;        // the slot's first four entries, 16 bits each: known without a look at the list
+  const uint4* ent;        // the slot's first eight entries, 16 bits each: known without a look at the list
   const uint16_t* list;    // runs of each bin of the tile, bin after bin
   const uint32_t* dst;     // where many runs are alone in their bin: of every run the place of its partial, or ~0 (the bin
                            // has slots, which sum it); null: every bin has slots

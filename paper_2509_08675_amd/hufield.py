@@ -454,7 +454,7 @@ def debug_bin_tables(dims, bins, variant=0):
 
 def debug_bin_runs(dims, bins, variant=0):
     """The host-built run tables of the binning (no device work): dict with ntiles, threads, E, runs_max, sym and the
-    arrays seg [ntiles, threads, 2], info [ntiles, 4], slot [lanes, 2], ent [lanes, 4], list [runs], dst [runs] or
+    arrays seg [ntiles, threads, 2], info [ntiles, 4], slot [lanes, 2], ent [lanes, 8], list [runs], dst [runs] or
     None (layout: hu_debug_bin_runs in hufield.h)."""
     import numpy as np
     d, b = make_dims(dims), make_bins(bins)
@@ -465,7 +465,7 @@ def debug_bin_runs(dims, bins, variant=0):
     seg = np.empty((ntiles, threads, 2), np.uint32)
     info = np.empty((ntiles, 4), np.uint32)
     slot = np.empty((lanes, 2), np.uint32)
-    ent = np.empty((lanes, 4), np.uint16)
+    ent = np.empty((lanes, 8), np.uint16)
     lst = np.empty(runs, np.uint16)
     dst = np.empty(runs, np.uint32) if direct else None
     _check(_lib.hu_debug_bin_runs(d, b, int(variant), None, seg.ctypes.data, info.ctypes.data, slot.ctypes.data,

@@ -243,7 +243,7 @@ def test_run_tables(hf, dims, bins, variant):
                 xu, pu = (int(v) for v in r["slot"][s0 + i + u])
                 assert xu >> 29 == lg and (u == 0 or pu == NONE)
                 mine = [int(lst[(xu & 0xFFFF) + (q << lg)]) for q in range(xu >> 16 & 0x1FFF)]
-                assert [int(v) for v in r["ent"][s0 + i + u][:len(mine)]] == mine[:4]
+                assert [int(v) for v in r["ent"][s0 + i + u][:len(mine)]] == mine[:8]
                 seen += mine
                 for m in mine:
                     part[u] += runs[m]
