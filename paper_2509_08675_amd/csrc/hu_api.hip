@@ -263,7 +263,7 @@ int hu_power_spectrum(hu_dims dims, int32_t batch, const void* x, int32_t dtype,
     if (c) ra.fill[fs++] = FillSpan{reinterpret_cast<uint32_t*>(c), reinterpret_cast<const uint32_t*>(geo.counts), 2 * nb};
     ra.fill_spans = fs;
     const int src = dtype == HU_F32 ? SRC_F32 : SRC_I8;
-    HU_HIP(timed("rows_r2c_load", st, [&] { return launch_rows_r2c(Lrow, src, 0, ra, B, st); }));
+    HU_HIP(timed("rows_r2c_load", st, [&] { return launch_rows_load(Lrow, src, ra, B, st); }));
     if (g.nd == 3) {
       ColsArgs cy{};
       cy.spec = spec;
@@ -482,7 +482,7 @@ int hu_spectrum_grad(hu_dims dims, const hu_filter* filt, uint64_t seed, hu_bins
   float2* spec = reinterpret_cast<float2*>(w + lay.spec);
 
   // the noise spectrum W, transformed along every axis but axis 0 (as in the generator)
-  RowsArgs ra{};
+  RowsNoiseArgs ra{};
   ra.spec = spec;
   ra.Nh = g.Nhp;
   ra.tiled = g.tiled;
@@ -492,7 +492,7 @@ int hu_spectrum_grad(hu_dims dims, const hu_filter* filt, uint64_t seed, hu_bins
   ra.tw = tw_row;
   ra.tw2 = tw2_row;
   ra.fill_spans = 0;
-  HU_HIP(timed("rows_r2c_noise", st, [&] { return launch_rows_r2c(Lrow, SRC_NOISE, 0, ra, 1, st); }));
+  HU_HIP(timed("rows_r2c_noise", st, [&] { return launch_rows_noise(Lrow, 0, ra, 1, st); }));
   if (g.nd == 3) {
     ColsArgs cy{};
     cy.spec = spec;
@@ -547,7 +547,7 @@ int hu_window_variance(hu_dims dims, int32_t batch, const void* x, int32_t dtype
     ra.tw2 = tw2_row;
     ra.fill_spans = 0;
     const int src = dtype == HU_F32 ? SRC_F32 : SRC_I8;
-    HU_HIP(timed("rows_r2c_load", st, [&] { return launch_rows_r2c(Lrow, src, 0, ra, B, st); }));
+    HU_HIP(timed("rows_r2c_load", st, [&] { return launch_rows_load(Lrow, src, ra, B, st); }));
     if (g.nd == 3) {
       ColsArgs cy{};
       cy.spec = spec;
@@ -665,7 +665,7 @@ int hu_two_point(hu_dims dims, int32_t batch, const int8_t* pm1, float* s2, void
     ra.tw = tw_row;
     ra.tw2 = tw2_row;
     ra.fill_spans = 0;
-    HU_HIP(timed("rows_r2c_load", st, [&] { return launch_rows_r2c(Lrow, SRC_I8, 0, ra, B, st); }));
+    HU_HIP(timed("rows_r2c_load", st, [&] { return launch_rows_load(Lrow, SRC_I8, ra, B, st); }));
     ColsArgs cy{};
     if (g.nd == 3) {
       cy.spec = spec;

@@ -1051,7 +1051,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
   }
 
   // pass A: noise -> R2C rows; block 0 of each field sets up that field's bin counts
-  RowsArgs ra{};
+  RowsNoiseArgs ra{};
   ra.spec = spec;
   ra.Nh = g.Nhp;
   ra.tiled = g.tiled;
@@ -1073,7 +1073,7 @@ int enqueue_class(const ClassRun& r, hipStream_t st) {
     ra.tw_y = tw_y0;
     HU_HIP(timed("plane_fwd", st, [&] { return launch_plane_fwd(Lrow, g.n[1], ra, g.n[0], B, st); }));
   } else {
-    HU_HIP(timed("rows_r2c_noise", st, [&] { return launch_rows_r2c(Lrow, SRC_NOISE, plan.v[P_R2C], ra, B, st); }));
+    HU_HIP(timed("rows_r2c_noise", st, [&] { return launch_rows_noise(Lrow, plan.v[P_R2C], ra, B, st); }));
   }
 
   ColsArgs cy{};

@@ -69,7 +69,6 @@ struct RowsArgs {
   float2* spec;            // half spectrum, [B][Nh] (Nh: per-field stride, padded layout)
   long long Nh, N, nrows;  // per field
   int tiled;               // 2D column-group layout (TW = 4) or row-major (3D)
-  uint64_t seeds[MAX_CHUNK];
   const FieldIO* io;       // per-field seeds and accumulators (batch path) or null
   int nb;                  // with io: bins + 1, for the per-field bin counts
   const uint32_t* cnt_src; // with io: precomputed bin counts (nb uint64)
@@ -79,6 +78,10 @@ struct RowsArgs {
   FillSpan fill[6];
   int fill_spans;
   const float2* tw_y;      // plane kernels (3D): stage table of n_y
+};
+// The noise source's arguments carry the seeds (2 KB, which a launch that loads its rows need not copy).
+struct RowsNoiseArgs : RowsArgs {
+  uint64_t seeds[MAX_CHUNK];
 };
 
 struct ColsArgs {
@@ -377,7 +380,9 @@ hipError_t launch_grad_coef(const GradCoefArgs& a, hipStream_t st);
 hipError_t launch_spectrum_loss(const LossArgs& a, hipStream_t st);
 hipError_t launch_grad_final(const GradFinalArgs& a, hipStream_t st);
 hipError_t launch_filter_spectrum(const FilterSpecArgs& a, hipStream_t st);
-hipError_t launch_rows_r2c(int L, int src, int variant, const RowsArgs& a, int batch, hipStream_t st);
+// the first row pass from stored fields (SRC_F32, SRC_I8), and from noise
+hipError_t launch_rows_load(int L, int src, const RowsArgs& a, int batch, hipStream_t st);
+hipError_t launch_rows_noise(int L, int variant, const RowsNoiseArgs& a, int batch, hipStream_t st);
 // radix: the alternative radix list of L where it has one (Plan<L, 1>)
 hipError_t launch_cols(int L, bool inv, int variant, const ColsArgs& a, hipStream_t st, int radix = 0);
 // split: the split exchange (real and imaginary parts in two rounds, half the LDS), lengths >= 192
@@ -402,7 +407,7 @@ size_t small_lds_bytes(int LR, int N0, int nb);
 // the plane kernels of 3D grids (hu_plane.hip) for row half-length LR and n_y = NY; their LDS (0:
 // no instantiation for the shape); grid (n0 planes, batch)
 size_t plane_lds_bytes(int LR, int NY);
-hipError_t launch_plane_fwd(int LR, int NY, const RowsArgs& a, int n0, int batch, hipStream_t st);
+hipError_t launch_plane_fwd(int LR, int NY, const RowsNoiseArgs& a, int n0, int batch, hipStream_t st);
 hipError_t launch_plane_inv(int LR, int NY, const RowsZArgs& a, bool thresh, int n0, int batch, hipStream_t st);
 hipError_t launch_field_lds(int LR, int N0, const SmallArgs& a, int batch, hipStream_t st);
 hipError_t launch_threshold(const ThreshArgs& a, int batch, hipStream_t st);

@@ -141,7 +141,7 @@ __device__ __forceinline__ void plane_copy(float2* __restrict__ dst_hbm, const f
 
 // grid (n0 planes, B fields)
 template <int LR, int NY>
-__global__ void __launch_bounds__((PlaneShape<LR, NY>::T)) k_plane_fwd(RowsArgs a) {
+__global__ void __launch_bounds__((PlaneShape<LR, NY>::T)) k_plane_fwd(RowsNoiseArgs a) {
   using S = PlaneShape<LR, NY>;
   constexpr int PR = S::PR, ER = S::ER, T = S::T, RSR = S::RSR, NX = 2 * LR;
   using RadR = typename Plan<LR>::fwd;
@@ -290,7 +290,7 @@ __global__ void __launch_bounds__((PlaneShape<LR, NY>::T)) k_plane_inv(RowsZArgs
 }
 
 template <int LR, int NY>
-static hipError_t launch_plane_fwd_L(const RowsArgs& a, int n0, int batch, hipStream_t st) {
+static hipError_t launch_plane_fwd_L(const RowsNoiseArgs& a, int n0, int batch, hipStream_t st) {
   using S = PlaneShape<LR, NY>;
   hipLaunchKernelGGL((k_plane_fwd<LR, NY>), dim3(n0, batch), dim3(S::T), S::lds_bytes, st, a);
   return hipGetLastError();
@@ -304,7 +304,7 @@ static hipError_t launch_plane_inv_L(const RowsZArgs& a, bool thresh, int n0, in
   return hipGetLastError();
 }
 
-hipError_t launch_plane_fwd(int LR, int NY, const RowsArgs& a, int n0, int batch, hipStream_t st) {
+hipError_t launch_plane_fwd(int LR, int NY, const RowsNoiseArgs& a, int n0, int batch, hipStream_t st) {
   switch (LR * 1000 + NY) {
 #define X(A, B) case A * 1000 + B: return launch_plane_fwd_L<A, B>(a, n0, batch, st);
     HU_PLANE_SHAPES(X)

@@ -263,8 +263,16 @@ __device__ __forceinline__ void tile_geom(long long row0, long long nrows, unsig
 }
 
 // grid (ceil(nrows / C), B), block C * P; thread (c, p) = (tid / P, tid % P) transforms row c.
+template <int SRC>
+struct RowsSrc {
+  using Args = RowsArgs;
+};
+template <>
+struct RowsSrc<SRC_NOISE> {
+  using Args = RowsNoiseArgs;
+};
 template <int L, int SRC, bool TILED, int V>
-__global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_r2c(RowsArgs a) {
+__global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_r2c(typename RowsSrc<SRC>::Args a) {
   constexpr int P = Plan<L>::P, E = Plan<L>::E, C = RowTile<L, V>::C, T = RowTile<L, V>::T;
   constexpr int RS = RowTile<L, V>::RS;
   using Rad = typename Plan<L>::fwd;
@@ -565,29 +573,30 @@ __global__ void __launch_bounds__((RowTile<L, V>::T)) k_rows_c2r(RowsZArgs a) {
 
 static inline unsigned ceil_div_u(long long a, long long b) { return (unsigned)((a + b - 1) / b); }
 
-template <int L, int SRC, bool TILED, int V>
-static hipError_t launch_rows_r2c_L(const RowsArgs& a, int batch, hipStream_t st) {
+template <int L, int SRC, int V>
+static hipError_t launch_rows_r2c_L(const typename RowsSrc<SRC>::Args& a, int batch, hipStream_t st) {
   constexpr int C = RowTile<L, V>::C, T = RowTile<L, V>::T;
   dim3 grid(ceil_div_u(a.nrows, C), batch);
   constexpr size_t lds = (size_t)C * RowTile<L, V>::RS * sizeof(float2);
-  hipLaunchKernelGGL((k_rows_r2c<L, SRC, TILED, V>), grid, dim3(T), lds, st, a);
+  if (a.tiled) hipLaunchKernelGGL((k_rows_r2c<L, SRC, true, V>), grid, dim3(T), lds, st, a);
+  else hipLaunchKernelGGL((k_rows_r2c<L, SRC, false, V>), grid, dim3(T), lds, st, a);
   return hipGetLastError();
 }
 
-template <int L, int SRC>
-static hipError_t launch_rows_r2c_S(int variant, const RowsArgs& a, int batch, hipStream_t st) {
-  if (variant)
-    return a.tiled ? launch_rows_r2c_L<L, SRC, true, 1>(a, batch, st) : launch_rows_r2c_L<L, SRC, false, 1>(a, batch, st);
-  return a.tiled ? launch_rows_r2c_L<L, SRC, true, 0>(a, batch, st) : launch_rows_r2c_L<L, SRC, false, 0>(a, batch, st);
+hipError_t launch_rows_noise(int L, int variant, const RowsNoiseArgs& a, int batch, hipStream_t st) {
+  switch (L) {
+#define X(LL) \
+  case LL: return variant ? launch_rows_r2c_L<LL, SRC_NOISE, 1>(a, batch, st) : launch_rows_r2c_L<LL, SRC_NOISE, 0>(a, batch, st);
+    HU_ROW_LENGTHS(X)
+#undef X
+    default: return hipErrorInvalidValue;
+  }
 }
 
-hipError_t launch_rows_r2c(int L, int src, int variant, const RowsArgs& a, int batch, hipStream_t st) {
+hipError_t launch_rows_load(int L, int src, const RowsArgs& a, int batch, hipStream_t st) {
   switch (L) {
-#define X(LL)                                                                                 \
-  case LL:                                                                                    \
-    if (src == SRC_NOISE) return launch_rows_r2c_S<LL, SRC_NOISE>(variant, a, batch, st);     \
-    if (src == SRC_F32) return launch_rows_r2c_S<LL, SRC_F32>(0, a, batch, st);               \
-    return launch_rows_r2c_S<LL, SRC_I8>(0, a, batch, st);
+#define X(LL) \
+  case LL: return src == SRC_F32 ? launch_rows_r2c_L<LL, SRC_F32, 0>(a, batch, st) : launch_rows_r2c_L<LL, SRC_I8, 0>(a, batch, st);
     HU_ROW_LENGTHS(X)
 #undef X
     default: return hipErrorInvalidValue;

@@ -37,8 +37,8 @@ def code_objects(blob):
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """{mangled name: (vector registers, bytes of scratch per lane)} of every kernel."""
+def metadata(tmp_path_factory):
+    """{mangled name: (vector registers, bytes of scratch per lane, bytes of arguments)} of every kernel."""
     path = str(tmp_path_factory.mktemp("co") / "k.o")
     out = {}
     with open(LIB, "rb") as fh:
@@ -51,8 +51,19 @@ def kernels(tmp_path_factory):
             name = re.search(r"^    \.name: +(\S+)", entry, flags=re.M).group(1)
             regs = int(re.search(r"^    \.vgpr_count: +(\d+)", entry, flags=re.M).group(1))
             scratch = int(re.search(r"^    \.private_segment_fixed_size: +(\d+)", entry, flags=re.M).group(1))
-            out[name] = (regs, scratch)
+            args = int(re.search(r"^    \.kernarg_segment_size: +(\d+)", entry, flags=re.M).group(1))
+            out[name] = (regs, scratch, args)
     return out
+
+
+@pytest.fixture(scope="module")
+def kernels(metadata):
+    return {name: use[:2] for name, use in metadata.items()}
+
+
+@pytest.fixture(scope="module")
+def co_args(metadata):
+    return {name: use[2] for name, use in metadata.items()}
 
 
 def filter_kernels(kernels, amp):
@@ -89,3 +100,21 @@ def test_no_kernel_that_nothing_launches(kernels):
         for r in rx:
             m = r.search(name)
             assert m is None or int(m.group(1)) > 1024, name
+
+
+def test_loading_row_passes_carry_no_seeds(co_args):
+    # the launch copies a kernel's arguments: 2 KB of seeds belong to the noise source alone
+    rx = re.compile(r"k_rows_r2cILi\d+ELi(\d)E")
+    sizes = {0: [], 1: [], 2: []}
+    for name, n in co_args.items():
+        m = rx.search(name)
+        if m:
+            sizes[int(m.group(1))].append(n)
+    assert min(sizes[0]) >= 2048 and sizes[1] and max(sizes[1] + sizes[2]) < 768
+
+
+def test_host_and_device_agree_on_kernel_names(kernels):
+    # a launch looks its kernel up by name: every name that the host code holds is in a code object
+    with open(LIB, "rb") as fh:
+        held = {m.decode() for m in re.findall(rb"_ZN2hu\d+k_\w+", fh.read())}
+    assert held and held <= set(kernels)
