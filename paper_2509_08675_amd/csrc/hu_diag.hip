@@ -88,8 +88,8 @@ __global__ void __launch_bounds__(256) k_wvar_table(WvarTabArgs a) {
 // the form factors.  Those, not memory, bound the pass (about 50 instructions each): evaluated per
 // mode it took 290 us for 16 x 2048^2 and 8 radii.  TAB: read from a table instead, evaluated once for
 // the fields of the launch; the fields of a tile run on one XCD, whose L2 then serves the table (both
-// kernels 113 us).  Each further eight radii are a table and a launch more, the transform with them (16 radii
-// 322 us for the call, where one launch that evaluated all of them took 637).
+// kernels 113 us).  Otherwise all pairs of a radius in flight at once: two at a time left the transcendentals'
+// latency open (3 x 128^3 57 -> 51 us a call, 512^2 31 -> 27, 48 x 64^2 28.2 -> 24.6).
 template <int L, int NDIM, bool TAB>
 __global__ void __launch_bounds__((ColTile<L, 0>::T)) k_cols_wvar(WvarArgs a) {
   constexpr int P = Plan<L>::P, E = Plan<L>::E, C = ColTile<L, 0>::C, T = ColTile<L, 0>::T, H = E / 2;
@@ -151,7 +151,7 @@ __global__ void __launch_bounds__((ColTile<L, 0>::T)) k_cols_wvar(WvarArgs a) {
       acc += (double)(xa[H] * wc[H]);
     } else {
       const float R = a.radii[j];
-#pragma unroll 2
+#pragma unroll
       for (int k = 0; k < H; ++k) {
         const float w2 = window_w2<NDIM>(kk[k] * R);
         acc += (double)(xa[k] * w2) + (double)(xb[k] * w2);

@@ -341,16 +341,21 @@ struct WvarArgs {
   const float* tab;        // room for the form factors of nr <= WVAR_TAB_RADII radii, or null: evaluated in the pass
 };
 
-// The squared form factors of the radii of one launch, [radius][tile][pair][thread].  Where the table pays, in
-// 2D: from four fields on (its kernel takes about as long as the evaluation for two: 6 x 512^2, 8 radii, 39 ->
-// 28 us), and for fewer than 2^23 modes of all fields from a few radii on, since its kernel is a launch of 2-5 us
-// (5 x 1024^2: 1 radius 30.1 us with it, 28.6 without, 3 radii 32.5 and 34.4; 12 x 384 x 768: 1 radius 37.5 and 32.9,
-// 4 radii even; 5 x 128^2: 20.3 and 17.0, even from 5 on).  In 3D a form factor is cheaper and the table as large
-// as the spectra of four fields: 4 x 256^3 took 169 us with it, the pairs evaluated in the pass about 145.
+// The squared form factors of the radii of one launch, [radius][tile][pair][thread].  It pays in 2D from four
+// fields on (its kernel takes about as long as the evaluation for two), and there where the evaluation that it
+// saves is longer than its kernel, a launch of 2-5 us: below 2^23 modes of all fields for five to eight radii (60 x
+// 512^2: 8 radii 69 us with it, 76 without, 4 radii 61 and 60, 2 radii 56 and 53), from there on for four too, and
+// for any number from 5 2^21 on (16 x 2048^2: 2 radii 178 and 185, 8 radii 215 and 256).  More than eight radii
+// need a table and the whole pass again for each further eight, where one launch evaluates all of them: worth
+// it only for the largest batches and a group at least half full (16 radii: 16 x 2048^2 325 and 365, 4 x 2048^2 126
+// and 122; 9 radii: 282 and 267, 100 and 87).  In 3D a form factor is cheaper and the table as large as the spectra
+// of four fields: a call on 4 x 256^3 took 367 us with it, 321 with the pairs evaluated in the pass.
 constexpr int WVAR_TAB_RADII = 8, WVAR_TAB_BATCH = 4;
 inline bool wvar_table(int ndim, int batch) { return ndim == 2 && batch >= WVAR_TAB_BATCH; }
 inline bool wvar_table_pays(long long modes, int radii) {
-  return modes >= (1LL << 23) || radii >= (modes >= (1LL << 21) ? 3 : 4);
+  const int rest = radii % WVAR_TAB_RADII;
+  if (modes >= (5LL << 21)) return radii <= WVAR_TAB_RADII || rest == 0 || rest >= WVAR_TAB_RADII / 2;
+  return radii <= WVAR_TAB_RADII && radii >= (modes >= (1LL << 23) ? 4 : 5);
 }
 struct WvarTabArgs {
   Axis0Geom gm;

@@ -130,20 +130,37 @@ def test_window_variance_table_matches_single_fields(hf, dims, batch, kind):
     np.testing.assert_allclose(a[0].cpu().numpy(), ref, rtol=2e-5, atol=0.0)
 
 
-# Few radii are evaluated in the pass; a workspace without room for the table takes that path for any number.
+# Form factors from the table or evaluated in the pass, by the number of radii; a workspace without room for the
+# table takes the second path for any number.
 @pytest.mark.parametrize("dims,batch", [((64, 96), 5), ((24, 48), 9), ((1024, 512), 9)])
-def test_window_variance_of_few_radii(hf, dims, batch):
+def test_window_variance_by_number_of_radii(hf, dims, batch):
     _say("variance, few radii", dims, batch)
     x = torch.from_numpy(np.stack([W.random_field(dims, s) for s in range(batch)])).cuda()
     full = hf.alloc_workspace(hf.HU_OP_WINDOW_VARIANCE, dims, batch)
     radii = [1.0, 0.5, 3.0, 7.5, 2.0, 4.0, 6.0, 9.0, 11.0]
     ref = O.window_variance(x[0].double().cpu().numpy(), radii)
-    for n in (1, 2, 3, 4, 8, 9):
+    for n in (1, 4, 5, 8, 9):
         a = hf.window_variance(x, radii[:n], work=full)
         b = hf.window_variance(x, radii[:n], work=full[:full.numel() - 256])
         torch.cuda.synchronize()
         assert torch.equal(a, b), n
         np.testing.assert_allclose(a[0].cpu().numpy(), ref[:n], rtol=2e-5, atol=0.0)
+
+
+# A large batch (2^23 modes and more) takes a table and a launch for each eight radii.
+def test_window_variance_table_of_many_radii(hf):
+    dims, batch = (2048, 1024), 10
+    _say("variance, many radii", dims, batch)
+    x = torch.randn((batch,) + dims, device="cuda", generator=torch.Generator("cuda").manual_seed(1))
+    full = hf.alloc_workspace(hf.HU_OP_WINDOW_VARIANCE, dims, batch)
+    radii = [0.5 + 1.5 * i for i in range(12)]
+    for n in (2, 9, 12):
+        a = hf.window_variance(x, radii[:n], work=full)
+        b = hf.window_variance(x, radii[:n], work=full[:full.numel() - 256])
+        torch.cuda.synchronize()
+        assert torch.equal(a, b), n
+    c = hf.window_variance(x[3:4], radii)
+    np.testing.assert_allclose(a[3].cpu().numpy(), c[0].cpu().numpy(), rtol=1e-13, atol=0.0)
 
 
 # Expected spectrum: 3D columns of a multiple of 32 modes (pairs), other columns, FP64 filter.
