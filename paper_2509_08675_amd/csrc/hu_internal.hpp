@@ -17,8 +17,9 @@ constexpr bool split_length(int L) { return L >= 192; }
 constexpr bool half_tile_length(int L) { return L <= 1024; }
 
 // column lengths whose binning threads may store a run that is alone in its bin themselves (TileBinDev::dst).
-// Not the longer ones: their runs are longer, and the code alone costs 16 x 2048^2 488 -> 496 us.
-constexpr bool direct_length(int L) { return L <= 512; }
+// Not the longer ones: their runs are longer, and the code alone costs 16 x 2048^2 488 -> 496 us a pipeline and
+// 70 x 384^2 50.1 -> 51.2 a spectrum.
+constexpr bool direct_length(int L) { return L <= 256; }
 
 
 enum { SRC_NOISE = 0, SRC_F32 = 1, SRC_I8 = 2 };

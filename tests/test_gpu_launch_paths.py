@@ -53,8 +53,8 @@ def test_binning_edges(hf, dims, bins):
         np.testing.assert_allclose(s[i].cpu().numpy(), rs, rtol=1e-5, atol=1e-6 * rs.max())
 
 
-# Runs alone in their bin, stored by the threads that form them (2D, angular bins, columns up to 512): every mode
-# a run of its own, columns of each element count, a tile's last columns missing, and the first length without.
+# Runs alone in their bin, stored by the threads that form them (2D, angular bins, columns up to 256): every mode
+# a run of its own, columns of each element count, a tile's last columns missing, and longer columns.
 @pytest.mark.parametrize("dims,bins", [((4, 32), (64, 36)), ((12, 24), (40, 60)), ((24, 48), (64, 36)), ((48, 16), (128, 36)),
                                        ((64, 6), (90, 91)), ((96, 96), (128, 36)), ((256, 64), (128, 60)), ((512, 24), (128, 63)),
                                        ((768, 16), (128, 63))])
