@@ -78,6 +78,7 @@ def algorithmic_bytes(dims, batch):
         "cols_y_inv": 2 * t,
         "rows_c2r_thresh": 2 * t + 5 * N * batch,   # read S, write S(+-1), field f32 and map int8
         "cols_bin": t,                     # read only
+        "amp": 4 * Nh,                     # one filter's amplitudes, for all fields
     }
     if len(dims) == 2:
         total = 6 * t + 5 * N * batch
