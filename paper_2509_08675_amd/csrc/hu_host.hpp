@@ -75,7 +75,8 @@ int check_bins(const hu_bins* b, int nd);
 bool aligned(const void* p, size_t a);
 // 2D grids with columns of up to 1024: the filter and binning passes take half-width tiles under either
 // plan entry.  Half the LDS and twice the workgroups per tile row: 60 fields of 1024^2 424 -> 393 us, of
-// 512^2 164 -> 151, one of 1024^2 55 -> 50, of 384 x 192 69 -> 62 (every size from 64^2 gains).  Not at 2048,
+// 512^2 164 -> 151, one of 1024^2 55 -> 50, of 384 x 192 69 -> 62 (every size from 64^2 gains, with 24 to 64 radial bins; with
+// thousands of bins a tile has nearly one partial per mode at either width).  Not at 2048,
 // where two columns would use 16 of every 32 bytes of the layout (one field 80 -> 89 us), nor in 3D (even).
 // A rule of the grid alone, so that the bins stay the same bits over all batch sizes.
 inline bool half_tiles(const Geom& g) { return g.nd == 2 && half_tile_length(g.n[0]); }

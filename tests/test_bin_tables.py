@@ -4,9 +4,11 @@
   angular edges), up to the full 2048^2 / 128 x 36 layout;
 * each tile's partials are its distinct bins in ascending order, every mode points at its bin's
   slot, and the per-bin lists (CSR) hold every partial once, in tile order;
-* the integer combination of a tile's runs (the kernels' scheme, emulated here with Python
-  integers) gives the same bits for any order of the runs, and the spectrum assembled from the
-  partials in CSR order equals the direct FP64 sum to rounding.
+* the run tables of the axis-0 passes, walked as the kernels do, list every run once and store every
+  partial once, and the spectrum is the sum over the modes;
+* the integer combination of runs (the scheme of the whole-field kernel and of the expected spectrum,
+  emulated here with Python integers) gives the same bits for any order of the runs, and the spectrum
+  assembled from the partials in CSR order equals the direct FP64 sum to rounding.
 """
 
 import math
